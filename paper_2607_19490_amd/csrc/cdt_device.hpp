@@ -70,20 +70,19 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
+constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
+
+__device__ __forceinline__ Words4 philox_round(Words4 c, uint32_t k0, uint32_t k1) {
+    const uint64_t p0 = static_cast<uint64_t>(kPhiloxM0) * c.x;
+    const uint64_t p1 = static_cast<uint64_t>(kPhiloxM1) * c.z;
+    return Words4{xor3(static_cast<uint32_t>(p1 >> 32), c.y, k0), static_cast<uint32_t>(p1),
+                  xor3(static_cast<uint32_t>(p0 >> 32), c.w, k1), static_cast<uint32_t>(p0)};
+}
+
 __device__ __forceinline__ Words4 philox10(Words4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c.x;
-        const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c.z;
-        Words4 n;
-        n.x = xor3(static_cast<uint32_t>(p1 >> 32), c.y, k0);
-        n.y = static_cast<uint32_t>(p1);
-        n.z = xor3(static_cast<uint32_t>(p0 >> 32), c.w, k1);
-        n.w = static_cast<uint32_t>(p0);
-        c = n;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
-    }
+    for (uint32_t r = 0; r < 10; ++r) c = philox_round(c, k0 + r * kPhiloxW0, k1 + r * kPhiloxW1);
     return c;
 }
 
@@ -103,14 +102,89 @@ __host__ __device__ constexpr uint32_t stream_tag(uint32_t stream, uint32_t id) 
     return (stream << 24) | (id & 0xFFFFFFu);
 }
 
+// A wave-uniform value held in a vector register.  A two-operand VALU
+// instruction issues in 2 cycles when both operands are vector registers and
+// in 4 with a scalar one (measured: v_xor_b32 2.6 against 4.4 cycles per
+// wave64 instruction and SIMD, launch included), so the few constants that
+// every Philox call XORs once are worth a register each.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
+// The draws of one (canary, shard) block.  The live passes spend most of
+// their time in philox10's rounds, and the counters (q, c, s, tag) of a
+// block's draws differ in few words, so the first three rounds are taken
+// apart by what they depend on (round outputs x, y, z, w, round keys k0, k1):
+//   round 0: x1, y1 from (c, s): uniform; z1 = hi(M0 q) ^ tag ^ k1, w1 = lo(M0 q);
+//   round 1: x2 = hi(M1 z1) ^ y1 ^ k0, y2 = lo(M1 z1);
+//            z2 = hi(M0 x1) ^ w1 ^ k1, which no tag enters, w2 = lo(M0 x1): uniform;
+//   round 2: x3 = hi(M1 z2) ^ y2 ^ k0, y3 = lo(M1 z2) (no tag), z3 = hi(M0 x2) ^ w2 ^ k1,
+//            w3 = lo(M0 x2).
+// BlockDraw holds the uniform parts, DrawBase what depends on q alone (two of
+// the 18 multiplies left per call, shared by every stream and run drawn at
+// the same q), and finish_draw does the rest: 16 multiplies, 14 three-operand
+// XORs and 4 two-operand ones (before: 18 and 19).  Same words as draw().
+// With irwin_hall4's subtraction the 16 x 128 x 256 x 8192 step of three runs
+// takes 18.6 ms (18.96 ms), a Student-t run of 16 x 128 x 128 x 4096 with its
+// Eq. 4 4.19 ms (4.31 ms), the fused pass of 32 x 32 x 64 x 8192 631 us (646).
+struct BlockDraw {
+    uint32_t k0, k1;          // the key
+    uint32_t z2, x2, z3, x3;  // hi(M0 x1) ^ k1, y1 ^ k0, w2 ^ k1 and k0 of rounds 1, 1, 2, 2
+};
+
+struct DrawBase {
+    uint32_t h0;  // hi(M0 q)
+    uint32_t x3;  // hi(M1 z2) ^ k0 of round 2
+    uint32_t y3;  // lo(M1 z2)
+};
+
+__device__ __forceinline__ BlockDraw block_draw(Key k, uint32_t c, uint32_t s) {
+    const uint64_t p1 = static_cast<uint64_t>(kPhiloxM1) * s;
+    const uint32_t x1 = static_cast<uint32_t>(p1 >> 32) ^ c ^ k.k0;
+    const uint64_t p0 = static_cast<uint64_t>(kPhiloxM0) * x1;
+    BlockDraw b;
+    b.k0 = k.k0;
+    b.k1 = k.k1;
+    b.z2 = in_vgpr(static_cast<uint32_t>(p0 >> 32) ^ (k.k1 + kPhiloxW1));
+    b.x2 = in_vgpr(static_cast<uint32_t>(p1) ^ (k.k0 + kPhiloxW0));
+    b.z3 = in_vgpr(static_cast<uint32_t>(p0) ^ (k.k1 + 2 * kPhiloxW1));
+    b.x3 = in_vgpr(k.k0 + 2 * kPhiloxW0);
+    return b;
+}
+
+__device__ __forceinline__ DrawBase draw_base(const BlockDraw& b, uint32_t q) {
+    const uint64_t p0 = static_cast<uint64_t>(kPhiloxM0) * q;
+    const uint64_t p1 = static_cast<uint64_t>(kPhiloxM1) * (static_cast<uint32_t>(p0) ^ b.z2);
+    return DrawBase{static_cast<uint32_t>(p0 >> 32), static_cast<uint32_t>(p1 >> 32) ^ b.x3,
+                    static_cast<uint32_t>(p1)};
+}
+
+// tag_key: the stream's tag ^ the key's high word.
+__device__ __forceinline__ Words4 finish_draw(const BlockDraw& b, const DrawBase& d,
+                                              uint32_t tag_key) {
+    const uint64_t p1 = static_cast<uint64_t>(kPhiloxM1) * (d.h0 ^ tag_key);
+    const uint64_t p0 =
+        static_cast<uint64_t>(kPhiloxM0) * (static_cast<uint32_t>(p1 >> 32) ^ b.x2);
+    Words4 c{d.x3 ^ static_cast<uint32_t>(p1), d.y3, static_cast<uint32_t>(p0 >> 32) ^ b.z3,
+             static_cast<uint32_t>(p0)};
+#pragma unroll
+    for (uint32_t r = 3; r < 10; ++r)
+        c = philox_round(c, b.k0 + r * kPhiloxW0, b.k1 + r * kPhiloxW1);
+    return c;
+}
+
 // Unit normal stand-in: the Irwin-Hall sum of the four 16-bit halves of two
 // Philox words, centred (4 * 32767.5) and scaled by fp32(sqrt(3/(2^32-1))).
-// v_sad_u16(w, 0, acc) adds both 16-bit halves of w to acc; starting the
-// accumulator at -131070 (mod 2^32) leaves the centred sum n as an int32.
+// v_sad_u16(w, 0, acc) adds both 16-bit halves of w to acc.  The accumulator
+// starts at the bits of 1.5 * 2^23 less 131070, so it ends as the bits of the
+// float 1.5 * 2^23 + n (|n| <= 131070, one bit step is 1), and subtracting
+// 1.5 * 2^23 leaves n exactly: a 2-cycle subtraction for the 4-cycle int-to-
+// float conversion.
 __device__ __forceinline__ float irwin_hall4(uint32_t w0, uint32_t w1) {
-    const uint32_t centred =
-        __builtin_amdgcn_sad_u16(w0, 0u, __builtin_amdgcn_sad_u16(w1, 0u, 0u - 131070u));
-    return static_cast<float>(static_cast<int>(centred)) * 0x1.bb67aep-16f;
+    const uint32_t bits = __builtin_amdgcn_sad_u16(
+        w0, 0u, __builtin_amdgcn_sad_u16(w1, 0u, 0x4B400000u - 131070u));
+    return (__uint_as_float(bits) - 0x1.8p23f) * 0x1.bb67aep-16f;
 }
 
 // fp32 -> fp16 bits, IEEE round to nearest even (v_cvt_f16_f32 under the

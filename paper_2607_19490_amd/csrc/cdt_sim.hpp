@@ -13,13 +13,25 @@
 
 namespace cdt {
 
-// Eight unit normals of one stream for elements e0..e0+7 (e0 % 8 == 0):
-// Philox calls q = e0/2 .. e0/2+3, words (x, y) -> even element, (z, w) -> odd.
-__device__ __forceinline__ void normals8(Key key, uint32_t e0, uint32_t c, uint32_t s,
-                                         uint32_t tag, float z[8]) {
+// The Philox calls q = e0/2 .. e0/2 + 3 that the one-normal streams of
+// elements e0..e0+7 (e0 % 8 == 0) share, up to their tags.
+struct NormalBase {
+    DrawBase d[4];
+};
+
+__device__ __forceinline__ NormalBase normal_base(const BlockDraw& b, uint32_t e0) {
+    NormalBase n;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) n.d[k] = draw_base(b, (e0 >> 1) + k);
+    return n;
+}
+
+// Eight unit normals of one stream: words (x, y) -> even element, (z, w) -> odd.
+__device__ __forceinline__ void normals8(const BlockDraw& b, const NormalBase& n,
+                                         uint32_t tag_key, float z[8]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const Words4 w = draw(key, (e0 >> 1) + k, c, s, tag);
+        const Words4 w = finish_draw(b, n.d[k], tag_key);
         z[2 * k] = irwin_hall4(w.x, w.y);
         z[2 * k + 1] = irwin_hall4(w.z, w.w);
     }
@@ -31,7 +43,7 @@ struct SimArgs {
     uint32_t canary_base;  // global index of canary 0 (RNG counters)
     uint64_t chunks_per_block, total_chunks;
     Key key;
-    uint32_t tag_benign, tag_t12, tag_t3, tag_add, tag_flip;
+    uint32_t tag_benign, tag_t12, tag_t3, tag_add, tag_flip;  // stream tags ^ key.k1 (finish_draw)
     uint32_t block_mode, t3, tamper, clean;
     uint64_t mal_mask;
     float sigma_b;
@@ -51,11 +63,11 @@ inline SimArgs make_sim_args(const SimLaunch& p, uint64_t chunks_per_block,
     A.total_chunks = total_chunks;
     A.key = Key{static_cast<uint32_t>(p.seed), static_cast<uint32_t>(p.seed >> 32)};
     // An independent benign recompute draws its noise from the ALT streams.
-    A.tag_benign = stream_tag(p.redraw ? kStreamAlt : kStreamBenign, p.cfg_id);
-    A.tag_t12 = stream_tag(p.redraw ? kStreamAltT12 : kStreamT12, p.cfg_id);
-    A.tag_t3 = stream_tag(p.redraw ? kStreamAltT3 : kStreamT3, p.cfg_id);
-    A.tag_add = stream_tag(kStreamTamperAdd, p.cfg_id);
-    A.tag_flip = stream_tag(kStreamTamperFlip, p.cfg_id);
+    A.tag_benign = A.key.k1 ^ stream_tag(p.redraw ? kStreamAlt : kStreamBenign, p.cfg_id);
+    A.tag_t12 = A.key.k1 ^ stream_tag(p.redraw ? kStreamAltT12 : kStreamT12, p.cfg_id);
+    A.tag_t3 = A.key.k1 ^ stream_tag(p.redraw ? kStreamAltT3 : kStreamT3, p.cfg_id);
+    A.tag_add = A.key.k1 ^ stream_tag(kStreamTamperAdd, p.cfg_id);
+    A.tag_flip = A.key.k1 ^ stream_tag(kStreamTamperFlip, p.cfg_id);
     A.block_mode = p.benign_mode == 1;
     A.t3 = p.benign_dist == 1;
     A.tamper = p.tamper;
@@ -85,6 +97,7 @@ struct SimBlock {
     bool mal;
     float bsc;  // Eq. 2 block noise scale (BLOCK mode)
     float tsc;  // Gaussian tamper scale
+    BlockDraw draw;
 };
 
 template <bool kBlock>
@@ -95,6 +108,7 @@ __device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block) 
     B.mal = (A.mal_mask >> B.s) & 1u;
     B.bsc = kBlock ? A.bscale[block] : 0.0f;
     B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[block] : 0.0f;
+    B.draw = block_draw(A.key, B.c, B.s);
     return B;
 }
 
@@ -133,16 +147,17 @@ __device__ __forceinline__ float t3_div(float a, float b) {
 // noise scale taken from the reference a (elementwise mode) and base = a for
 // independent stages (base = a + carried error in the propagation model).
 template <bool kT3, bool kBlock>
-__device__ __forceinline__ void benign8(const SimArgs& A, const SimBlock& B, uint32_t e0,
-                                        const float a[8], const float base[8], float v[8]) {
+__device__ __forceinline__ void benign8(const SimArgs& A, const SimBlock& B, const NormalBase& nb,
+                                        uint32_t e0, const float a[8], const float base[8],
+                                        float v[8]) {
     float zb[8];
-    normals8(A.key, e0, B.c, B.s, A.tag_benign, zb);
+    normals8(B.draw, nb, A.tag_benign, zb);
     if (kT3) {
         float z3[8];
-        normals8(A.key, e0, B.c, B.s, A.tag_t3, z3);
+        normals8(B.draw, nb, A.tag_t3, z3);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const Words4 w = draw(A.key, e0 + k, B.c, B.s, A.tag_t12);
+            const Words4 w = finish_draw(B.draw, draw_base(B.draw, e0 + k), A.tag_t12);
             const float z1 = irwin_hall4(w.x, w.y);
             const float z2 = irwin_hall4(w.z, w.w);
             const float q = (z1 * z1 + z2 * z2) + z3[k] * z3[k];
@@ -158,21 +173,21 @@ __device__ __forceinline__ void benign8(const SimArgs& A, const SimBlock& B, uin
 
 // Eq. 3: the tampering of a malicious shard, in place on v (which holds the
 // benign output; the clean base replaces it by the noise-free base first).
-__device__ __forceinline__ void tamper8(const SimArgs& A, const SimBlock& B, uint32_t e0,
-                                        const float base[8], float v[8]) {
+__device__ __forceinline__ void tamper8(const SimArgs& A, const SimBlock& B, const NormalBase& nb,
+                                        uint32_t e0, const float base[8], float v[8]) {
     if (A.clean) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = base[k];
     }
     if (A.tamper & 1u) {
         float zt[8];
-        normals8(A.key, e0, B.c, B.s, A.tag_add, zt);
+        normals8(B.draw, nb, A.tag_add, zt);
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = v[k] + B.tsc * zt[k];
     }
     if (A.tamper & 2u) {
-        const Words4 u0 = draw(A.key, e0 >> 2, B.c, B.s, A.tag_flip);
-        const Words4 u1 = draw(A.key, (e0 >> 2) + 1, B.c, B.s, A.tag_flip);
+        const Words4 u0 = finish_draw(B.draw, draw_base(B.draw, e0 >> 2), A.tag_flip);
+        const Words4 u1 = finish_draw(B.draw, draw_base(B.draw, (e0 >> 2) + 1), A.tag_flip);
         const uint32_t u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
         for (int k = 0; k < 8; ++k)
@@ -199,8 +214,9 @@ __device__ __forceinline__ u32x4 sim_group8(const SimArgs& A, const SimBlock& B,
                                             const f32x4& a_lo, const f32x4& a_hi) {
     const float a[8] = {a_lo.x, a_lo.y, a_lo.z, a_lo.w, a_hi.x, a_hi.y, a_hi.z, a_hi.w};
     float v[8];
-    benign8<kT3, kBlock>(A, B, e0, a, a, v);
-    if (B.mal) tamper8(A, B, e0, a, v);
+    const NormalBase nb = normal_base(B.draw, e0);
+    benign8<kT3, kBlock>(A, B, nb, e0, a, a, v);
+    if (B.mal) tamper8(A, B, nb, e0, a, v);
     return pack_half8(v);
 }
 
@@ -216,8 +232,9 @@ __device__ __forceinline__ u32x4 chain_group8(const SimArgs& A, const SimBlock& 
     float u[8], v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) u[k] = first ? a[k] : a[k] + gain * d[k];
-    benign8<kT3, kBlock>(A, B, e0, a, u, v);
-    if (B.mal) tamper8(A, B, e0, u, v);
+    const NormalBase nb = normal_base(B.draw, e0);
+    benign8<kT3, kBlock>(A, B, nb, e0, a, u, v);
+    if (B.mal) tamper8(A, B, nb, e0, u, v);
     const u32x4 o = pack_half8(v);
     const uint32_t w[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll

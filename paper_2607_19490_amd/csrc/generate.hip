@@ -86,6 +86,7 @@ __global__ __launch_bounds__(kGenThreads) void ref_synth_kernel(
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x) {
         const ChunkPos p = chunk_pos(xcd_contiguous(it, total_chunks), chunks_per_block, C);
         float4* out = reinterpret_cast<float4*>(ref + p.block * n);
+        const BlockDraw bd = block_draw(key, canary_base + p.c, p.s);
 #pragma unroll
         for (int item = 0; item < kGenItems; ++item) {
             const uint32_t g = p.g0 + item * kGenThreads + threadIdx.x;
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(kGenThreads) void ref_synth_kernel(
             const float4 g_lo = *reinterpret_cast<const float4*>(gain + j0);
             const float4 g_hi = *reinterpret_cast<const float4*>(gain + j0 + 4);
             float z[8];
-            normals8(key, e0, canary_base + p.c, p.s, tag, z);
+            normals8(bd, normal_base(bd, e0), tag ^ key.k1, z);
             out[2 * g] = make_float4(z[0] * g_lo.x, z[1] * g_lo.y, z[2] * g_lo.z, z[3] * g_lo.w);
             out[2 * g + 1] =
                 make_float4(z[4] * g_hi.x, z[5] * g_hi.y, z[6] * g_hi.z, z[7] * g_hi.w);
@@ -175,8 +176,11 @@ __device__ __forceinline__ void sim_chunk(const SimArgs& A, uint64_t chunk,
     }
 }
 
+// The Gaussian pass is held to 64 registers (4 spilled), so that two
+// workgroups share a CU.
 template <bool kT3, bool kBlock, bool kStream = false>
-__global__ __launch_bounds__(sim_threads<kT3>()) void canary_sim_kernel(
+__global__ __launch_bounds__(sim_threads<kT3>())
+__attribute__((amdgpu_waves_per_eu(kT3 ? 4 : 8))) void canary_sim_kernel(
     SimArgs A, const float* __restrict__ ref, uint16_t* __restrict__ h) {
     for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x)
         sim_chunk<kT3, kBlock, kStream>(A, xcd_contiguous(it, A.total_chunks), ref, h);

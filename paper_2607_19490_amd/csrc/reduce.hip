@@ -147,13 +147,14 @@ __global__ __launch_bounds__(kReduceThreads) void tamper_norms_partial_kernel(
             const f32x4 lo = ab[2 * g], hi = ab[2 * g + 1];
             const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             float v[8], z[8];
+            const NormalBase nb = normal_base(B.draw, g * 8);
             if (A.clean) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] = a[k];
             } else {
-                benign8<kT3, kBlock>(A, B, g * 8, a, a, v);
+                benign8<kT3, kBlock>(A, B, nb, g * 8, a, a, v);
             }
-            normals8(A.key, g * 8, B.c, B.s, A.tag_add, z);
+            normals8(B.draw, nb, A.tag_add, z);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const double vd = static_cast<double>(v[k]), zd = static_cast<double>(z[k]);
@@ -206,8 +207,9 @@ __global__ __launch_bounds__(kReduceThreads) void chain_norms_partial_kernel(
             float u[8], v[8], z[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) u[k] = m == 0 ? a[k] : a[k] + gain * d[k];
-            benign8<kT3, kBlock>(A, B, g * 8, a, u, v);
-            normals8(A.key, g * 8, B.c, B.s, A.tag_add, z);
+            const NormalBase nb = normal_base(B.draw, g * 8);
+            benign8<kT3, kBlock>(A, B, nb, g * 8, a, u, v);
+            normals8(B.draw, nb, A.tag_add, z);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const double vd = static_cast<double>(A.clean ? u[k] : v[k]);
