@@ -349,12 +349,12 @@ def run_main(torch, cdt, W, args):
 
     res = {
         "metric": "drift-scored activation GB/s",
-        "value": round(value, 2),
+        "value": round(value, 4),
         "unit": "GB/s",
         "n_gpus": 1,
         "steps": args.steps,
         "warmup": args.warmup,
-        "ms_per_step": round(ms_step, 4),
+        "ms_per_step": round(ms_step, 6),
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
