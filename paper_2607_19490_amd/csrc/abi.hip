@@ -528,13 +528,12 @@ int plan_drift_batch(const char* fn, uint32_t n_jobs, const cdt_drift_job* jobs,
     std::vector<cdt::BatchKey> keys(nt);
     for (uint32_t j = 0; j < nt; ++j) {
         const cdt::DriftJobDev& d = plan->table[j];
-        keys[j] = cdt::BatchKey{d.ref, d.cpb * d.S * d.C, d.S, d.C, d.n8};
+        keys[j] = cdt::BatchKey{d.ref, d.cpb * d.S * d.C, d.S, d.C, d.n8, 0, 0};
     }
     plan->groups.resize(nt);
     uint32_t ng = 0;
     plan->total_iters = cdt::plan_batch_groups(nt, keys.data(),
-                                               cdt::kDriftJobsPerIter, cdt::kDriftJobMajorFrom,
-                                               plan->groups.data(), &ng);
+                                               cdt::kDriftJobsPerIter, plan->groups.data(), &ng);
     plan->groups.resize(ng);
     if (plan->total_blocks > kMaxBlocks * 16)
         return fail(CDT_ELIMIT, "%s: the batch holds too many blocks", fn);

@@ -12,22 +12,18 @@
 namespace cdt {
 
 // Elementwise kernels: a thread owns groups of 8 consecutive elements (one
-// 16-byte fp16 vector, two 16-byte fp32 vectors); a 1024-thread workgroup
-// covers kGenItems groups per thread of one block per chunk.  On the
-// 16 x 256 x 256 x 8192 live pass, with the XCD-contiguous chunk order,
-// 1024 x 8 runs 9.8 ms against 10.1 ms for 1024 x 2, 9.9 ms for 1024 x 16,
-// 10.1 ms for 1024 x 32 and 10.2-10.3 ms for 256 x 2..8 (the next group's
+// 16-byte fp16 vector, two 16-byte fp32 vectors); a workgroup covers up to
+// kGenItems groups per thread of one block per chunk (the next group's
 // reference is always loaded before the current one is generated, so only
-// the first load of a chunk is exposed).
+// the first load of a chunk is exposed).  The single-run Gaussian live pass
+// of a large array takes 1024 threads, everything else 256 (gen_shape).
 constexpr int kGenThreads = 1024;
-// Batch groups (BatchGroupDev): jobs per iteration, and the unit count
-// from which a group is walked job-major, for the live pass and Eq. 4.
-constexpr uint32_t kSimJobsPerIter = 1;
-constexpr uint32_t kSimJobMajorFrom = 8;
-constexpr uint32_t kDriftJobsPerIter = 8;
-constexpr uint32_t kDriftJobMajorFrom = 0xFFFFFFFFu;
+constexpr int kGenThreadsSmall = 256;
 constexpr int kGenItems = 8;
 constexpr uint32_t kGenChunkGroups = kGenThreads * kGenItems;
+// Most jobs of a batch unit (BatchGroupDev), for the live pass and Eq. 4.
+constexpr uint32_t kSimJobsPerIter = 4;
+constexpr uint32_t kDriftJobsPerIter = 8;
 
 struct SimLaunch {
     uint32_t S, C, T, H;
@@ -65,65 +61,42 @@ hipError_t launch_block_scales(uint64_t nblocks, uint32_t T, uint32_t H, const d
 hipError_t launch_canary_sim(const SimLaunch& p, const float* ref, uint16_t* h, hipStream_t st);
 
 // A run of consecutive jobs of a batched launch that read one reference
-// array in one layout, and the order its iterations take.  An iteration is one chunk of
-// up to `jobs_per_iter` of the group's jobs (a unit); each XCD takes one
-// contiguous eighth of the group's iterations, and
-//   * chunk-major: on each chunk, the group's units one after another, so
-//     neighbouring workgroups of one XCD read the same reference chunk at
-//     nearly the same time and all but the first read of it are served by
-//     the XCD's L2;
-//   * job-major: each unit from its first chunk on, so with at least 8
-//     units the 8 XCDs generate 8 different jobs over the same reference
-//     offsets at the same time and the last-level cache serves most of the
-//     re-reads.
-// Eq. 4 scores up to 8 jobs per iteration, chunk-major, reading each
-// reference chunk once for them (the sweep's 24-run groups: 13.3-13.8 ms of
-// Eq. 4 per sweep in units of up to 8, 13.8-14.3 ms in units of up to 4,
-// whose later units re-read each chunk, some of it from HBM).  The live pass generates one job per
-// iteration (its work is the random numbers, not the reads), job-major from
-// 8 jobs on: for the sweep's 24-run groups that beats chunk-major (33.5 ms
-// against 39.4-45.8 ms over the sweep), whose reuse in L2 does not make up
-// for the traffic it adds there; with fewer jobs chunk-major wins (3 runs of
-// the 16 x 256 x 256 x 8192 shape: 25.9 ms against 29 ms).
+// array in one layout.  An iteration is one chunk of up to `jobs_per_iter` of
+// the group's jobs (a unit), and an XCD takes a chunk's units one after
+// another, so that all but the first read of the reference chunk are served
+// by its L2.
 struct BatchGroupDev {
     uint64_t iter_begin;  // first iteration of the group (a multiple of 8)
     uint64_t chunks;      // chunks of one of its jobs
     uint32_t first_job, n_jobs;
-    uint32_t chunk_major, jobs_per_iter;
+    uint32_t units, jobs_per_iter;
 };
 
 // Iteration `it` of a grouped batch -> (first job of its unit, jobs in the
-// unit, chunk, jobs in the group); false for the padding that rounds each
-// group up to a multiple of 8 iterations.  The group is found by a binary
-// search (workgroup-uniform).  Iteration it runs on XCD it % 8 (a grid
-// stride that is a multiple of 8), and so does the group-local index, since
-// every group starts on a multiple of 8.
+// unit, chunk); false for the padding that rounds each group's chunks up to a
+// multiple of 8.  The group is found by a binary search (workgroup-uniform).
+// Iteration it runs on XCD it % 8 (a grid stride that is a multiple of 8),
+// and so does the group-local index, since every group starts on a multiple
+// of 8.  kContiguous: each XCD walks one contiguous eighth of the chunks;
+// else the chunks go round the XCDs one by one.
+template <bool kContiguous>
 __device__ __forceinline__ bool batch_iter(const BatchGroupDev* __restrict__ groups,
                                            uint32_t n_groups, uint64_t it, uint32_t* job,
-                                           uint32_t* unit_jobs, uint64_t* chunk,
-                                           uint32_t* group_jobs) {
+                                           uint32_t* unit_jobs, uint64_t* chunk) {
     uint32_t lo = 0, hi = n_groups;  // last group whose first iteration <= it
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) / 2;
         if (groups[mid].iter_begin <= it) lo = mid; else hi = mid;
     }
     const BatchGroupDev& G = groups[lo];
-    const uint64_t units = (G.n_jobs + G.jobs_per_iter - 1) / G.jobs_per_iter;
-    const uint64_t local = it - G.iter_begin, span = G.chunks * units;
-    if (local >= span) return false;
-    const uint64_t x = xcd_contiguous(local, span);
-    uint64_t u;
-    if (G.chunk_major) {
-        *chunk = x / units;
-        u = x - *chunk * units;
-    } else {
-        u = x / G.chunks;
-        *chunk = x - u * G.chunks;
-    }
-    const uint32_t first = static_cast<uint32_t>(u) * G.jobs_per_iter;
+    const uint64_t local = it - G.iter_begin;
+    const uint64_t l = local / kXcds, lc = l / G.units;
+    const uint64_t c = lc * kXcds + local % kXcds;
+    if (c >= G.chunks) return false;
+    *chunk = kContiguous ? xcd_contiguous(c, G.chunks) : c;
+    const uint32_t first = static_cast<uint32_t>(l - lc * G.units) * G.jobs_per_iter;
     *job = G.first_job + first;
     *unit_jobs = G.n_jobs - first < G.jobs_per_iter ? G.n_jobs - first : G.jobs_per_iter;
-    *group_jobs = G.n_jobs;
     return true;
 }
 
@@ -134,6 +107,8 @@ struct BatchKey {
     const void* ref;
     uint64_t chunks;
     uint32_t S, C, n8;
+    uint64_t seed;         // live pass: what the random counters are keyed by
+    uint32_t canary_base;
     bool operator==(const BatchKey& o) const {
         return ref == o.ref && chunks == o.chunks && S == o.S && C == o.C && n8 == o.n8;
     }
@@ -142,18 +117,23 @@ struct BatchKey {
 // Host side: the groups of a batch whose job j (jobs without chunks left
 // out by the caller) has key keys[j]; consecutive jobs with equal keys form
 // a group (the kernels may then read one job's reference layout for all of
-// them).  A group is walked chunk-major when it has fewer than
-// `job_major_from` units.  Fills groups[0 .. *n_groups) and returns the
-// padded iteration count.
-inline uint64_t plan_batch_groups(uint32_t n_jobs, const BatchKey* keys, uint32_t jobs_per_iter,
-                                  uint32_t job_major_from, BatchGroupDev* groups,
-                                  uint32_t* n_groups) {
+// them), cut into units of up to max_jobs jobs, as even as they can be: a
+// launch whose units alternate between 4 jobs and 2 keeps some CUs on the
+// long ones (six runs of the 12 x 100 x 48 x 768 shape: 427 us for the live
+// pass, Eq. 4 and the ranking with 4 + 2, 377 us with 3 + 3).  Jobs whose
+// random counters differ in more than the tag are not put into one unit.
+// Fills groups[0 .. *n_groups) and returns the padded iteration count.
+inline uint64_t plan_batch_groups(uint32_t n_jobs, const BatchKey* keys, uint32_t max_jobs,
+                                  BatchGroupDev* groups, uint32_t* n_groups) {
     *n_groups = 0;
     for (uint32_t j = 0; j < n_jobs; ++j) {
         if (*n_groups) {
             BatchGroupDev& last = groups[*n_groups - 1];
-            if (keys[last.first_job] == keys[j]) {
+            const BatchKey& k = keys[last.first_job];
+            if (k == keys[j]) {
                 ++last.n_jobs;
+                if (k.seed != keys[j].seed || k.canary_base != keys[j].canary_base)
+                    last.jobs_per_iter = 1;
                 continue;
             }
         }
@@ -162,17 +142,17 @@ inline uint64_t plan_batch_groups(uint32_t n_jobs, const BatchKey* keys, uint32_
         g.chunks = keys[j].chunks;
         g.first_job = j;
         g.n_jobs = 1;
-        g.chunk_major = 1;
-        g.jobs_per_iter = jobs_per_iter;
+        g.units = 1;
+        g.jobs_per_iter = max_jobs;
         groups[(*n_groups)++] = g;
     }
     uint64_t total = 0;
     for (uint32_t k = 0; k < *n_groups; ++k) {
         BatchGroupDev& g = groups[k];
-        const uint64_t units = (g.n_jobs + jobs_per_iter - 1) / jobs_per_iter;
-        g.chunk_major = units < job_major_from;
+        g.units = (g.n_jobs + g.jobs_per_iter - 1) / g.jobs_per_iter;
+        g.jobs_per_iter = (g.n_jobs + g.units - 1) / g.units;
         g.iter_begin = total;
-        total += (g.chunks * units + 7) / 8 * 8;
+        total += (g.chunks + kXcds - 1) / kXcds * kXcds * g.units;
     }
     return total;
 }

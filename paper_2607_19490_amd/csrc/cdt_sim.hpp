@@ -40,6 +40,7 @@ __device__ __forceinline__ void normals8(const BlockDraw& b, const NormalBase& n
 // Launch-uniform parameters of the live pass.
 struct SimArgs {
     uint32_t C, n8;
+    uint32_t chunk_groups;  // 8-element groups of a chunk
     uint32_t canary_base;  // global index of canary 0 (RNG counters)
     uint64_t chunks_per_block, total_chunks;
     Key key;
@@ -53,10 +54,11 @@ struct SimArgs {
     const float* tscale;
 };
 
-inline SimArgs make_sim_args(const SimLaunch& p, uint64_t chunks_per_block,
-                             uint64_t total_chunks) {
+inline SimArgs make_sim_args(const SimLaunch& p, uint32_t chunk_groups,
+                             uint64_t chunks_per_block, uint64_t total_chunks) {
     SimArgs A;
     A.C = p.C;
+    A.chunk_groups = chunk_groups;
     A.canary_base = p.canary_base;
     A.n8 = static_cast<uint32_t>(static_cast<uint64_t>(p.T) * p.H / 8);
     A.chunks_per_block = chunks_per_block;
@@ -90,12 +92,24 @@ struct SimJobDev {
     uint16_t* h;
 };
 
+// What a run's benign noise needs in one block (all uniform): its stream
+// tags and its scale (the elementwise level, or the block's own scale).
+struct BenignRun {
+    uint32_t tag_benign, tag_t12, tag_t3;
+    float scale;
+};
+
+template <bool kBlock>
+__device__ __forceinline__ BenignRun benign_run(const SimArgs& A, uint64_t block) {
+    return BenignRun{A.tag_benign, A.tag_t12, A.tag_t3, kBlock ? A.bscale[block] : A.sigma_b};
+}
+
 // Block-uniform state: which (shard, canary) and its scales; c is the
 // global canary index that keys the noise.
 struct SimBlock {
     uint32_t s, c;
     bool mal;
-    float bsc;  // Eq. 2 block noise scale (BLOCK mode)
+    BenignRun benign;
     float tsc;  // Gaussian tamper scale
     BlockDraw draw;
 };
@@ -106,7 +120,7 @@ __device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block) 
     B.s = static_cast<uint32_t>(block / A.C);
     B.c = A.canary_base + static_cast<uint32_t>(block - static_cast<uint64_t>(B.s) * A.C);
     B.mal = (A.mal_mask >> B.s) & 1u;
-    B.bsc = kBlock ? A.bscale[block] : 0.0f;
+    B.benign = benign_run<kBlock>(A, block);
     B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[block] : 0.0f;
     B.draw = block_draw(A.key, B.c, B.s);
     return B;
@@ -147,17 +161,17 @@ __device__ __forceinline__ float t3_div(float a, float b) {
 // noise scale taken from the reference a (elementwise mode) and base = a for
 // independent stages (base = a + carried error in the propagation model).
 template <bool kT3, bool kBlock>
-__device__ __forceinline__ void benign8(const SimArgs& A, const SimBlock& B, const NormalBase& nb,
+__device__ __forceinline__ void benign8(const BenignRun& R, const BlockDraw& bd, const NormalBase& nb,
                                         uint32_t e0, const float a[8], const float base[8],
                                         float v[8]) {
     float zb[8];
-    normals8(B.draw, nb, A.tag_benign, zb);
+    normals8(bd, nb, R.tag_benign, zb);
     if (kT3) {
         float z3[8];
-        normals8(B.draw, nb, A.tag_t3, z3);
+        normals8(bd, nb, R.tag_t3, z3);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const Words4 w = finish_draw(B.draw, draw_base(B.draw, e0 + k), A.tag_t12);
+            const Words4 w = finish_draw(bd, draw_base(bd, e0 + k), R.tag_t12);
             const float z1 = irwin_hall4(w.x, w.y);
             const float z2 = irwin_hall4(w.z, w.w);
             const float q = (z1 * z1 + z2 * z2) + z3[k] * z3[k];
@@ -166,7 +180,7 @@ __device__ __forceinline__ void benign8(const SimArgs& A, const SimBlock& B, con
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const float sc = kBlock ? B.bsc : A.sigma_b * fabsf(a[k]);
+        const float sc = kBlock ? R.scale : R.scale * fabsf(a[k]);
         v[k] = base[k] + sc * zb[k];
     }
 }
@@ -215,7 +229,7 @@ __device__ __forceinline__ u32x4 sim_group8(const SimArgs& A, const SimBlock& B,
     const float a[8] = {a_lo.x, a_lo.y, a_lo.z, a_lo.w, a_hi.x, a_hi.y, a_hi.z, a_hi.w};
     float v[8];
     const NormalBase nb = normal_base(B.draw, e0);
-    benign8<kT3, kBlock>(A, B, nb, e0, a, a, v);
+    benign8<kT3, kBlock>(B.benign, B.draw, nb, e0, a, a, v);
     if (B.mal) tamper8(A, B, nb, e0, a, v);
     return pack_half8(v);
 }
@@ -233,7 +247,7 @@ __device__ __forceinline__ u32x4 chain_group8(const SimArgs& A, const SimBlock& 
 #pragma unroll
     for (int k = 0; k < 8; ++k) u[k] = first ? a[k] : a[k] + gain * d[k];
     const NormalBase nb = normal_base(B.draw, e0);
-    benign8<kT3, kBlock>(A, B, nb, e0, a, u, v);
+    benign8<kT3, kBlock>(B.benign, B.draw, nb, e0, a, u, v);
     if (B.mal) tamper8(A, B, nb, e0, u, v);
     const u32x4 o = pack_half8(v);
     const uint32_t w[4] = {o.x, o.y, o.z, o.w};

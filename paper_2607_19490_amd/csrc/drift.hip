@@ -351,9 +351,9 @@ __global__ __launch_bounds__(kReduceThreads) void drift_batch_partial_kernel(
     const DriftJobDev* __restrict__ jobs, const BatchGroupDev* __restrict__ groups,
     uint32_t n_groups, uint64_t total_iters) {
     for (uint64_t it = blockIdx.x; it < total_iters; it += gridDim.x) {
-        uint32_t j, unit_jobs, group_jobs;
+        uint32_t j, unit_jobs;
         uint64_t chunk;
-        if (!batch_iter(groups, n_groups, it, &j, &unit_jobs, &chunk, &group_jobs)) continue;
+        if (!batch_iter<true>(groups, n_groups, it, &j, &unit_jobs, &chunk)) continue;
         static_assert(kDriftJobsPerIter == 8, "one case per unit size");
         if (unit_jobs == 8) {
             drift_chunk_jobs<8, kReadOnly>(jobs + j, chunk);

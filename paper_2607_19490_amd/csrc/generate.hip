@@ -66,7 +66,7 @@ struct ChunkPos {
 };
 
 __device__ __forceinline__ ChunkPos chunk_pos(uint64_t chunk, uint64_t chunks_per_block,
-                                              uint32_t C, uint32_t chunk_groups = kGenChunkGroups) {
+                                              uint32_t C, uint32_t chunk_groups) {
     ChunkPos p;
     p.block = chunk / chunks_per_block;
     p.g0 = static_cast<uint32_t>(chunk - p.block * chunks_per_block) * chunk_groups;
@@ -84,7 +84,8 @@ __global__ __launch_bounds__(kGenThreads) void ref_synth_kernel(
     float* __restrict__ ref) {
     const uint64_t n = static_cast<uint64_t>(n8) * 8;
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x) {
-        const ChunkPos p = chunk_pos(xcd_contiguous(it, total_chunks), chunks_per_block, C);
+        const ChunkPos p = chunk_pos(xcd_contiguous(it, total_chunks), chunks_per_block, C,
+                                     kGenChunkGroups);
         float4* out = reinterpret_cast<float4*>(ref + p.block * n);
         const BlockDraw bd = block_draw(key, canary_base + p.c, p.s);
 #pragma unroll
@@ -126,82 +127,146 @@ __global__ void block_scales_kernel(uint64_t nblocks, double n, const double* __
 // Live pass (Eqs. 2-3) -> fp16.
 // ---------------------------------------------------------------------------
 // Specialised on the two launch-uniform noise modes so that the common
-// (Gaussian, elementwise) path carries no Student-t or block-scale code.
-template <bool kT3>
-constexpr int sim_threads() { return kGenThreads; }
-
-template <bool kT3>
-constexpr uint32_t sim_chunk_groups() { return sim_threads<kT3>() * kGenItems; }
-
+// (Gaussian, elementwise) path carries no Student-t or block-scale code, and
+// on the threads per workgroup (GenShape).
+//
 // kStream: the same chunks, loads, prefetch and stores with the live pass
 // replaced by h = fp16(a) (no random numbers): the memory bound of the live
 // pass's access pattern, against which the live pass is judged.
-// One chunk of one run's live pass; shared by the single-run and batched
-// launches.
-template <bool kT3, bool kBlock, bool kStream>
+template <bool kT3, bool kBlock, bool kStream, int kThreads>
 __device__ __forceinline__ void sim_chunk(const SimArgs& A, uint64_t chunk,
                                           const float* __restrict__ ref,
                                           uint16_t* __restrict__ h) {
-    constexpr int kThreads = sim_threads<kT3>();
     const uint64_t n = static_cast<uint64_t>(A.n8) * 8;
-    {
-        const ChunkPos p = chunk_pos(chunk, A.chunks_per_block, A.C, sim_chunk_groups<kT3>());
-        const SimBlock B = sim_block<kBlock>(A, p.block);
-        const gptr<const f32x4> in = global_ptr(reinterpret_cast<const f32x4*>(ref + p.block * n));
-        const gptr<u32x4> out = global_ptr(reinterpret_cast<u32x4*>(h + p.block * n));
-        // Double buffer: the next group's reference loads are issued before
-        // the Philox work on the current group, so loads overlap the ALU work.
-        uint32_t g = p.g0 + threadIdx.x;
-        f32x4 nxt_lo = f32x4{0.f, 0.f, 0.f, 0.f}, nxt_hi = nxt_lo;
-        if (g < A.n8) {
-            nxt_lo = load_stream(in + 2 * g);
-            nxt_hi = load_stream(in + 2 * g + 1);
-        }
+    const ChunkPos p = chunk_pos(chunk, A.chunks_per_block, A.C, A.chunk_groups);
+    const SimBlock B = sim_block<kBlock>(A, p.block);
+    const gptr<const f32x4> in = global_ptr(reinterpret_cast<const f32x4*>(ref + p.block * n));
+    const gptr<u32x4> out = global_ptr(reinterpret_cast<u32x4*>(h + p.block * n));
+    const uint32_t g_end = min(p.g0 + A.chunk_groups, A.n8);
+    // Double buffer: the next group's reference loads are issued before
+    // the Philox work on the current group, so loads overlap the ALU work.
+    uint32_t g = p.g0 + threadIdx.x;
+    f32x4 nxt_lo = f32x4{0.f, 0.f, 0.f, 0.f}, nxt_hi = nxt_lo;
+    if (g < g_end) {
+        nxt_lo = load_stream(in + 2 * g);
+        nxt_hi = load_stream(in + 2 * g + 1);
+    }
 #pragma unroll 1
-        for (int item = 0; item < kGenItems; ++item, g += kThreads) {
-            if (g >= A.n8) break;
-            const f32x4 a_lo = nxt_lo, a_hi = nxt_hi;
-            const uint32_t g_next = g + kThreads;
-            if (item + 1 < kGenItems && g_next < A.n8) {
-                nxt_lo = load_stream(in + 2 * g_next);
-                nxt_hi = load_stream(in + 2 * g_next + 1);
-            }
-            if constexpr (kStream) {
-                const float a[8] = {a_lo.x, a_lo.y, a_lo.z, a_lo.w, a_hi.x, a_hi.y, a_hi.z, a_hi.w};
-                store_stream(out + g, pack_half8(a));
-            } else {
-                store_stream(out + g, sim_group8<kT3, kBlock>(A, B, g * 8, a_lo, a_hi));
-            }
+    while (g < g_end) {
+        const f32x4 a_lo = nxt_lo, a_hi = nxt_hi;
+        const uint32_t g_next = g + kThreads;
+        if (g_next < g_end) {
+            nxt_lo = load_stream(in + 2 * g_next);
+            nxt_hi = load_stream(in + 2 * g_next + 1);
         }
+        if constexpr (kStream) {
+            const float a[8] = {a_lo.x, a_lo.y, a_lo.z, a_lo.w, a_hi.x, a_hi.y, a_hi.z, a_hi.w};
+            store_stream(out + g, pack_half8(a));
+        } else {
+            store_stream(out + g, sim_group8<kT3, kBlock>(A, B, g * 8, a_lo, a_hi));
+        }
+        g = g_next;
     }
 }
 
-// The Gaussian pass is held to 64 registers (4 spilled), so that two
-// workgroups share a CU.
-template <bool kT3, bool kBlock, bool kStream = false>
-__global__ __launch_bounds__(sim_threads<kT3>())
-__attribute__((amdgpu_waves_per_eu(kT3 ? 4 : 8))) void canary_sim_kernel(
+// Chunks go round the XCDs one by one (see canary_sim_batch_kernel; with five
+// shards, one of them under all three tampers, 1.42 ms against 1.69 ms for a
+// 5 x 64 x 256 x 8192 run and its Eq. 4).
+template <bool kT3, bool kBlock, bool kStream, int kThreads>
+__global__ __launch_bounds__(kThreads) void canary_sim_kernel(
     SimArgs A, const float* __restrict__ ref, uint16_t* __restrict__ h) {
     for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x)
-        sim_chunk<kT3, kBlock, kStream>(A, xcd_contiguous(it, A.total_chunks), ref, h);
+        sim_chunk<kT3, kBlock, kStream, kThreads>(A, it, ref, h);
+}
+
+// One chunk of a unit of kJ runs over one reference, in a block that none of
+// them tampers with: each group of 8 references is loaded once, and the part
+// of its Philox calls that no run enters (normal_base: 2 of the 18 multiplies
+// of a call) is formed once for all of them.  The runs share one seed and
+// canary range (plan_batch_groups).  What every group of a run needs is held
+// in scalar registers from the chunk's start (read from the table per group,
+// the sweep's step takes 6.0 ms).  60 VGPRs with four Gaussian runs, 100 with
+// four Student-t ones.
+template <bool kT3, bool kBlock, int kJ>
+__device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ unit,
+                                                  const ChunkPos& p) {
+    const SimArgs& A0 = unit[0].A;
+    const uint64_t n = static_cast<uint64_t>(A0.n8) * 8;
+    const uint32_t g_end = min(p.g0 + A0.chunk_groups, A0.n8);
+    const gptr<const f32x4> in =
+        global_ptr(reinterpret_cast<const f32x4*>(unit[0].ref + p.block * n));
+    const BlockDraw bd = block_draw(A0.key, A0.canary_base + p.c, p.s);
+    BenignRun run[kJ];
+    gptr<u32x4> out[kJ];
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) {
+        run[j] = benign_run<kBlock>(unit[j].A, p.block);
+        out[j] = global_ptr(reinterpret_cast<u32x4*>(unit[j].h + p.block * n));
+    }
+    uint32_t g = p.g0 + threadIdx.x;
+    f32x4 nxt_lo = f32x4{0.f, 0.f, 0.f, 0.f}, nxt_hi = nxt_lo;
+    if (g < g_end) {
+        nxt_lo = load_stream(in + 2 * g);
+        nxt_hi = load_stream(in + 2 * g + 1);
+    }
+#pragma unroll 1
+    while (g < g_end) {
+        const f32x4 a_lo = nxt_lo, a_hi = nxt_hi;
+        const uint32_t g_next = g + kGenThreadsSmall;
+        if (g_next < g_end) {
+            nxt_lo = load_stream(in + 2 * g_next);
+            nxt_hi = load_stream(in + 2 * g_next + 1);
+        }
+        const float a[8] = {a_lo.x, a_lo.y, a_lo.z, a_lo.w, a_hi.x, a_hi.y, a_hi.z, a_hi.w};
+        const NormalBase nb = normal_base(bd, g * 8);
+#pragma unroll
+        for (int j = 0; j < kJ; ++j) {
+            float v[8];
+            benign8<kT3, kBlock>(run[j], bd, nb, g * 8, a, a, v);
+            store_stream(out[j] + g, pack_half8(v));
+            __builtin_amdgcn_sched_barrier(0);  // one run's temporaries at a time
+        }
+        g = g_next;
+    }
 }
 
 // Batched live pass: the jobs' chunks form one iteration range walked by
-// one grid, group by group (batch_iter): the runs of a group share their
-// references and are walked chunk-major, so a reference chunk is read from
-// HBM once and served from L2 to the group's other runs, and each XCD
-// generates its own eighth of the group.  Each chunk is generated exactly as
-// the single-run launch generates it.
+// one grid, group by group (batch_iter).  An iteration is one chunk of a unit
+// of the group's runs: together where none of them tampers with the block
+// (benign_chunk_jobs), else run by run, each exactly as the single-run launch
+// generates it.  The units of a larger group are walked chunk-major, so its
+// later units find the chunk in L2.  A malicious block costs up to 2.5 times a
+// benign one, so the chunks go round the XCDs one by one: with a contiguous
+// eighth per XCD, the XCD that holds the malicious shard of 16 finishes last
+// (the step of three 16 x 128 x 256 x 8192 runs: 16.0 ms against 18.1 ms;
+// 18.5 ms with the runs generated apart, 19.3 ms at 18 multiplies a call).
+// With 24 runs of 16 x 32 x 64 x 4096 the step takes 3.3 ms (3.75 ms).
 template <bool kT3, bool kBlock>
-__global__ __launch_bounds__(sim_threads<kT3>()) void canary_sim_batch_kernel(
+__global__ __launch_bounds__(kGenThreadsSmall) void canary_sim_batch_kernel(
     const SimJobDev* __restrict__ jobs, const BatchGroupDev* __restrict__ groups,
     uint32_t n_groups, uint64_t total_iters) {
     for (uint64_t it = blockIdx.x; it < total_iters; it += gridDim.x) {
-        uint32_t j, unit_jobs, group_jobs;
+        uint32_t first, unit_jobs;
         uint64_t chunk;
-        if (!batch_iter(groups, n_groups, it, &j, &unit_jobs, &chunk, &group_jobs)) continue;
-        const SimJobDev& J = jobs[j];
-        sim_chunk<kT3, kBlock, false>(J.A, chunk, J.ref, J.h);
+        if (!batch_iter<false>(groups, n_groups, it, &first, &unit_jobs, &chunk)) continue;
+        const SimJobDev* __restrict__ unit = jobs + first;
+        bool together = unit_jobs > 1;
+        const SimArgs& A0 = unit[0].A;
+        const ChunkPos p = chunk_pos(chunk, A0.chunks_per_block, A0.C, A0.chunk_groups);
+        for (uint32_t j = 0; j < unit_jobs; ++j)
+            together = together && !((unit[j].A.mal_mask >> p.s) & 1u);
+        static_assert(kSimJobsPerIter <= 4, "one case per unit size");
+        if (!together) {
+#pragma unroll 1
+            for (uint32_t j = 0; j < unit_jobs; ++j)
+                sim_chunk<kT3, kBlock, false, kGenThreadsSmall>(unit[j].A, chunk, unit[j].ref, unit[j].h);
+        } else if (unit_jobs == 4) {
+            benign_chunk_jobs<kT3, kBlock, 4>(unit, p);
+        } else if (unit_jobs == 3) {
+            benign_chunk_jobs<kT3, kBlock, 3>(unit, p);
+        } else {
+            benign_chunk_jobs<kT3, kBlock, 2>(unit, p);
+        }
     }
 }
 
@@ -249,6 +314,47 @@ __global__ __launch_bounds__(chain_threads<kT3>()) void canary_chain_kernel(SimA
             }
         }
     }
+}
+
+// How a live pass's work is cut: threads per workgroup and 8-element groups
+// per chunk.
+struct GenShape {
+    uint32_t threads, chunk_groups;
+    uint64_t cpb;  // chunks per block
+};
+
+// 256-thread chunks of as many groups per thread (up to kGenItems) as leave
+// 4096 workgroups, cut evenly within a block of n8 groups.  Fewer groups
+// where the launch is small fill the chip (Student-t, 12 x 30 x 48 x 768:
+// 88 us with Eq. 4 and the ranking, 102 us in 8192-group chunks).
+inline GenShape gen_shape(uint64_t n8, uint64_t all_groups) {
+    constexpr uint64_t kT = kGenThreadsSmall;
+    uint64_t items = all_groups / (kT * 4096);
+    items = items < 1 ? 1 : items > kGenItems ? kGenItems : items;
+    const uint64_t cpb = (n8 + kT * items - 1) / (kT * items);
+    const uint64_t per = (n8 + cpb - 1) / cpb;
+    GenShape g;
+    g.threads = kT;
+    g.chunk_groups = static_cast<uint32_t>((per + kT - 1) / kT * kT);
+    g.cpb = (n8 + g.chunk_groups - 1) / g.chunk_groups;
+    return g;
+}
+
+// The single-run Gaussian pass is half bound by its mixed read and write
+// stream, which longer chunks serve better once the array is large: 1024 x 8
+// against 256 x 8 on 16 x 64 x 256 x 8192 takes 4.24 against 4.32 ms (live
+// pass and Eq. 4), the same on 8 x 64 x 128 x 4096 (0.56 ms), and fills the
+// chip worse below that (8 x 16 x 47 x 1032: 57 against 54 us).  The Student-t
+// pass and the batched passes are bound by their arithmetic and take 256
+// threads at every size (four Student-t runs of the 8 x 64 x 128 x 4096 shape:
+// 3.25 against 3.51 ms).
+inline GenShape gen_shape_single(uint64_t n8, uint64_t nblocks, bool t3) {
+    if (t3 || n8 * nblocks < (1ull << 22)) return gen_shape(n8, n8 * nblocks);
+    GenShape g;
+    g.threads = kGenThreads;
+    g.chunk_groups = kGenChunkGroups;
+    g.cpb = (n8 + kGenChunkGroups - 1) / kGenChunkGroups;
+    return g;
 }
 
 // Grid for a chunked elementwise walk: 64 workgroups per CU; larger jobs
@@ -302,7 +408,7 @@ template <bool kT3, bool kBlock>
 hipError_t launch_chain_t(const SimLaunch& p, const float* ref, uint16_t* h, hipStream_t st) {
     const uint64_t n8 = static_cast<uint64_t>(p.T) * p.H / 8;
     const uint64_t cpc = (n8 + chain_chunk_groups<kT3>() - 1) / chain_chunk_groups<kT3>();
-    const SimArgs A = make_sim_args(p, cpc, cpc * p.C);  // cpc chunks per canary
+    const SimArgs A = make_sim_args(p, chain_chunk_groups<kT3>(), cpc, cpc * p.C);  // cpc chunks per canary
     hipLaunchKernelGGL((canary_chain_kernel<kT3, kBlock>), dim3(gen_grid(A.total_chunks)),
                        dim3(chain_threads<kT3>()), 0, st, A, p.S, p.carry, ref, h);
     return hipGetLastError();
@@ -317,17 +423,25 @@ hipError_t launch_canary_chain(const SimLaunch& p, const float* ref, uint16_t* h
     return launch_chain_t<false, false>(p, ref, h, st);
 }
 
-template <bool kT3>
+template <bool kT3, bool kBlock, int kThreads>
+void launch_sim_k(const SimArgs& A, const float* ref, uint16_t* h, hipStream_t st) {
+    hipLaunchKernelGGL((canary_sim_kernel<kT3, kBlock, false, kThreads>),
+                       dim3(gen_grid(A.total_chunks)), dim3(kThreads), 0, st, A, ref, h);
+}
+
+template <bool kT3, bool kBlock>
 hipError_t launch_sim_t(const SimLaunch& p, const float* ref, uint16_t* h, hipStream_t st) {
     const uint64_t n8 = static_cast<uint64_t>(p.T) * p.H / 8;
     const uint64_t nblocks = static_cast<uint64_t>(p.S) * p.C;
-    const uint64_t cpb = (n8 + sim_chunk_groups<kT3>() - 1) / sim_chunk_groups<kT3>();
-    const SimArgs A = make_sim_args(p, cpb, cpb * nblocks);
-    const dim3 grid(gen_grid(A.total_chunks)), block(sim_threads<kT3>());
-    if (A.block_mode)
-        hipLaunchKernelGGL((canary_sim_kernel<kT3, true>), grid, block, 0, st, A, ref, h);
-    else
-        hipLaunchKernelGGL((canary_sim_kernel<kT3, false>), grid, block, 0, st, A, ref, h);
+    const GenShape g = gen_shape_single(n8, nblocks, kT3);
+    const SimArgs A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
+    if constexpr (!kT3) {
+        if (g.threads == kGenThreads) {
+            launch_sim_k<kT3, kBlock, kGenThreads>(A, ref, h, st);
+            return hipGetLastError();
+        }
+    }
+    launch_sim_k<kT3, kBlock, kGenThreadsSmall>(A, ref, h, st);
     return hipGetLastError();
 }
 
@@ -336,8 +450,11 @@ hipError_t launch_canary_sim(const SimLaunch& p, const float* ref, uint16_t* h, 
     const uint64_t nblocks = static_cast<uint64_t>(p.S) * p.C;
     if (n == 0 || nblocks == 0) return hipSuccess;
     if (p.carry != 0.0f) return launch_canary_chain(p, ref, h, st);
-    return p.benign_dist == 1 ? launch_sim_t<true>(p, ref, h, st)
-                              : launch_sim_t<false>(p, ref, h, st);
+    const bool t3 = p.benign_dist == 1, block_mode = p.benign_mode == 1;
+    if (t3 && block_mode) return launch_sim_t<true, true>(p, ref, h, st);
+    if (t3) return launch_sim_t<true, false>(p, ref, h, st);
+    if (block_mode) return launch_sim_t<false, true>(p, ref, h, st);
+    return launch_sim_t<false, false>(p, ref, h, st);
 }
 
 // Table layout: n_jobs SimJobDev, then (256-byte aligned) up to n_jobs
@@ -354,7 +471,7 @@ template <bool kT3, bool kBlock>
 void launch_sim_batch_t(const SimJobDev* jobs, const BatchGroupDev* groups, uint32_t n_groups,
                         uint64_t total, hipStream_t st) {
     hipLaunchKernelGGL((canary_sim_batch_kernel<kT3, kBlock>), dim3(gen_grid(total)),
-                       dim3(sim_threads<kT3>()), 0, st, jobs, groups, n_groups, total);
+                       dim3(kGenThreadsSmall), 0, st, jobs, groups, n_groups, total);
 }
 
 hipError_t launch_canary_sim_batch(uint32_t n_jobs, const SimLaunch* runs,
@@ -364,6 +481,9 @@ hipError_t launch_canary_sim_batch(uint32_t n_jobs, const SimLaunch* runs,
     std::vector<BatchKey> keys;
     jobs.reserve(n_jobs);
     bool t3 = false, block_mode = false;
+    uint64_t all_groups = 0;
+    for (uint32_t j = 0; j < n_jobs; ++j)
+        all_groups += static_cast<uint64_t>(runs[j].T) * runs[j].H / 8 * runs[j].S * runs[j].C;
     for (uint32_t j = 0; j < n_jobs; ++j) {
         const SimLaunch& p = runs[j];
         const uint64_t n8 = static_cast<uint64_t>(p.T) * p.H / 8;
@@ -371,14 +491,14 @@ hipError_t launch_canary_sim_batch(uint32_t n_jobs, const SimLaunch* runs,
         if (n8 == 0 || nblocks == 0) continue;
         t3 = p.benign_dist == 1;
         block_mode = p.benign_mode == 1;
-        const uint64_t cpb = t3 ? (n8 + sim_chunk_groups<true>() - 1) / sim_chunk_groups<true>()
-                                : (n8 + sim_chunk_groups<false>() - 1) / sim_chunk_groups<false>();
+        const GenShape g = gen_shape(n8, all_groups);
         SimJobDev d;
-        d.A = make_sim_args(p, cpb, cpb * nblocks);
+        d.A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
         d.ref = refs[j];
         d.h = hs[j];
         jobs.push_back(d);
-        keys.push_back(BatchKey{refs[j], cpb * nblocks, p.S, p.C, static_cast<uint32_t>(n8)});
+        keys.push_back(BatchKey{refs[j], g.cpb * nblocks, p.S, p.C, static_cast<uint32_t>(n8), p.seed,
+                                p.canary_base});
     }
     if (jobs.empty()) return hipSuccess;
     const uint32_t n = static_cast<uint32_t>(jobs.size());
@@ -386,7 +506,7 @@ hipError_t launch_canary_sim_batch(uint32_t n_jobs, const SimLaunch* runs,
     std::vector<char> staged(goff + n * sizeof(BatchGroupDev), 0);
     BatchGroupDev* groups = reinterpret_cast<BatchGroupDev*>(staged.data() + goff);
     uint32_t n_groups = 0;
-    const uint64_t total = plan_batch_groups(n, keys.data(), kSimJobsPerIter, kSimJobMajorFrom,
+    const uint64_t total = plan_batch_groups(n, keys.data(), kSimJobsPerIter,
                                              groups, &n_groups);
     memcpy(staged.data(), jobs.data(), n * sizeof(SimJobDev));
     const size_t bytes = goff + n_groups * sizeof(BatchGroupDev);
@@ -416,10 +536,15 @@ hipError_t launch_canary_sim_stream(uint32_t S, uint32_t C, uint32_t T, uint32_t
     p.C = C;
     p.T = T;
     p.H = H;
-    const uint64_t cpb = (n8 + sim_chunk_groups<false>() - 1) / sim_chunk_groups<false>();
-    const SimArgs A = make_sim_args(p, cpb, cpb * nblocks);
-    hipLaunchKernelGGL((canary_sim_kernel<false, false, true>), dim3(gen_grid(A.total_chunks)),
-                       dim3(sim_threads<false>()), 0, st, A, ref, h);
+    const GenShape g = gen_shape_single(n8, nblocks, false);
+    const SimArgs A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
+    const dim3 grid(gen_grid(A.total_chunks));
+    if (g.threads == kGenThreads)
+        hipLaunchKernelGGL((canary_sim_kernel<false, false, true, kGenThreads>), grid,
+                           dim3(kGenThreads), 0, st, A, ref, h);
+    else
+        hipLaunchKernelGGL((canary_sim_kernel<false, false, true, kGenThreadsSmall>), grid,
+                           dim3(kGenThreadsSmall), 0, st, A, ref, h);
     return hipGetLastError();
 }
 

@@ -99,7 +99,7 @@ def test_canary_sim_batch_equals_single(gpu, dist, mode):
 
 # Jobs over shared references, in the order given: consecutive jobs over one
 # reference array form a group (Eq. 4: units of up to 8 jobs per reference
-# read; the live pass: chunk-major below 8 jobs, job-major from 8 on); a
+# read; the live pass: units of up to 4); a
 # reference that comes back after another one starts a new group.  Per
 # entry: (reference index, shape index).  Groups of 1, 2, 3, 4, 5, 6, 9
 # (8 + 1) and 15 (8 + 7) jobs, so every unit size from 1 to 8 is scored,
@@ -316,3 +316,39 @@ def test_canary_sim_stream_is_fp16_of_reference(gpu, shape):
     h = cdt.canary_sim_stream(ad)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(h_bits(h), oracle.f16_rne(a))
+
+
+# Units of 2, 3 and 4 runs whose malicious shards leave whole blocks benign
+# for all of them (generated together) beside blocks that some tamper with;
+# runs of another seed or canary range in the group.  H*T/8 groups per block:
+# one, one short of a 256-group chunk, exactly one, one more, several.
+@pytest.mark.parametrize("dist,mode", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", [(3, 2, 1, 8), (5, 3, 15, 136), (2, 2, 8, 256), (3, 2, 257, 8),
+                                   (4, 2, 47, 1032)])
+def test_canary_sim_batch_units(gpu, shape, dist, mode):
+    torch, cdt = gpu
+    announce(f"canary_sim_batch units {shape} dist={dist} mode={mode}")
+    S, C, T, H = shape
+    ref = to_dev(torch, inputs.ref_normal(shape, seed=21, outlier_frac=0.01))
+    q, m = cdt.ref_stats(ref)
+    ts, bs = cdt.block_scales(q, m, T, H, 0.05, 1e-2)
+    for n_runs, odd in ((2, None), (3, None), (4, None), (5, None), (6, None), (4, "seed"),
+                        (3, "canary_base")):
+        jobs = []
+        for j in range(n_runs):
+            kw = dict(seed=0x123456789ABC, cfg_id=30 + j, sigma_b=1e-2, benign_dist=dist,
+                      benign_mode=mode, mal_mask=1 << (S - 1 if j % 3 else S // 2),
+                      tamper=(1, 2, 4, 7)[j % 4], tscale=ts, bscale=bs, flip_p=0.25, scale=1.5)
+            if odd and j == n_runs - 1:
+                kw[odd] = 77
+            jobs.append((ref, torch.empty(shape, dtype=torch.float16, device="cuda"), kw))
+        cdt.canary_sim_batch(jobs)
+        for j, (_, h, kw) in enumerate(jobs):
+            one = cdt.canary_sim(ref, **kw)
+            torch.cuda.synchronize()
+            assert torch.equal(h.view(torch.int16), one.view(torch.int16)), (n_runs, odd, j)
+    _, h, kw = jobs[0]
+    kw_o = {k: v for k, v in kw.items() if k not in ("tscale", "bscale")}
+    want = oracle.canary_sim(ref.cpu().numpy(), tscale=ts.cpu().numpy(), bscale=bs.cpu().numpy(),
+                             **kw_o)
+    np.testing.assert_array_equal(h_bits(h), want)
