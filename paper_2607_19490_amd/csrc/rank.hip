@@ -1,19 +1,19 @@
 // Detection AUROC (Eqs. 5-6), its Mann-Whitney form and the scrambled-label
-// control of Section 4.5, batched over configurations.
+// control of Section 4.5, batched over configurations.  All of it is bound by
+// latency: a configuration holds a few thousand scores.
 //
-// Per-canary counts: one workgroup per configuration; each wave takes one
-// canary at a time with lane s holding shard s's score as an order key
-// (S <= 64 = one wave), and loads its next canary's scores before ranking
-// the current one.  Every positive lane compares itself with every negative
-// shard through wave shuffles; integer counts are summed over waves in a
-// fixed order.
+// Per-canary counts: one workgroup per configuration; a wave takes as many
+// canaries at a time as fit its 64 lanes with one lane per shard (four of 16
+// shards), and loads its next ones' scores before ranking the current ones.
+// The scores of the smaller class (one malicious shard, as a rule) are handed
+// round the canary's lanes by one shuffle each and compared with the others.
 //
-// Pooled Mann-Whitney: one 1024-thread workgroup per configuration sorts the
-// C*S (key, label) pairs with a bitonic network, scans the negatives in
-// sorted order, and for each positive binary-searches its tie group: it beats
-// the negatives before the group and ties those inside it.  Each thread holds
-// E = max(1, P2 / 1024) consecutive elements of the padded length P2 in
-// registers: compare-exchange stages between elements of one thread run in
+// Pooled Mann-Whitney: one workgroup per configuration sorts the keys of the
+// smaller class with a bitonic network, and every score of the larger class
+// finds its place among them by a binary search: the keys below it and, if
+// the one at its place equals it, the keys that tie.  Each thread holds
+// E = max(1, P2 / 1024) consecutive keys of the padded length P2 in
+// registers: compare-exchange stages between keys of one thread run in
 // registers, stages between threads of one wave through lane shuffles, and
 // only the stages that span waves go through LDS, with one barrier each.
 #include "cdt_device.hpp"
@@ -23,21 +23,20 @@
 namespace cdt {
 namespace {
 
-// 16 waves per configuration: on 256 canaries (one 70B-shaped run) each wave
-// walks 16 of them instead of 64 at 256 threads.
 constexpr int kCountThreads = 1024;
 constexpr int kCountWaves = kCountThreads / kWave;
 constexpr int kPoolThreads = 1024;
 constexpr uint32_t kPoolMax = 16384;
+constexpr uint32_t kPoolKeys = kPoolMax / 2;  // the smaller class's scores
 
 __device__ __forceinline__ uint64_t shard_mask(uint32_t S) {
     return S >= 64 ? ~0ull : ((1ull << S) - 1ull);
 }
 
-// r-th set bit (0-based) of m; m has more than r bits set.
-__device__ __forceinline__ uint32_t nth_set_bit(uint64_t m, uint32_t r) {
-    for (uint32_t i = 0; i < r; ++i) m &= m - 1;
-    return static_cast<uint32_t>(__builtin_ctzll(m));
+// r-th bit (0-based) that is clear in m, counting from bit 0.
+__device__ __forceinline__ uint32_t nth_clear_bit(uint64_t m, uint32_t r) {
+    for (; m; m &= m - 1) r += static_cast<uint32_t>(__builtin_ctzll(m)) <= r;
+    return r;
 }
 
 // Random-baseline score of (canary t, shard s): 24 random bits scaled into
@@ -57,10 +56,13 @@ __device__ __forceinline__ bool cfg_in_bounds(const AurocCfgDev& cfg, uint64_t n
 
 constexpr unsigned long long kBadCfg = ~0ull;  // counts of a configuration out of bounds
 
-// What one wave needs to rank a configuration's canaries (lane = shard).
+// What one wave needs to rank a configuration's canaries, `per_wave` at a
+// time: lane = (canary within the wave) * width + shard, width the power of
+// two from S on.
 struct RankCtx {
     uint64_t pos, neg;
-    uint32_t n_benign, tag, tag_random;
+    uint32_t n_benign, tag, tag_random, width, per_wave;
+    uint32_t shard, sub;  // this lane's
     bool lane_in, lane_pos, control, include_true, random;
 };
 
@@ -70,8 +72,13 @@ __device__ __forceinline__ RankCtx rank_ctx(const AurocCfgDev& cfg, uint32_t fla
     RankCtx r;
     r.pos = cfg.pos_mask & all;
     r.neg = all & ~r.pos;
-    r.lane_in = lane < cfg.S;
-    r.lane_pos = r.lane_in && ((r.pos >> lane) & 1u);
+    r.width = 1;
+    while (r.width < cfg.S) r.width <<= 1;
+    r.per_wave = kWave / r.width;
+    r.shard = lane & (r.width - 1);
+    r.sub = lane / r.width;
+    r.lane_in = r.shard < cfg.S;
+    r.lane_pos = r.lane_in && ((r.pos >> r.shard) & 1u);
     r.control = flags & 1u;
     r.include_true = flags & 4u;
     r.random = flags & 8u;
@@ -81,88 +88,85 @@ __device__ __forceinline__ RankCtx rank_ctx(const AurocCfgDev& cfg, uint32_t fla
     return r;
 }
 
-// One canary's Eq. 5 counts as this lane sees them: a positive lane's wins
-// and ties over the negative shards (q = 0, 1), the scrambled-label
-// control's chosen stage against this lane's (q = 2, 3) and the random
-// baseline's (q = 4, 5).  cur is this lane's score, t the canary's local
-// index.  Every lane of the wave must call it.
-__device__ __forceinline__ void rank_canary(const RankCtx& r, const AurocCfgDev& cfg, Key key,
-                                            uint32_t t, float cur, uint32_t (&c)[6]) {
-    const uint32_t lane = threadIdx.x % kWave;
-    for (int q = 0; q < 6; ++q) c[q] = 0;
-    const uint32_t k = r.lane_in ? order_key(cur) : 0u;
-    for (uint32_t j = 0; j < cfg.S; ++j) {
-        const uint32_t kj = __shfl(k, j, kWave);
-        if (r.lane_pos && ((r.neg >> j) & 1u)) {
-            c[0] += k > kj;
-            c[1] += k == kj;
-        }
-    }
-    if (r.random) {
-        const uint32_t kr =
-            r.lane_in ? order_key(random_score(key, cfg.canary_base + t, lane, r.tag_random)) : 0u;
-        for (uint32_t j = 0; j < cfg.S; ++j) {
-            const uint32_t kj = __shfl(kr, j, kWave);
-            if (r.lane_pos && ((r.neg >> j) & 1u)) {
-                c[4] += kr > kj;
-                c[5] += kr == kj;
-            }
-        }
-    }
-    if (r.control && r.n_benign > 0) {
-        const uint32_t u = draw(key, cfg.canary_base + t, 0, 0, r.tag).x;
-        const uint32_t js = nth_set_bit(r.neg, u % r.n_benign);
-        const uint32_t kjs = __shfl(k, js, kWave);
-        const bool counted =
-            r.lane_in && lane != js && (r.include_true || !((r.pos >> lane) & 1u));
-        if (counted) {
-            c[2] += kjs > k;
-            c[3] += kjs == k;
-        }
+// Wins and ties of the positive shards over the negative ones, as this
+// lane's part of its canary's pairs: the smaller class's keys go round.
+// counted: this lane holds a score (its shard exists and so does its canary).
+__device__ __forceinline__ void pair_counts(const RankCtx& r, uint32_t k, bool counted,
+                                            uint32_t& wins, uint32_t& ties) {
+    const bool pos_round = __builtin_popcountll(r.pos) <= __builtin_popcountll(r.neg);
+    const int base = static_cast<int>(r.sub * r.width);
+    const bool mine = counted && (pos_round ? !r.lane_pos : r.lane_pos);
+    for (uint64_t m = pos_round ? r.pos : r.neg; m; m &= m - 1) {
+        const uint32_t kj = __shfl(k, base + __builtin_ctzll(m), kWave);
+        wins += mine && (pos_round ? kj > k : k > kj);
+        ties += mine && kj == k;
     }
 }
 
-// Eqs. 5-6 counts of configuration blockIdx.x (every thread of the
-// workgroup calls it).
+// The Eq. 5 counts of this lane's canary t as the lane sees them: the
+// detector's wins and ties (q = 0, 1), the scrambled-label control's chosen
+// stage against this lane's (q = 2, 3) and the random baseline's (q = 4, 5);
+// summed over the canary's lanes they are the canary's.  cur is this lane's
+// score.  Every lane of the wave must call it; lanes past the last canary
+// count nothing.
+__device__ __forceinline__ void rank_canaries(const RankCtx& r, const AurocCfgDev& cfg, Key key,
+                                              uint32_t t, float cur, uint32_t (&c)[6]) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) c[q] = 0;
+    const bool counted = r.lane_in && t < cfg.C;
+    const uint32_t k = order_key(cur);
+    pair_counts(r, k, counted, c[0], c[1]);
+    if (r.random) {
+        const uint32_t kr =
+            order_key(random_score(key, cfg.canary_base + t, r.shard, r.tag_random));
+        pair_counts(r, kr, counted, c[4], c[5]);
+    }
+    if (r.control && r.n_benign > 0) {
+        const uint32_t u = draw(key, cfg.canary_base + t, 0, 0, r.tag).x;
+        const uint32_t js = nth_clear_bit(r.pos, u % r.n_benign);
+        const uint32_t kjs = __shfl(k, static_cast<int>(r.sub * r.width + js), kWave);
+        const bool against = counted && r.shard != js && (r.include_true || !r.lane_pos);
+        c[2] = against && kjs > k;
+        c[3] = against && kjs == k;
+    }
+}
+
+// This lane's score of canary t, 0 where it has none.
+__device__ __forceinline__ float lane_score(const RankCtx& r, const AurocCfgDev& cfg,
+                                            const float* __restrict__ base, uint64_t t) {
+    return r.lane_in && t < cfg.C ? base[t * cfg.S + r.shard] : 0.0f;
+}
+
+// Eqs. 5-6 counts of configuration cfg_index (every thread of the workgroup calls it).
 __device__ __forceinline__ void counts_body(
-    const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
-    Key key, uint32_t flags, unsigned long long* __restrict__ counts,
+    uint32_t cfg_index, const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores,
+    uint64_t n_scores, Key key, uint32_t flags, unsigned long long* __restrict__ counts,
     unsigned long long* __restrict__ baseline) {
-    const AurocCfgDev cfg = cfgs[blockIdx.x];
+    const AurocCfgDev cfg = cfgs[cfg_index];
     if (!cfg_in_bounds(cfg, n_scores)) {  // uniform over the workgroup
         if (threadIdx.x == 0) {
-            for (int q = 0; q < 6; ++q) counts[6ull * blockIdx.x + q] = kBadCfg;
+            for (int q = 0; q < 6; ++q) counts[6ull * cfg_index + q] = kBadCfg;
             if (flags & 8u)
-                for (int q = 0; q < 3; ++q) baseline[3ull * blockIdx.x + q] = kBadCfg;
+                for (int q = 0; q < 3; ++q) baseline[3ull * cfg_index + q] = kBadCfg;
         }
         return;
     }
     const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const RankCtx r = rank_ctx(cfg, flags);
-    const uint64_t pos = r.pos;
-    const bool control = r.control, include_true = r.include_true, random = r.random;
-    const uint32_t n_benign = r.n_benign;
-
-    unsigned long long g = 0, e = 0, gc = 0, ec = 0, gr = 0, er = 0;
+    unsigned long long part[6] = {0, 0, 0, 0, 0, 0};
     const float* base = scores + cfg.score_off;
-    const bool lane_in = r.lane_in;
-    float next = (wave < cfg.C && lane_in) ? base[static_cast<uint64_t>(wave) * cfg.S + lane] : 0.f;
-    for (uint32_t t = wave; t < cfg.C; t += kCountWaves) {
+    const uint64_t step = kCountWaves * r.per_wave;
+    float next = lane_score(r, cfg, base, wave * r.per_wave + r.sub);
+    for (uint64_t t0 = wave * r.per_wave; t0 < cfg.C; t0 += step) {
         const float cur = next;
-        const uint32_t tn = t + kCountWaves;
-        if (tn < cfg.C && lane_in) next = base[static_cast<uint64_t>(tn) * cfg.S + lane];
+        next = lane_score(r, cfg, base, t0 + step + r.sub);
         uint32_t c[6];
-        rank_canary(r, cfg, key, t, cur, c);
-        g += c[0];
-        e += c[1];
-        gc += c[2];
-        ec += c[3];
-        gr += c[4];
-        er += c[5];
+        rank_canaries(r, cfg, key, static_cast<uint32_t>(t0 + r.sub), cur, c);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) part[q] += c[q];
     }
 
     __shared__ unsigned long long lds[6][kCountWaves];
-    unsigned long long part[6] = {g, e, gc, ec, gr, er};
 #pragma unroll
     for (int q = 0; q < 6; ++q) part[q] = wave_sum(part[q]);
     if (lane == 0) {
@@ -174,18 +178,18 @@ __device__ __forceinline__ void counts_body(
         unsigned long long tot[6] = {0, 0, 0, 0, 0, 0};
         for (int q = 0; q < 6; ++q)
             for (int w = 0; w < kCountWaves; ++w) tot[q] += lds[q][w];
-        const unsigned long long n_pos = __builtin_popcountll(pos);
-        unsigned long long* out = counts + 6ull * blockIdx.x;
+        const unsigned long long n_pos = __builtin_popcountll(r.pos);
+        unsigned long long* out = counts + 6ull * cfg_index;
         out[0] = tot[0];
         out[1] = tot[1];
-        out[2] = static_cast<unsigned long long>(cfg.C) * n_pos * n_benign;
+        out[2] = static_cast<unsigned long long>(cfg.C) * n_pos * r.n_benign;
         unsigned long long n_ctrl = 0;
-        if (control && n_benign > 0) n_ctrl = include_true ? cfg.S - 1 : n_benign - 1;
-        out[3] = control ? tot[2] : 0;
-        out[4] = control ? tot[3] : 0;
+        if (r.control && r.n_benign > 0) n_ctrl = r.include_true ? cfg.S - 1 : r.n_benign - 1;
+        out[3] = r.control ? tot[2] : 0;
+        out[4] = r.control ? tot[3] : 0;
         out[5] = static_cast<unsigned long long>(cfg.C) * n_ctrl;
-        if (random) {
-            unsigned long long* rb = baseline + 3ull * blockIdx.x;
+        if (r.random) {
+            unsigned long long* rb = baseline + 3ull * cfg_index;
             rb[0] = tot[4];
             rb[1] = tot[5];
             rb[2] = out[2];
@@ -194,7 +198,7 @@ __device__ __forceinline__ void counts_body(
 }
 
 // Eq. 5 per canary: the same ranking as auroc_counts_kernel, each canary's
-// six counts summed over its wave and written by lane 0 to
+// six counts summed over its lanes and written by the first of them to
 // out[(offset[g] + t) * 6 + q].  A configuration out of bounds gets
 // 0xFFFFFFFF in its entries instead of being read.
 __global__ __launch_bounds__(kCountThreads) void auroc_canaries_kernel(
@@ -203,42 +207,42 @@ __global__ __launch_bounds__(kCountThreads) void auroc_canaries_kernel(
     uint32_t* __restrict__ out) {
     const AurocCfgDev cfg = cfgs[blockIdx.x];
     uint32_t* o = out + 6ull * offsets[blockIdx.x];
-    const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const uint32_t wave = threadIdx.x / kWave;
     if (!cfg_in_bounds(cfg, n_scores)) {  // uniform over the workgroup
         for (uint64_t i = threadIdx.x; i < 6ull * cfg.C; i += kCountThreads) o[i] = ~0u;
         return;
     }
     const RankCtx r = rank_ctx(cfg, flags);
     const float* base = scores + cfg.score_off;
-    float next =
-        (wave < cfg.C && r.lane_in) ? base[static_cast<uint64_t>(wave) * cfg.S + lane] : 0.f;
-    for (uint32_t t = wave; t < cfg.C; t += kCountWaves) {
+    const uint64_t step = kCountWaves * r.per_wave;
+    float next = lane_score(r, cfg, base, wave * r.per_wave + r.sub);
+    for (uint64_t t0 = wave * r.per_wave; t0 < cfg.C; t0 += step) {
         const float cur = next;
-        const uint32_t tn = t + kCountWaves;
-        if (tn < cfg.C && r.lane_in) next = base[static_cast<uint64_t>(tn) * cfg.S + lane];
+        next = lane_score(r, cfg, base, t0 + step + r.sub);
+        const uint64_t t = t0 + r.sub;
         uint32_t c[6];
-        rank_canary(r, cfg, key, t, cur, c);
-        unsigned long long w[6];
+        rank_canaries(r, cfg, key, static_cast<uint32_t>(t), cur, c);
+        // a canary's counts stay below 64 * 64: two to a word
+        uint32_t w[3] = {c[0] | c[1] << 16, c[2] | c[3] << 16, c[4] | c[5] << 16};
+        for (uint32_t off = r.width >> 1; off > 0; off >>= 1) {
 #pragma unroll
-        for (int q = 0; q < 6; ++q) w[q] = wave_sum(static_cast<unsigned long long>(c[q]));
-        if (lane == 0) {
+            for (int q = 0; q < 3; ++q) w[q] += __shfl_xor(w[q], static_cast<int>(off), kWave);
+        }
+        if (r.shard == 0 && t < cfg.C) {
 #pragma unroll
-            for (int q = 0; q < 6; ++q) o[6ull * t + q] = static_cast<uint32_t>(w[q]);
+            for (int q = 0; q < 3; ++q) {
+                o[6 * t + 2 * q] = w[q] & 0xFFFFu;
+                o[6 * t + 2 * q + 1] = w[q] >> 16;
+            }
         }
     }
-}
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m) {
-    const int lo = __shfl_xor(static_cast<int>(static_cast<uint32_t>(x)), m, kWave);
-    const int hi = __shfl_xor(static_cast<int>(static_cast<uint32_t>(x >> 32)), m, kWave);
-    return (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo);
 }
 
 // Ascending bitonic sort of P2 (a power of two, <= kE * kPoolThreads)
 // elements, thread t holding elements t*kE .. t*kE + kE - 1 in x; v is LDS
 // scratch of P2 elements.  Every thread of the workgroup must call it.
 template <int kE>
-__device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[kE], uint32_t P2, uint64_t* v) {
+__device__ __forceinline__ void bitonic_sort_regs(uint32_t (&x)[kE], uint32_t P2, uint32_t* v) {
     const uint32_t t = threadIdx.x, base = t * kE;
     for (uint32_t k = 2; k <= P2; k <<= 1) {
         uint32_t j = k >> 1;
@@ -251,7 +255,7 @@ __device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[kE], uint32_t P2
                 for (uint32_t p = t; p < P2 / 2; p += kPoolThreads) {
                     const uint32_t i = 2 * p - (p & (j - 1));
                     const uint32_t l = i + j;
-                    const uint64_t a = v[i], b = v[l];
+                    const uint32_t a = v[i], b = v[l];
                     if ((a > b) == ((i & k) == 0)) {
                         v[i] = b;
                         v[l] = a;
@@ -268,7 +272,7 @@ __device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[kE], uint32_t P2
             const bool keep_min = ((t & m) == 0) == ((base & k) == 0);
 #pragma unroll
             for (int r = 0; r < kE; ++r) {
-                const uint64_t y = shfl_xor_u64(x[r], m);
+                const uint32_t y = __shfl_xor(x[r], m, kWave);
                 x[r] = keep_min ? (x[r] < y ? x[r] : y) : (x[r] < y ? y : x[r]);
             }
         }
@@ -279,7 +283,7 @@ __device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[kE], uint32_t P2
                 for (int r = 0; r < kE; ++r) {
                     const int rp = r ^ jj;
                     if (rp > r) {
-                        const uint64_t a = x[r], b = x[rp];
+                        const uint32_t a = x[r], b = x[rp];
                         if ((a > b) == (((base + r) & k) == 0)) {
                             x[r] = b;
                             x[rp] = a;
@@ -291,18 +295,18 @@ __device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[kE], uint32_t P2
     }
 }
 
-// Loads the configuration's n (key, label) pairs padded to P2, sorts them,
-// and leaves the sorted array in v[0 .. P2).
+// The smaller class's n keys (its `m` shards, listed in `shards`, of every
+// canary), padded to P2, sorted and left in v[0 .. P2).  The pads are the
+// largest key, which a NaN score shares.
 template <int kE>
-__device__ void pooled_sort(const float* tab, uint32_t n, uint32_t P2, uint32_t S, uint64_t pos,
-                            uint64_t* v) {
-    uint64_t x[kE];
+__device__ void pooled_sort(const float* tab, uint32_t n, uint32_t P2, uint32_t S, uint32_t m,
+                            const uint8_t* shards, uint32_t* v) {
+    uint32_t x[kE];
     const uint32_t base = threadIdx.x * kE;
 #pragma unroll
     for (int r = 0; r < kE; ++r) {
-        const uint32_t i = base + r;
-        x[r] = i < n ? (static_cast<uint64_t>(order_key(tab[i])) << 32) | ((pos >> (i % S)) & 1u)
-                     : ~0ull;  // padding sorts last
+        const uint32_t i = base + r, t = i / m;
+        x[r] = i < n ? order_key(tab[t * S + shards[i - t * m]]) : 0xFFFFFFFFu;
     }
     bitonic_sort_regs<kE>(x, P2, v);
 #pragma unroll
@@ -311,92 +315,111 @@ __device__ void pooled_sort(const float* tab, uint32_t n, uint32_t P2, uint32_t 
     __syncthreads();
 }
 
-// Element layout in the pooled sort: key << 32 | label (label 1 = positive);
-// after the negative scan: key << 32 | negatives_before << 1 | label.
-// Pooled Mann-Whitney counts of configuration blockIdx.x (every thread of
-// the workgroup calls it).
+// How many of the P2 sorted keys of v lie below each of kN keys (kOrEqual:
+// or equal it), P2 a power of two.
+template <int kN, bool kOrEqual>
+__device__ __forceinline__ void place_keys(const uint32_t* v, uint32_t P2,
+                                           const uint32_t (&key)[kN], uint32_t (&at)[kN]) {
+#pragma unroll
+    for (int q = 0; q < kN; ++q) at[q] = 0;
+    for (uint32_t step = P2 >> 1; step > 0; step >>= 1) {
+#pragma unroll
+        for (int q = 0; q < kN; ++q) {
+            const uint32_t x = v[at[q] + step - 1];
+            at[q] += (kOrEqual ? x <= key[q] : x < key[q]) ? step : 0u;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kN; ++q) {
+        const uint32_t x = v[at[q]];
+        at[q] += kOrEqual ? x <= key[q] : x < key[q];
+    }
+}
+
+// Pooled Mann-Whitney counts of configuration cfg_index (every thread of the
+// workgroup calls it).
 __device__ __forceinline__ void pooled_body(
-    const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
-    unsigned long long* __restrict__ pooled) {
-    __shared__ uint64_t v[kPoolMax];
-    __shared__ uint32_t scan[kPoolThreads];
+    uint32_t cfg_index, const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores,
+    uint64_t n_scores, unsigned long long* __restrict__ pooled) {
+    __shared__ uint32_t v[kPoolKeys];
+    __shared__ uint8_t shards[kWave];
     __shared__ unsigned long long red[2][kPoolThreads / kWave];
-    const AurocCfgDev cfg = cfgs[blockIdx.x];
+    const AurocCfgDev cfg = cfgs[cfg_index];
+    unsigned long long* out = pooled + 3ull * cfg_index;
     if (!cfg_in_bounds(cfg, n_scores) ||
         static_cast<uint64_t>(cfg.S) * cfg.C > kPoolMax) {  // uniform over the workgroup
         if (threadIdx.x == 0)
-            for (int q = 0; q < 3; ++q) pooled[3ull * blockIdx.x + q] = kBadCfg;
+            for (int q = 0; q < 3; ++q) out[q] = kBadCfg;
         return;
     }
-    const uint32_t n = cfg.S * cfg.C;
+    const uint64_t pos = cfg.pos_mask & shard_mask(cfg.S);
+    const uint64_t neg = shard_mask(cfg.S) & ~pos;
+    const uint32_t n_pos = __builtin_popcountll(pos), n_neg = __builtin_popcountll(neg);
+    const bool pos_sorted = n_pos <= n_neg;
+    const uint64_t sorted = pos_sorted ? pos : neg;
+    const uint32_t m = pos_sorted ? n_pos : n_neg;
+    if (m == 0 || cfg.C == 0) {  // no pairs
+        if (threadIdx.x < 3) out[threadIdx.x] = 0;
+        return;
+    }
+    if (threadIdx.x < cfg.S && ((sorted >> threadIdx.x) & 1u))
+        shards[__builtin_popcountll(sorted & ((1ull << threadIdx.x) - 1))] =
+            static_cast<uint8_t>(threadIdx.x);
+    __syncthreads();
+    const float* tab = scores + cfg.score_off;
+    const uint32_t n = m * cfg.C;
     uint32_t P2 = 1;
     while (P2 < n) P2 <<= 1;
-    const uint64_t pos = cfg.pos_mask & shard_mask(cfg.S);
-    const float* tab = scores + cfg.score_off;
-
-    static_assert(kPoolMax == 16 * kPoolThreads, "at most 16 elements per thread");
+    static_assert(kPoolKeys == 8 * kPoolThreads, "at most 8 keys per thread");
     switch (P2 <= kPoolThreads ? 1u : P2 / kPoolThreads) {  // uniform over the workgroup
-        case 1: pooled_sort<1>(tab, n, P2, cfg.S, pos, v); break;
-        case 2: pooled_sort<2>(tab, n, P2, cfg.S, pos, v); break;
-        case 4: pooled_sort<4>(tab, n, P2, cfg.S, pos, v); break;
-        case 8: pooled_sort<8>(tab, n, P2, cfg.S, pos, v); break;
-        default: pooled_sort<16>(tab, n, P2, cfg.S, pos, v); break;
+        case 1: pooled_sort<1>(tab, n, P2, cfg.S, m, shards, v); break;
+        case 2: pooled_sort<2>(tab, n, P2, cfg.S, m, shards, v); break;
+        case 4: pooled_sort<4>(tab, n, P2, cfg.S, m, shards, v); break;
+        default: pooled_sort<8>(tab, n, P2, cfg.S, m, shards, v); break;
     }
 
-    // Exclusive scan of negatives over the sorted order: each thread owns a
-    // contiguous run of `per` elements.
-    const uint32_t per = (n + kPoolThreads - 1) / kPoolThreads;
-    const uint32_t lo = threadIdx.x * per;
-    const uint32_t hi = min(lo + per, n);
-    uint32_t cnt = 0;
-    for (uint32_t i = lo; i < hi; ++i) cnt += !(v[i] & 1u);
-    scan[threadIdx.x] = cnt;
-    __syncthreads();
-    for (uint32_t off = 1; off < kPoolThreads; off <<= 1) {
-        const uint32_t add = threadIdx.x >= off ? scan[threadIdx.x - off] : 0u;
-        __syncthreads();
-        scan[threadIdx.x] += add;
-        __syncthreads();
-    }
-    const uint32_t n_neg = scan[kPoolThreads - 1];
-    uint32_t before = scan[threadIdx.x] - cnt;
-    for (uint32_t i = lo; i < hi; ++i) {
-        const uint64_t x = v[i];
-        v[i] = (x & ~0xFFFFFFFFull) | (static_cast<uint64_t>(before) << 1) | (x & 1u);
-        before += !(x & 1u);
-    }
-    __syncthreads();
-
-    // Positives: negatives strictly below the key, and inside its tie group.
-    unsigned long long gp = 0, ep = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += kPoolThreads) {
-        const uint64_t x = v[i];
-        if (!(x & 1u)) continue;
-        const uint32_t key = static_cast<uint32_t>(x >> 32);
-        uint32_t a = 0, b = n;  // first index with key >= this key
-        while (a < b) {
-            const uint32_t m = (a + b) >> 1;
-            if (static_cast<uint32_t>(v[m] >> 32) < key) a = m + 1; else b = m;
+    // The larger class, kN scores per thread at a time so that their searches
+    // overlap: keys below and keys equal.
+    constexpr int kN = 4;
+    const uint32_t all = cfg.S * cfg.C, stride = kPoolThreads % cfg.S;
+    uint32_t s = threadIdx.x % cfg.S;
+    unsigned long long below = 0, equal = 0;
+    uint32_t searched = 0;
+    for (uint32_t e0 = threadIdx.x; e0 < all; e0 += kN * kPoolThreads) {
+        uint32_t key[kN], at[kN], upto[kN];
+        bool in[kN], tie = false;
+#pragma unroll
+        for (int q = 0; q < kN; ++q) {
+            const uint32_t e = e0 + q * kPoolThreads;
+            in[q] = e < all && !((sorted >> s) & 1u);
+            key[q] = in[q] ? order_key(tab[e]) : 0u;
+            s += stride;
+            s -= s >= cfg.S ? cfg.S : 0u;
         }
-        const uint32_t first = a;
-        a = first;
-        b = n;  // first index with key > this key
-        while (a < b) {
-            const uint32_t m = (a + b) >> 1;
-            if (static_cast<uint32_t>(v[m] >> 32) <= key) a = m + 1; else b = m;
+        place_keys<kN, false>(v, P2, key, at);
+#pragma unroll
+        for (int q = 0; q < kN; ++q) {
+            upto[q] = at[q];
+            tie = tie || (in[q] && at[q] < n && v[at[q]] == key[q]);
         }
-        const uint32_t last = a;
-        const uint32_t neg_lt = first < n ? static_cast<uint32_t>((v[first] >> 1) & 0x7FFFFFFFu) : n_neg;
-        const uint32_t neg_le = last < n ? static_cast<uint32_t>((v[last] >> 1) & 0x7FFFFFFFu) : n_neg;
-        gp += neg_lt;
-        ep += neg_le - neg_lt;
+        if (tie) place_keys<kN, true>(v, P2, key, upto);
+#pragma unroll
+        for (int q = 0; q < kN; ++q) {
+            if (!in[q]) continue;
+            below += at[q];
+            equal += min(upto[q], n) - at[q];  // a NaN's place also counts the pads
+            ++searched;
+        }
     }
-    gp = wave_sum(gp);
-    ep = wave_sum(ep);
+    // Sorted positives: a negative is beaten by the keys above it.
+    unsigned long long wins =
+        pos_sorted ? static_cast<unsigned long long>(searched) * n - below - equal : below;
+    wins = wave_sum(wins);
+    equal = wave_sum(equal);
     const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     if (lane == 0) {
-        red[0][wave] = gp;
-        red[1][wave] = ep;
+        red[0][wave] = wins;
+        red[1][wave] = equal;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -405,34 +428,38 @@ __device__ __forceinline__ void pooled_body(
             G += red[0][w];
             E += red[1][w];
         }
-        const unsigned long long n_pos = static_cast<unsigned long long>(n) - n_neg;
-        unsigned long long* out = pooled + 3ull * blockIdx.x;
         out[0] = G;
         out[1] = E;
-        out[2] = n_pos * n_neg;
+        out[2] = static_cast<unsigned long long>(n_pos) * cfg.C * n_neg * cfg.C;
     }
 }
-
 
 __global__ __launch_bounds__(kCountThreads) void auroc_counts_kernel(
     const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
     Key key, uint32_t flags, unsigned long long* __restrict__ counts,
     unsigned long long* __restrict__ baseline) {
-    counts_body(cfgs, scores, n_scores, key, flags, counts, baseline);
+    counts_body(blockIdx.x, cfgs, scores, n_scores, key, flags, counts, baseline);
 }
 
-// The counts and the pooled ranking of a configuration in one workgroup:
-// one launch instead of two when the pooled form is asked for (the two
-// parts share nothing but the configuration; the counts use a few hundred
-// bytes of LDS, the sort up to 128 KiB).
+// The counts and the pooled ranking of a configuration, a workgroup each in
+// one launch.  16 waves per workgroup: a 256-canary run of 16 shards takes
+// four rounds of the counts and four scores per thread of the search.
+// Kernel times with every count, against one workgroup per configuration that
+// sorted all of its scores: 4 x 8 scores 5.5 us (11.3 us), 16 x 256 scores
+// three times 8.7 us (67 us), 216 configurations of 8, 16 and 32 x 32 scores
+// 12.1 us (34.5 us); 40 of 48 x 240 scores, with the per-canary counts and
+// every launch, 59 us (498 us).
 static_assert(kCountThreads == kPoolThreads, "one workgroup shape for both parts");
 __global__ __launch_bounds__(kCountThreads) void auroc_counts_pooled_kernel(
     const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
     Key key, uint32_t flags, unsigned long long* __restrict__ counts,
     unsigned long long* __restrict__ baseline, unsigned long long* __restrict__ pooled) {
-    counts_body(cfgs, scores, n_scores, key, flags, counts, baseline);
-    pooled_body(cfgs, scores, n_scores, pooled);
+    if (blockIdx.x & 1u)
+        pooled_body(blockIdx.x >> 1, cfgs, scores, n_scores, pooled);
+    else
+        counts_body(blockIdx.x >> 1, cfgs, scores, n_scores, key, flags, counts, baseline);
 }
+
 // Eq. 6 from integer counts: G / pairs (ties count 0, the equation as
 // printed) and (G + E / 2) / pairs (ties count one half, the Mann-Whitney
 // form), in fp64.  A triple with no pairs, or one holding the out-of-bounds
@@ -498,7 +525,7 @@ hipError_t launch_auroc(uint32_t n_cfg, const AurocCfgDev* cfgs_dev, const float
     if (n_cfg == 0) return hipSuccess;
     const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
     if (flags & 2u) {
-        hipLaunchKernelGGL(auroc_counts_pooled_kernel, dim3(n_cfg), dim3(kCountThreads), 0, st,
+        hipLaunchKernelGGL(auroc_counts_pooled_kernel, dim3(2 * n_cfg), dim3(kCountThreads), 0, st,
                            cfgs_dev, scores, n_scores, key, flags,
                            reinterpret_cast<unsigned long long*>(counts),
                            reinterpret_cast<unsigned long long*>(baseline),

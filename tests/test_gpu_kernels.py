@@ -481,3 +481,36 @@ def test_tamper_scale_exact(gpu, kw, shape):
     assert rel_err(norms.cpu().numpy(), norms_o) < max(1e-14, 2 * T * H * 2.0**-53)
     d = ulp_diff_f32(ts.cpu().numpy(), ts_o)
     assert d.max() <= 1 and (d == 0).mean() > 0.9
+
+
+# Shards below, at and above a power of two (a wave ranks 64 / width canaries
+# at a time), either class the smaller one, 1 to 8192 sorted scores (each
+# power of two a padded length; NaN ties with the pads) and canary counts
+# that leave a wave's last round partial.
+@pytest.mark.parametrize("S,C,mask", [
+    (1, 5, 1), (2, 1, 1), (2, 33, 2), (3, 341, 0b110), (5, 13, 0b10010), (8, 2048, 0b1111),
+    (9, 57, 0b1), (16, 1024, 0b1111111100000000), (17, 100, 0x1FFFE), (31, 528, 0x7FFFFFFE),
+    (33, 31, 0x155555555), (64, 256, 0xFFFFFFFF), (64, 255, (1 << 64) - 2), (64, 3, 0),
+    (7, 9, 0b1111111), (32, 512, 0x00010001)])
+def test_auroc_either_class_smaller(gpu, S, C, mask):
+    torch, cdt = gpu
+    announce(f"auroc {S}x{C} mask {mask:x}")
+    for kw in (dict(), dict(tie_levels=3, nan_frac=0.2), dict(nan_frac=1.0)):
+        t = inputs.scores(C, S, seed=S + C, gap=0.2, mal=[s for s in range(S) if mask >> s & 1],
+                          **kw)
+        t[0, 0] = -0.0
+        t[C // 2, S - 1] = np.inf
+        for flags in (11, 15):
+            counts, pooled, base = cdt.auroc([(S, C, 0, mask, 21)], to_dev(torch, t.ravel()),
+                                             seed=8, flags=flags)
+            per = cdt.auroc_canaries([(S, C, 0, mask, 21)], to_dev(torch, t.ravel()), seed=8,
+                                     flags=flags & ~2)
+            torch.cuda.synchronize()
+            want, want_p = oracle.auroc_config(t, mask, seed=8, cfg_id=21, flags=flags)
+            np.testing.assert_array_equal(cdt.u64(counts)[0], want)
+            np.testing.assert_array_equal(cdt.u64(pooled)[0], want_p)
+            np.testing.assert_array_equal(
+                cdt.u64(base)[0], oracle.random_baseline(C, S, mask, seed=8, cfg_id=21))
+            np.testing.assert_array_equal(
+                per.cpu().numpy().view(np.uint32),
+                oracle.auroc_canaries(t, mask, seed=8, cfg_id=21, flags=flags & ~2))
