@@ -508,14 +508,15 @@ int plan_drift_batch(const char* fn, uint32_t n_jobs, const cdt_drift_job* jobs,
         d.ref = J.ref;
         d.score = J.score;
         d.sums = J.num_den;
-        d.cpb = cdt::reduce_chunks_per_block(n);
+        const cdt::ReduceShape g = cdt::reduce_shape(n / 8);
+        d.cpb = g.cpb;
+        d.chunk_groups = g.chunk_groups;
         d.block_begin = plan->total_blocks;
         d.n8 = static_cast<uint32_t>(n / 8);
         d.S = J.S;
         d.C = J.C;
-        d.direct = d.cpb == 1;
-        const uint64_t chunks = d.cpb * nb;
-        if (!d.direct) {
+        const uint64_t chunks = cdt::reduce_chunks_per_block(n) * nb;
+        if (d.cpb != 1) {
             d.partial = reinterpret_cast<double*>(static_cast<uintptr_t>(plan->partial_doubles));
             plan->partial_doubles += chunks * 2;
         }
@@ -590,7 +591,7 @@ int stage_drift_batch(const char* fn, uint32_t n_jobs, const cdt_drift_job* jobs
     char* base = static_cast<char*>(ws);
     double* partials = reinterpret_cast<double*>(base + batch_partials_offset(*plan));
     for (cdt::DriftJobDev& d : plan->table)
-        if (!d.direct) d.partial = partials + reinterpret_cast<uintptr_t>(d.partial);
+        if (d.cpb != 1) d.partial = partials + reinterpret_cast<uintptr_t>(d.partial);
     std::vector<char> staged(batch_partials_offset(*plan), 0);
     memcpy(staged.data(), plan->table.data(), plan->table.size() * sizeof(cdt::DriftJobDev));
     memcpy(staged.data() + batch_groups_offset(*plan), plan->groups.data(),

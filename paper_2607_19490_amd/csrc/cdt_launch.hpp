@@ -186,10 +186,10 @@ struct DriftJobDev {
     const float* ref;
     float* score;
     double* sums;     // [C][S][2] or null
-    double* partial;  // its per-chunk partial sums (unused when direct)
-    uint64_t cpb;     // chunks per block
+    double* partial;  // its per-chunk partial sums (unused with one chunk per block)
+    uint64_t cpb;     // chunks per block (ReduceShape)
     uint64_t block_begin;
-    uint32_t n8, S, C, direct;
+    uint32_t n8, S, C, chunk_groups;
 };
 
 hipError_t launch_drift_batch(const DriftJobDev* jobs_dev, uint32_t n_jobs,

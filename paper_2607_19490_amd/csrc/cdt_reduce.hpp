@@ -26,8 +26,32 @@ constexpr int kReduceThreads = 256;
 constexpr int kReduceUnroll = 8;
 constexpr uint64_t kReduceChunkElems = 32768;
 
+// Most chunks of a block of n elements (what workspaces are sized for).
 inline uint64_t reduce_chunks_per_block(uint64_t n) {
     return (n + kReduceChunkElems - 1) / kReduceChunkElems;
+}
+
+// How a block of n8 8-element groups is cut: into the fewest chunks of at most
+// kReduceChunkElems elements, as even as whole rounds of the workgroup (one
+// group per thread) allow.  It depends on the block's size alone, so that a
+// canary's score is the same bits in every slice of a run.  Even chunks
+// matter for blocks just above a chunk: 12 x 100 blocks of 48 x 768 elements
+// are 9 + 9 rounds, and 16 + 2 left half of the workgroups nearly idle
+// (kernel times: Eq. 4 44 us against 58 us, cosine 49 against 71, exact-norm
+// scales 75 against 114 us).
+struct ReduceShape {
+    uint64_t cpb;           // chunks per block
+    uint32_t chunk_groups;  // groups of a chunk
+};
+
+inline ReduceShape reduce_shape(uint64_t n8) {
+    if (n8 == 0) return ReduceShape{0, 0};
+    const uint64_t most = reduce_chunks_per_block(n8 * 8), per = (n8 + most - 1) / most;
+    ReduceShape r;
+    r.chunk_groups =
+        static_cast<uint32_t>((per + kReduceThreads - 1) / kReduceThreads * kReduceThreads);
+    r.cpb = (n8 + r.chunk_groups - 1) / r.chunk_groups;
+    return r;
 }
 
 // Reduction variants of Eq. 4: the relative-L2 mismatch (the detector) and
@@ -40,7 +64,6 @@ constexpr int kReduceMaxSums = 3;
 
 namespace {
 
-constexpr uint32_t kChunkGroups = static_cast<uint32_t>(kReduceChunkElems / 8);
 constexpr int kWavesPerGroup = kReduceThreads / kWave;
 
 // Sum kN per-thread values over the workgroup; thread 0 gets the result.

@@ -87,97 +87,118 @@ __device__ __forceinline__ uint32_t fold_group(const u32x4& hv, const u32x4& rv,
 // direct (a block is one chunk): the chunk's sums are the block's, and the
 // score is written here; the combine launch is skipped (it would add the one
 // partial to zero, which changes nothing).
+// kU whole rounds of the workgroup (every thread's group is in range) from
+// group `base` on: all loads first, then the sums.
+template <DriftMetric kM, bool kReadOnly, int kU>
+__device__ __forceinline__ void drift_rounds(gptr<const u32x4> hb, gptr<const f32x4> ab,
+                                             gptr<const u32x4> rb, uint32_t base,
+                                             double (&acc)[DriftTraits<kM>::kSums],
+                                             uint32_t& fold) {
+    u32x4 hv[kU], rv[kU];
+    f32x4 a0[kU], a1[kU];
+    const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const uint32_t g = base + u * kReduceThreads + threadIdx.x;
+        hv[u] = __builtin_nontemporal_load(hb + g);
+        rv[u] = u32x4{0u, 0u, 0u, 0u};
+        a0[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        a1[u] = a0[u];
+        if constexpr (DriftTraits<kM>::kHalfRef) {
+            rv[u] = __builtin_nontemporal_load(rb + g);
+        } else {
+            const gptr<const f32x4> aw = ab + 2 * (base + u * kReduceThreads + wave0);
+            quads_to_groups(__builtin_nontemporal_load(aw + lane),
+                            __builtin_nontemporal_load(aw + kWave + lane), a0[u], a1[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        if constexpr (kReadOnly)
+            fold ^= fold_group(hv[u], rv[u], a0[u], a1[u]);
+        else
+            accumulate8<kM>(hv[u], rv[u], a0[u], a1[u], acc);
+    }
+}
+
 // One chunk of one block array: its partial sums (or, direct, its block's
-// score), in a fixed order.  Shared by the single-array and batched launches.
+// score), in a fixed order: a thread's groups ascend, whatever the steps they
+// are loaded in.  Steps of kReduceUnroll rounds, then of 4, 2 and 1, then a
+// round that is not whole: only its lanes branch per load (all rounds of a
+// last step did, and every round against an fp16 reference).  118 VGPRs, four
+// waves per SIMD (136, three); 16 x 256 x 256 x 8192: 7.20 against 7.25 ms.
+// The batched form keeps one loop of predicated steps: cut the same way, the
+// compiler holds fewer of its loads in flight (158 VGPRs instead of 256) and
+// the 16 x 128 x 256 x 8192 step of three runs takes 17.8 ms, not 15.7.
+// Shared by the single-array and batched launches.
 template <DriftMetric kM, bool kReadOnly>
 __device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
                                             const void* __restrict__ ref, uint32_t n8,
-                                            uint64_t chunks_per_block, uint64_t chunk,
-                                            double* __restrict__ partial, bool direct, uint32_t S,
-                                            uint32_t C, float* __restrict__ score,
+                                            uint64_t chunks_per_block, uint32_t chunk_groups,
+                                            uint64_t chunk, double* __restrict__ partial,
+                                            uint32_t S, uint32_t C, float* __restrict__ score,
                                             double* __restrict__ sums) {
     using Tr = DriftTraits<kM>;
     const uint64_t n = static_cast<uint64_t>(n8) * 8;
-    {
-        const uint64_t b = chunk / chunks_per_block;
-        const uint32_t g0 = static_cast<uint32_t>(chunk - b * chunks_per_block) * kChunkGroups;
-        const uint32_t g_end = min(g0 + kChunkGroups, n8);
-        const gptr<const u32x4> hb = global_ptr(reinterpret_cast<const u32x4*>(h + b * n));
-        gptr<const f32x4> ab = nullptr;  // fp32 reference block
-        gptr<const u32x4> rb = nullptr;  // fp16 reference block
-        if constexpr (Tr::kHalfRef)
-            rb = global_ptr(
-                reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(ref) + b * n));
-        else
-            ab = global_ptr(
-                reinterpret_cast<const f32x4*>(static_cast<const float*>(ref) + b * n));
-        double acc[Tr::kSums];
+    const uint64_t b = chunk / chunks_per_block;
+    const uint32_t g0 = static_cast<uint32_t>(chunk - b * chunks_per_block) * chunk_groups;
+    const uint32_t g_end = min(g0 + chunk_groups, n8);
+    const gptr<const u32x4> hb = global_ptr(reinterpret_cast<const u32x4*>(h + b * n));
+    gptr<const f32x4> ab = nullptr;  // fp32 reference block
+    gptr<const u32x4> rb = nullptr;  // fp16 reference block
+    if constexpr (Tr::kHalfRef)
+        rb = global_ptr(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(ref) + b * n));
+    else
+        ab = global_ptr(reinterpret_cast<const f32x4*>(static_cast<const float*>(ref) + b * n));
+    double acc[Tr::kSums];
 #pragma unroll
-        for (int k = 0; k < Tr::kSums; ++k) acc[k] = 0.0;
-        uint32_t fold = 0;
-        for (uint32_t base = g0; base < g_end; base += kReduceThreads * kReduceUnroll) {
-            u32x4 hv[kReduceUnroll], rv[kReduceUnroll];
-            f32x4 a0[kReduceUnroll], a1[kReduceUnroll];
-            if (!Tr::kHalfRef && base + kReduceThreads * kReduceUnroll <= g_end) {
-                // every group of the step is in range (workgroup-uniform)
-                const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
-#pragma unroll
-                for (int u = 0; u < kReduceUnroll; ++u) {
-                    const uint32_t g = base + u * kReduceThreads + threadIdx.x;
-                    const gptr<const f32x4> aw = ab + 2 * (base + u * kReduceThreads + wave0);
-                    hv[u] = __builtin_nontemporal_load(hb + g);
-                    rv[u] = u32x4{0u, 0u, 0u, 0u};
-                    quads_to_groups(__builtin_nontemporal_load(aw + lane),
-                                    __builtin_nontemporal_load(aw + kWave + lane), a0[u], a1[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < kReduceUnroll; ++u) {
-                    if constexpr (kReadOnly)
-                        fold ^= fold_group(hv[u], rv[u], a0[u], a1[u]);
-                    else
-                        accumulate8<kM>(hv[u], rv[u], a0[u], a1[u], acc);
-                }
-                continue;
-            }
-#pragma unroll
-            for (int u = 0; u < kReduceUnroll; ++u) {
-                const uint32_t g = base + u * kReduceThreads + threadIdx.x;
-                hv[u] = u32x4{0u, 0u, 0u, 0u};
-                rv[u] = hv[u];
-                a0[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-                a1[u] = a0[u];
-                if (g < g_end) {
-                    hv[u] = __builtin_nontemporal_load(hb + g);
-                    if constexpr (Tr::kHalfRef) {
-                        rv[u] = __builtin_nontemporal_load(rb + g);
-                    } else {
-                        a0[u] = __builtin_nontemporal_load(ab + 2 * g);
-                        a1[u] = __builtin_nontemporal_load(ab + 2 * g + 1);
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kReduceUnroll; ++u) {
-                if constexpr (kReadOnly)
-                    fold ^= fold_group(hv[u], rv[u], a0[u], a1[u]);
-                else
-                    accumulate8<kM>(hv[u], rv[u], a0[u], a1[u], acc);
-            }
-        }
-        if constexpr (kReadOnly) {
-            if (fold == kFoldSentinel) {
-                if (direct) score[0] = __uint_as_float(fold);
-                else partial[chunk * Tr::kSums] = static_cast<double>(fold);
-            }
+    for (int k = 0; k < Tr::kSums; ++k) acc[k] = 0.0;
+    uint32_t fold = 0, base = g0;
+    for (; base + kReduceThreads * kReduceUnroll <= g_end; base += kReduceThreads * kReduceUnroll)
+        drift_rounds<kM, kReadOnly, kReduceUnroll>(hb, ab, rb, base, acc, fold);
+    static_assert(kReduceUnroll == 8, "steps of 4, 2 and 1 make up the rest");
+    const uint32_t rest = (g_end - base) / kReduceThreads;  // workgroup-uniform
+    if (rest & 4u) {
+        drift_rounds<kM, kReadOnly, 4>(hb, ab, rb, base, acc, fold);
+        base += kReduceThreads * 4;
+    }
+    if (rest & 2u) {
+        drift_rounds<kM, kReadOnly, 2>(hb, ab, rb, base, acc, fold);
+        base += kReduceThreads * 2;
+    }
+    if (rest & 1u) {
+        drift_rounds<kM, kReadOnly, 1>(hb, ab, rb, base, acc, fold);
+        base += kReduceThreads;
+    }
+    if (const uint32_t g = base + threadIdx.x; g < g_end) {
+        const u32x4 hv = __builtin_nontemporal_load(hb + g);
+        u32x4 rv = u32x4{0u, 0u, 0u, 0u};
+        f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f}, a1 = a0;
+        if constexpr (Tr::kHalfRef) {
+            rv = __builtin_nontemporal_load(rb + g);
         } else {
-            block_sum<Tr::kSums>(acc);
-            if (threadIdx.x == 0) {
-                if (direct) {
-                    finish_block<kM>(acc, chunk, S, C, score, sums);
-                } else {
+            a0 = __builtin_nontemporal_load(ab + 2 * g);
+            a1 = __builtin_nontemporal_load(ab + 2 * g + 1);
+        }
+        if constexpr (kReadOnly)
+            fold ^= fold_group(hv, rv, a0, a1);
+        else
+            accumulate8<kM>(hv, rv, a0, a1, acc);
+    }
+    const bool direct = chunks_per_block == 1;
+    if constexpr (kReadOnly) {
+        if (fold == kFoldSentinel) {
+            if (direct && score) score[0] = __uint_as_float(fold);
+            else partial[chunk * Tr::kSums] = static_cast<double>(fold);
+        }
+    } else {
+        block_sum<Tr::kSums>(acc);
+        if (threadIdx.x == 0) {
+            if (direct) {
+                finish_block<kM>(acc, chunk, S, C, score, sums);
+            } else {
 #pragma unroll
-                    for (int k = 0; k < Tr::kSums; ++k) partial[chunk * Tr::kSums + k] = acc[k];
-                }
+                for (int k = 0; k < Tr::kSums; ++k) partial[chunk * Tr::kSums + k] = acc[k];
             }
         }
     }
@@ -186,11 +207,12 @@ __device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
 template <DriftMetric kM, bool kReadOnly = false>
 __global__ __launch_bounds__(kReduceThreads) void drift_partial_kernel(
     const uint16_t* __restrict__ h, const void* __restrict__ ref, uint32_t n8,
-    uint64_t chunks_per_block, uint64_t total_chunks, double* __restrict__ partial, bool direct,
-    uint32_t S, uint32_t C, float* __restrict__ score, double* __restrict__ sums) {
+    uint64_t chunks_per_block, uint32_t chunk_groups, uint64_t total_chunks,
+    double* __restrict__ partial, uint32_t S, uint32_t C, float* __restrict__ score,
+    double* __restrict__ sums) {
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x)
-        drift_chunk<kM, kReadOnly>(h, ref, n8, chunks_per_block, xcd_contiguous(it, total_chunks),
-                                   partial, direct, S, C, score, sums);
+        drift_chunk<kM, kReadOnly>(h, ref, n8, chunks_per_block, chunk_groups,
+                                   xcd_contiguous(it, total_chunks), partial, S, C, score, sums);
 }
 
 // Eq. 4's element step for kJ arrays against one reference: the reference
@@ -242,8 +264,8 @@ __device__ __forceinline__ void drift_chunk_jobs(const DriftJobDev* __restrict__
     const DriftJobDev& J0 = jobs[0];
     const uint64_t n = static_cast<uint64_t>(J0.n8) * 8;
     const uint64_t b = chunk / J0.cpb;
-    const uint32_t g0 = static_cast<uint32_t>(chunk - b * J0.cpb) * kChunkGroups;
-    const uint32_t g_end = min(g0 + kChunkGroups, J0.n8);
+    const uint32_t g0 = static_cast<uint32_t>(chunk - b * J0.cpb) * J0.chunk_groups;
+    const uint32_t g_end = min(g0 + J0.chunk_groups, J0.n8);
     const gptr<const f32x4> ab = global_ptr(reinterpret_cast<const f32x4*>(J0.ref + b * n));
     gptr<const u32x4> hb[kJ];
 #pragma unroll
@@ -272,7 +294,7 @@ __device__ __forceinline__ void drift_chunk_jobs(const DriftJobDev* __restrict__
                     hv[j][u] =
                         __builtin_nontemporal_load(hb[j] + base + u * kReduceThreads + threadIdx.x);
         } else {
-            // the last, partial step of a ragged block: every lane loads an
+            // the chunk's last, partial step: every lane loads an
             // element in range (its own, or the chunk's last) and keeps zeros
             // where its own is out of range
 #pragma unroll
@@ -319,7 +341,7 @@ __device__ __forceinline__ void drift_chunk_jobs(const DriftJobDev* __restrict__
         for (int j = 0; j < kJ; ++j) {
             const DriftJobDev& J = jobs[j];
             const double acc[2] = {sums[j], sums[kJ]};
-            if (J.direct) {
+            if (J.cpb == 1) {
                 finish_block<DriftMetric::kL2>(acc, chunk, J.S, J.C, J.score, J.sums);
             } else {
                 J.partial[chunk * 2] = acc[0];
@@ -371,8 +393,8 @@ __global__ __launch_bounds__(kReduceThreads) void drift_batch_partial_kernel(
             drift_chunk_jobs<2, kReadOnly>(jobs + j, chunk);
         } else {
             const DriftJobDev& J = jobs[j];
-            drift_chunk<DriftMetric::kL2, kReadOnly>(J.h, J.ref, J.n8, J.cpb, chunk, J.partial,
-                                                     J.direct, J.S, J.C, J.score, J.sums);
+            drift_chunk<DriftMetric::kL2, kReadOnly>(J.h, J.ref, J.n8, J.cpb, J.chunk_groups,
+                                                     chunk, J.partial, J.S, J.C, J.score, J.sums);
         }
     }
 }
@@ -382,7 +404,7 @@ __global__ void drift_batch_combine_kernel(const DriftJobDev* __restrict__ jobs,
     const uint64_t g = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (g >= total_blocks) return;
     const DriftJobDev& J = jobs[find_job(jobs, n_jobs, g)];
-    if (J.direct) return;  // scored by the partial kernel itself
+    if (J.cpb == 1) return;  // scored by the partial kernel itself
     const uint64_t b = g - J.block_begin;
     double acc[2] = {0.0, 0.0};
     for (uint64_t i = 0; i < J.cpb; ++i) {
@@ -426,14 +448,14 @@ hipError_t launch_drift_t(uint32_t S, uint32_t C, uint32_t T, uint32_t H, const 
     const uint64_t n = static_cast<uint64_t>(T) * H;
     const uint64_t nblocks = static_cast<uint64_t>(S) * C;
     if (nblocks == 0) return hipSuccess;
-    const uint64_t cpb = reduce_chunks_per_block(n);
-    const uint64_t total = cpb * nblocks;
+    const ReduceShape g = reduce_shape(n / 8);
+    const uint64_t cpb = g.cpb, total = cpb * nblocks;
     double* partial = static_cast<double*>(ws);
     const bool direct = cpb == 1;
     if (total > 0) {
         hipLaunchKernelGGL(drift_partial_kernel<kM>, dim3(reduce_grid(total)),
                            dim3(kReduceThreads), 0, st, h, ref, static_cast<uint32_t>(n / 8), cpb,
-                           total, partial, direct, S, C, score, sums);
+                           g.chunk_groups, total, partial, S, C, score, sums);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -471,12 +493,12 @@ hipError_t launch_drift_batch_read_stream(const DriftJobDev* jobs_dev,
 hipError_t launch_drift_read_stream(uint32_t S, uint32_t C, uint32_t T, uint32_t H,
                                    const uint16_t* h, const float* ref, void* ws, hipStream_t st) {
     const uint64_t n = static_cast<uint64_t>(T) * H;
-    const uint64_t total = reduce_chunks_per_block(n) * S * C;
+    const ReduceShape g = reduce_shape(n / 8);
+    const uint64_t total = g.cpb * S * C;
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL((drift_partial_kernel<DriftMetric::kL2, true>), dim3(reduce_grid(total)),
-                       dim3(kReduceThreads), 0, st, h, ref, static_cast<uint32_t>(n / 8),
-                       reduce_chunks_per_block(n), total, static_cast<double*>(ws), false, S, C,
-                       nullptr, nullptr);
+                       dim3(kReduceThreads), 0, st, h, ref, static_cast<uint32_t>(n / 8), g.cpb,
+                       g.chunk_groups, total, static_cast<double*>(ws), S, C, nullptr, nullptr);
     return hipGetLastError();
 }
 

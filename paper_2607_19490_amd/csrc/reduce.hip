@@ -26,13 +26,13 @@ struct ReduceChunk {
     uint32_t g0, g_end, rounds;
 };
 
-__device__ __forceinline__ ReduceChunk reduce_chunk(uint64_t it, uint64_t total_chunks,
-                                                    uint64_t chunks_per_block, uint32_t n8) {
+__device__ __forceinline__ ReduceChunk reduce_chunk(uint64_t it, uint64_t chunks_per_block,
+                                                    uint32_t chunk_groups, uint32_t n8) {
     ReduceChunk p;
     p.chunk = it;
     p.block = p.chunk / chunks_per_block;
-    p.g0 = static_cast<uint32_t>(p.chunk - p.block * chunks_per_block) * kChunkGroups;
-    p.g_end = min(p.g0 + kChunkGroups, n8);
+    p.g0 = static_cast<uint32_t>(p.chunk - p.block * chunks_per_block) * chunk_groups;
+    p.g_end = min(p.g0 + chunk_groups, n8);
     p.rounds = (p.g_end - p.g0 + kReduceThreads - 1) / kReduceThreads;
     return p;
 }
@@ -44,13 +44,14 @@ __device__ __forceinline__ ReduceChunk reduce_chunk(uint64_t it, uint64_t total_
 // returns false past the last one.
 struct ReduceWalk {
     uint64_t it, total_chunks, chunks_per_block;
-    uint32_t n8, round;
+    uint32_t chunk_groups, n8, round;
     ReduceChunk cur;
 
     __device__ __forceinline__ ReduceWalk(uint64_t first, uint64_t total, uint64_t cpb,
-                                          uint32_t n8_)
-        : it(first), total_chunks(total), chunks_per_block(cpb), n8(n8_), round(0) {
-        if (first < total) cur = reduce_chunk(first, total, cpb, n8_);
+                                          uint32_t groups, uint32_t n8_)
+        : it(first), total_chunks(total), chunks_per_block(cpb), chunk_groups(groups), n8(n8_),
+          round(0) {
+        if (first < total) cur = reduce_chunk(first, cpb, groups, n8_);
     }
     __device__ __forceinline__ bool valid() const { return it < total_chunks; }
     __device__ __forceinline__ bool last_round() const { return round + 1 == cur.rounds; }
@@ -62,7 +63,7 @@ struct ReduceWalk {
         round = 0;
         it += gridDim.x;
         if (it >= total_chunks) return false;
-        cur = reduce_chunk(it, total_chunks, chunks_per_block, n8);
+        cur = reduce_chunk(it, chunks_per_block, chunk_groups, n8);
         return true;
     }
 };
@@ -85,7 +86,7 @@ void sim_score_partial_kernel(
     double* __restrict__ partial) {
     constexpr DriftMetric kM = DriftMetric::kL2;
     const uint64_t n = static_cast<uint64_t>(A.n8) * 8;
-    ReduceWalk w(blockIdx.x, A.total_chunks, A.chunks_per_block, A.n8);
+    ReduceWalk w(blockIdx.x, A.total_chunks, A.chunks_per_block, A.chunk_groups, A.n8);
     if (!w.valid()) return;
     auto load = [&](const ReduceWalk& at, f32x4& lo, f32x4& hi) {
         lo = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -141,8 +142,8 @@ __global__ __launch_bounds__(kReduceThreads) void tamper_norms_partial_kernel(
     for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x) {
         const uint64_t chunk = xcd_contiguous(it, A.total_chunks);
         const uint64_t b = chunk / A.chunks_per_block;
-        const uint32_t g0 = static_cast<uint32_t>(chunk - b * A.chunks_per_block) * kChunkGroups;
-        const uint32_t g_end = min(g0 + kChunkGroups, A.n8);
+        const uint32_t g0 = static_cast<uint32_t>(chunk - b * A.chunks_per_block) * A.chunk_groups;
+        const uint32_t g_end = min(g0 + A.chunk_groups, A.n8);
         const SimBlock B = sim_block<kBlock>(A, b);
         const f32x4* ab = reinterpret_cast<const f32x4*>(ref + b * n);
         double acc[2] = {0.0, 0.0};
@@ -190,8 +191,8 @@ __global__ __launch_bounds__(kReduceThreads) void chain_norms_partial_kernel(
         const uint32_t c = static_cast<uint32_t>(chunk / A.chunks_per_block);
         const uint32_t g0 =
             static_cast<uint32_t>(chunk - static_cast<uint64_t>(c) * A.chunks_per_block) *
-            kChunkGroups;
-        const uint32_t g_end = min(g0 + kChunkGroups, A.n8);
+            A.chunk_groups;
+        const uint32_t g_end = min(g0 + A.chunk_groups, A.n8);
         double acc[2] = {0.0, 0.0};
         for (uint32_t g = g0 + threadIdx.x; g < g_end; g += kReduceThreads) {
             float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -282,56 +283,68 @@ __global__ void tamper_scale_combine_kernel(const double* __restrict__ partial,
     }
 }
 
+// sum a^2 and sum |a| over one group of 8.
+__device__ __forceinline__ void add_stats8(const f32x4& a0, const f32x4& a1, double (&acc)[2]) {
+    const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const double x = static_cast<double>(av[k]);
+        acc[0] = fma(x, x, acc[0]);
+        acc[1] += fabs(x);
+    }
+}
+
+// kU whole rounds of the workgroup from group `base` on: all loads first.
+template <int kU>
+__device__ __forceinline__ void stats_rounds(const f32x4* ab, uint32_t base, double (&acc)[2]) {
+    f32x4 a0[kU], a1[kU];
+    const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const f32x4* aw = ab + 2 * (base + u * kReduceThreads + wave0);
+        quads_to_groups(__builtin_nontemporal_load(aw + lane),
+                        __builtin_nontemporal_load(aw + kWave + lane), a0[u], a1[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) add_stats8(a0[u], a1[u], acc);
+}
+
 __global__ __launch_bounds__(kReduceThreads) void ref_stats_partial_kernel(
-    const float* __restrict__ ref, uint32_t n8, uint64_t chunks_per_block, uint64_t total_chunks,
-    double2* __restrict__ partial) {
+    const float* __restrict__ ref, uint32_t n8, uint64_t chunks_per_block, uint32_t chunk_groups,
+    uint64_t total_chunks, double2* __restrict__ partial) {
     // Same chunking, XCD order and reads as drift_score: kReduceUnroll groups
     // in flight per thread, the reference in contiguous runs moved to the
     // owning lanes (quads_to_groups); each thread adds its groups in
-    // ascending order (groups past the block end contribute exact zeros).
+    // ascending order.
     const uint64_t n = static_cast<uint64_t>(n8) * 8;
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x) {
         const uint64_t chunk = xcd_contiguous(it, total_chunks);
         const uint64_t b = chunk / chunks_per_block;
-        const uint32_t g0 = static_cast<uint32_t>(chunk - b * chunks_per_block) * kChunkGroups;
-        const uint32_t g_end = min(g0 + kChunkGroups, n8);
+        const uint32_t g0 = static_cast<uint32_t>(chunk - b * chunks_per_block) * chunk_groups;
+        const uint32_t g_end = min(g0 + chunk_groups, n8);
         const f32x4* ab = reinterpret_cast<const f32x4*>(ref + b * n);
-        double Q = 0.0, M = 0.0;
-        for (uint32_t base = g0; base < g_end; base += kReduceThreads * kReduceUnroll) {
-            f32x4 a0[kReduceUnroll], a1[kReduceUnroll];
-            if (base + kReduceThreads * kReduceUnroll <= g_end) {  // workgroup-uniform
-                const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
-#pragma unroll
-                for (int u = 0; u < kReduceUnroll; ++u) {
-                    const f32x4* aw = ab + 2 * (base + u * kReduceThreads + wave0);
-                    quads_to_groups(__builtin_nontemporal_load(aw + lane),
-                                    __builtin_nontemporal_load(aw + kWave + lane), a0[u], a1[u]);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < kReduceUnroll; ++u) {
-                    const uint32_t g = base + u * kReduceThreads + threadIdx.x;
-                    a0[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    a1[u] = a0[u];
-                    if (g < g_end) {
-                        a0[u] = __builtin_nontemporal_load(ab + 2 * g);
-                        a1[u] = __builtin_nontemporal_load(ab + 2 * g + 1);
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kReduceUnroll; ++u) {
-                const float av[8] = {a0[u].x, a0[u].y, a0[u].z, a0[u].w,
-                                     a1[u].x, a1[u].y, a1[u].z, a1[u].w};
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const double x = static_cast<double>(av[k]);
-                    Q = fma(x, x, Q);
-                    M += fabs(x);
-                }
-            }
+        double acc[2] = {0.0, 0.0};
+        uint32_t base = g0;
+        for (; base + kReduceThreads * kReduceUnroll <= g_end;
+             base += kReduceThreads * kReduceUnroll)
+            stats_rounds<kReduceUnroll>(ab, base, acc);
+        static_assert(kReduceUnroll == 8, "steps of 4, 2 and 1 make up the rest");
+        const uint32_t rest = (g_end - base) / kReduceThreads;  // workgroup-uniform
+        if (rest & 4u) {
+            stats_rounds<4>(ab, base, acc);
+            base += kReduceThreads * 4;
         }
-        double acc[2] = {Q, M};
+        if (rest & 2u) {
+            stats_rounds<2>(ab, base, acc);
+            base += kReduceThreads * 2;
+        }
+        if (rest & 1u) {
+            stats_rounds<1>(ab, base, acc);
+            base += kReduceThreads;
+        }
+        if (const uint32_t g = base + threadIdx.x; g < g_end)
+            add_stats8(__builtin_nontemporal_load(ab + 2 * g),
+                       __builtin_nontemporal_load(ab + 2 * g + 1), acc);
         block_sum<2>(acc);
         if (threadIdx.x == 0) partial[chunk] = make_double2(acc[0], acc[1]);
     }
@@ -370,11 +383,11 @@ hipError_t launch_sim_score(const SimLaunch& p, const float* ref, uint16_t* h, f
     const uint64_t n = static_cast<uint64_t>(p.T) * p.H;
     const uint64_t nblocks = static_cast<uint64_t>(p.S) * p.C;
     if (nblocks == 0) return hipSuccess;
-    const uint64_t cpb = reduce_chunks_per_block(n);
-    const uint64_t total = cpb * nblocks;
+    const ReduceShape shape = reduce_shape(n / 8);
+    const uint64_t cpb = shape.cpb, total = cpb * nblocks;
     double* partial = static_cast<double*>(ws);
     if (total > 0) {
-        const SimArgs A = make_sim_args(p, kChunkGroups, cpb, total);
+        const SimArgs A = make_sim_args(p, shape.chunk_groups, cpb, total);
         const dim3 grid(reduce_grid(total));
         if (A.t3 && A.block_mode)
             launch_sim_score_t<true, true>(A, grid, ref, h, partial, st);
@@ -396,11 +409,11 @@ hipError_t launch_tamper_scale_exact(const SimLaunch& p, const float* ref, doubl
     const uint64_t n = static_cast<uint64_t>(p.T) * p.H;
     const uint64_t nblocks = static_cast<uint64_t>(p.S) * p.C;
     if (nblocks == 0) return hipSuccess;
-    const uint64_t cpb = reduce_chunks_per_block(n);
-    const uint64_t total = cpb * nblocks;
+    const ReduceShape shape = reduce_shape(n / 8);
+    const uint64_t cpb = shape.cpb, total = cpb * nblocks;
     double* partial = static_cast<double*>(ws);
     if (total > 0) {
-        const SimArgs A = make_sim_args(p, kChunkGroups, cpb, total);
+        const SimArgs A = make_sim_args(p, shape.chunk_groups, cpb, total);
         const dim3 grid(reduce_grid(total)), block(kReduceThreads);
         if (A.t3 && A.block_mode)
             hipLaunchKernelGGL((tamper_norms_partial_kernel<true, true>), grid, block, 0, st, A,
@@ -440,11 +453,12 @@ hipError_t launch_tamper_scale_exact_chain(const SimLaunch& p, const float* ref,
                        dim3(256), 0, st, nblocks, tscale, norms);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n == 0) return e;
-    const uint64_t cpb = reduce_chunks_per_block(n);
+    const ReduceShape shape = reduce_shape(n / 8);
+    const uint64_t cpb = shape.cpb;
     // The scales of earlier malicious stages are read from tscale itself.
     SimLaunch q = p;
     q.tscale = tscale;
-    const SimArgs A = make_sim_args(q, kChunkGroups, cpb, cpb * p.C);  // one stage's blocks
+    const SimArgs A = make_sim_args(q, shape.chunk_groups, cpb, cpb * p.C);  // one stage's blocks
     double* partial = static_cast<double*>(ws);
     for (uint32_t m = 0; m < p.S; ++m) {  // malicious stages in pipeline order
         if (!((p.mal_mask >> m) & 1u)) continue;
@@ -471,13 +485,13 @@ hipError_t launch_ref_stats(uint32_t S, uint32_t C, uint32_t T, uint32_t H, cons
     const uint64_t n = static_cast<uint64_t>(T) * H;
     const uint64_t nblocks = static_cast<uint64_t>(S) * C;
     if (nblocks == 0) return hipSuccess;
-    const uint64_t cpb = reduce_chunks_per_block(n);
-    const uint64_t total = cpb * nblocks;
+    const ReduceShape shape = reduce_shape(n / 8);
+    const uint64_t cpb = shape.cpb, total = cpb * nblocks;
     double2* partial = static_cast<double2*>(ws);
     if (total > 0) {
         hipLaunchKernelGGL(ref_stats_partial_kernel, dim3(reduce_grid(total)),
                            dim3(kReduceThreads), 0, st, ref, static_cast<uint32_t>(n / 8), cpb,
-                           total, partial);
+                           shape.chunk_groups, total, partial);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
