@@ -272,45 +272,37 @@ __global__ __launch_bounds__(kGenThreadsSmall) void canary_sim_batch_kernel(
 
 // Propagation model: a thread walks one group of 8 elements of one canary
 // through all S stages in order, carrying the live error in registers; a
-// workgroup chunk covers kChainChunkGroups groups of one canary, so the
-// per-stage block state is workgroup-uniform.  Same bytes as the live pass
-// (4 B read, 2 B written per element); nothing is re-read.  With Student-t
-// noise the carried error and the extra draws need more than the 128
-// registers a 1024-thread workgroup allows, so that variant runs 256-thread
-// workgroups (no spills: 26.5 ms against 27.9 ms on the 16 x 256 x 256 x 8192
-// shape); the Gaussian variant keeps 1024 threads (10.5 ms against 11.5 ms).
-template <bool kT3>
-constexpr int chain_threads() { return kT3 ? 256 : kGenThreads; }
-
-template <bool kT3>
-constexpr uint32_t chain_chunk_groups() { return chain_threads<kT3>() * kGenItems; }
-
-template <bool kT3, bool kBlock>
-__global__ __launch_bounds__(chain_threads<kT3>()) void canary_chain_kernel(SimArgs A, uint32_t S,
-                                                                   float gain,
-                                                                   const float* __restrict__ ref,
-                                                                   uint16_t* __restrict__ h) {
+// workgroup chunk covers groups of one canary, so the per-stage block state is
+// workgroup-uniform.  Same bytes as the live pass (4 B read, 2 B written per
+// element); nothing is re-read.  Loading the next stage's reference before the
+// current one is generated costs more registers than it hides (8 x 64 x 128 x
+// 4096 with its scales and Eq. 4: 740 against 729 us).
+template <bool kT3, bool kBlock, int kThreads>
+__global__ __launch_bounds__(kThreads) void canary_chain_kernel(SimArgs A, uint32_t S, float gain,
+                                                                const float* __restrict__ ref,
+                                                                uint16_t* __restrict__ h) {
     const uint64_t n = static_cast<uint64_t>(A.n8) * 8;
+    const uint64_t stage4 = static_cast<uint64_t>(A.C) * n / 4;  // 4-element quads of a stage
     for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x) {
         const uint64_t chunk = xcd_contiguous(it, A.total_chunks);
         const uint32_t c = static_cast<uint32_t>(chunk / A.chunks_per_block);
         const uint32_t g0 =
             static_cast<uint32_t>(chunk - static_cast<uint64_t>(c) * A.chunks_per_block) *
-            chain_chunk_groups<kT3>();
+            A.chunk_groups;
+        const uint32_t g_end = min(g0 + A.chunk_groups, A.n8);
 #pragma unroll 1
-        for (int item = 0; item < kGenItems; ++item) {
-            const uint32_t g = g0 + item * chain_threads<kT3>() + threadIdx.x;
-            if (g >= A.n8) break;
+        for (uint32_t g = g0 + threadIdx.x; g < g_end; g += kThreads) {
             float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            const f32x4* in = reinterpret_cast<const f32x4*>(ref + c * n) + 2 * g;
+            u32x4* out = reinterpret_cast<u32x4*>(h + c * n) + g;
 #pragma unroll 1
             for (uint32_t s = 0; s < S; ++s) {
-                const uint64_t block = static_cast<uint64_t>(s) * A.C + c;
-                const SimBlock B = sim_block<kBlock>(A, block);
-                const f32x4* in = reinterpret_cast<const f32x4*>(ref + block * n);
-                u32x4* out = reinterpret_cast<u32x4*>(h + block * n);
-                const f32x4 a_lo = load_stream(in + 2 * g), a_hi = load_stream(in + 2 * g + 1);
-                store_stream(out + g,
+                const f32x4 a_lo = load_stream(in), a_hi = load_stream(in + 1);
+                in += stage4;
+                const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(s) * A.C + c);
+                store_stream(out,
                              chain_group8<kT3, kBlock>(A, B, g * 8, s == 0, gain, a_lo, a_hi, d));
+                out += stage4 / 2;
             }
         }
     }
@@ -350,6 +342,20 @@ inline GenShape gen_shape(uint64_t n8, uint64_t all_groups) {
 // 3.25 against 3.51 ms).
 inline GenShape gen_shape_single(uint64_t n8, uint64_t nblocks, bool t3) {
     if (t3 || n8 * nblocks < (1ull << 22)) return gen_shape(n8, n8 * nblocks);
+    GenShape g;
+    g.threads = kGenThreads;
+    g.chunk_groups = kGenChunkGroups;
+    g.cpb = (n8 + kGenChunkGroups - 1) / kGenChunkGroups;
+    return g;
+}
+
+// The propagation pass has C canaries of n8 groups (S stages each) to spread:
+// 256 threads until that fills 1024-thread chunks well (live pass, scales, Eq. 4
+// and ranking, 256 against 1024 threads: 8 x 128 x 16 x 4096 187 against 242 us,
+// 8 x 64 x 64 x 4096 397 against 373 us, 8 x 64 x 128 x 4096 757 against 744 us).
+// The Student-t variant needs more than the 128 registers that 1024 threads leave.
+inline GenShape gen_shape_chain(uint64_t n8, uint64_t C, bool t3) {
+    if (t3 || n8 * C < (1ull << 21)) return gen_shape(n8, n8 * C);
     GenShape g;
     g.threads = kGenThreads;
     g.chunk_groups = kGenChunkGroups;
@@ -407,10 +413,18 @@ hipError_t launch_block_scales(uint64_t nblocks, uint32_t T, uint32_t H, const d
 template <bool kT3, bool kBlock>
 hipError_t launch_chain_t(const SimLaunch& p, const float* ref, uint16_t* h, hipStream_t st) {
     const uint64_t n8 = static_cast<uint64_t>(p.T) * p.H / 8;
-    const uint64_t cpc = (n8 + chain_chunk_groups<kT3>() - 1) / chain_chunk_groups<kT3>();
-    const SimArgs A = make_sim_args(p, chain_chunk_groups<kT3>(), cpc, cpc * p.C);  // cpc chunks per canary
-    hipLaunchKernelGGL((canary_chain_kernel<kT3, kBlock>), dim3(gen_grid(A.total_chunks)),
-                       dim3(chain_threads<kT3>()), 0, st, A, p.S, p.carry, ref, h);
+    const GenShape g = gen_shape_chain(n8, p.C, kT3);  // chunks per canary
+    const SimArgs A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * p.C);
+    const dim3 grid(gen_grid(A.total_chunks));
+    if constexpr (!kT3) {
+        if (g.threads == kGenThreads) {
+            hipLaunchKernelGGL((canary_chain_kernel<kT3, kBlock, kGenThreads>), grid,
+                               dim3(kGenThreads), 0, st, A, p.S, p.carry, ref, h);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((canary_chain_kernel<kT3, kBlock, kGenThreadsSmall>), grid,
+                       dim3(kGenThreadsSmall), 0, st, A, p.S, p.carry, ref, h);
     return hipGetLastError();
 }
 

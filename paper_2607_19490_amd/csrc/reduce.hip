@@ -179,13 +179,14 @@ __global__ __launch_bounds__(kReduceThreads) void tamper_norms_partial_kernel(
 // canary_chain_kernel walks it (earlier malicious stages tampered with the
 // scales already written to A.tscale), and at stage m the untampered output
 // v (or the clean base u) and the TAMPER_ADD normals are summed in fp64.
-// Chunks are reduction chunks of one canary's stage-m block: chunk index =
-// canary * chunks_per_block + chunk within the block.
+// Chunks are pieces of one canary's stage-m block (chain_norms_shape), chunk
+// index = canary * chunks_per_block + piece.
 template <bool kT3, bool kBlock>
 __global__ __launch_bounds__(kReduceThreads) void chain_norms_partial_kernel(
     SimArgs A, uint32_t m, float gain, const float* __restrict__ ref,
     double* __restrict__ partial) {
     const uint64_t n = static_cast<uint64_t>(A.n8) * 8;
+    const uint64_t stage4 = static_cast<uint64_t>(A.C) * n / 4;  // 4-element quads of a stage
     for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x) {
         const uint64_t chunk = xcd_contiguous(it, A.total_chunks);
         const uint32_t c = static_cast<uint32_t>(chunk / A.chunks_per_block);
@@ -194,19 +195,19 @@ __global__ __launch_bounds__(kReduceThreads) void chain_norms_partial_kernel(
             A.chunk_groups;
         const uint32_t g_end = min(g0 + A.chunk_groups, A.n8);
         double acc[2] = {0.0, 0.0};
+#pragma unroll 1
         for (uint32_t g = g0 + threadIdx.x; g < g_end; g += kReduceThreads) {
             float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            const f32x4* in = reinterpret_cast<const f32x4*>(ref + c * n) + 2 * g;
 #pragma unroll 1
             for (uint32_t s = 0; s < m; ++s) {
-                const uint64_t block = static_cast<uint64_t>(s) * A.C + c;
-                const SimBlock B = sim_block<kBlock>(A, block);
-                const f32x4* in = reinterpret_cast<const f32x4*>(ref + block * n);
-                chain_group8<kT3, kBlock>(A, B, g * 8, s == 0, gain, in[2 * g], in[2 * g + 1], d);
+                const f32x4 a_lo = in[0], a_hi = in[1];
+                in += stage4;
+                const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(s) * A.C + c);
+                chain_group8<kT3, kBlock>(A, B, g * 8, s == 0, gain, a_lo, a_hi, d);
             }
-            const uint64_t block = static_cast<uint64_t>(m) * A.C + c;
-            const SimBlock B = sim_block<kBlock>(A, block);
-            const f32x4* in = reinterpret_cast<const f32x4*>(ref + block * n);
-            const f32x4 lo = in[2 * g], hi = in[2 * g + 1];
+            const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(m) * A.C + c);
+            const f32x4 lo = in[0], hi = in[1];
             const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             float u[8], v[8], z[8];
 #pragma unroll
@@ -230,24 +231,26 @@ __global__ __launch_bounds__(kReduceThreads) void chain_norms_partial_kernel(
     }
 }
 
-// Stage m's scales from chain_norms_partial_kernel's partials: one thread per
-// canary adds its chunks in order.
-__global__ void chain_scale_combine_kernel(const double* __restrict__ partial,
-                                           uint64_t chunks_per_block, uint32_t C, uint32_t m,
-                                           double eps, float* __restrict__ tscale,
-                                           double* __restrict__ norms) {
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    double vv = 0.0, zz = 0.0;
-    for (uint64_t i = 0; i < chunks_per_block; ++i) {
-        vv += partial[(c * chunks_per_block + i) * 2];
-        zz += partial[(c * chunks_per_block + i) * 2 + 1];
-    }
-    const uint64_t b = static_cast<uint64_t>(m) * C + c;
-    tscale[b] = zz > 0.0 ? static_cast<float>(eps * sqrt(vv / zz)) : 0.0f;
-    if (norms) {
-        norms[2 * b] = vv;
-        norms[2 * b + 1] = zz;
+// Stage m's scales from chain_norms_partial_kernel's partials: one wave per
+// canary, its lanes' strided sums added by the wave's butterfly.
+__global__ __launch_bounds__(kWave) void chain_scale_combine_kernel(
+    const double* __restrict__ partial, uint64_t chunks_per_block, uint32_t C, uint32_t m,
+    double eps, float* __restrict__ tscale, double* __restrict__ norms) {
+    for (uint64_t c = blockIdx.x; c < C; c += gridDim.x) {
+        double vv = 0.0, zz = 0.0;
+        for (uint64_t i = threadIdx.x; i < chunks_per_block; i += kWave) {
+            vv += partial[(c * chunks_per_block + i) * 2];
+            zz += partial[(c * chunks_per_block + i) * 2 + 1];
+        }
+        vv = wave_sum(vv);
+        zz = wave_sum(zz);
+        if (threadIdx.x != 0) continue;
+        const uint64_t b = static_cast<uint64_t>(m) * C + c;
+        tscale[b] = zz > 0.0 ? static_cast<float>(eps * sqrt(vv / zz)) : 0.0f;
+        if (norms) {
+            norms[2 * b] = vv;
+            norms[2 * b + 1] = zz;
+        }
     }
 }
 
@@ -436,6 +439,27 @@ hipError_t launch_tamper_scale_exact(const SimLaunch& p, const float* ref, doubl
     return hipGetLastError();
 }
 
+// The pieces of a block in chain_norms_partial_kernel.  A stage's norms are
+// one canary's block each, S times less work than a whole pass has, so a block
+// is cut finer than reduce_shape cuts it: into pieces of 256 groups (one per
+// thread) or of the largest power of two that leaves 32 of them, as far as the
+// workspace, sized for S stages, holds their sums.  With canary_chain_kernel's
+// finer chunks and two colluders, exact scales, live pass, Eq. 4 and ranking
+// of a 12 x 100 x 48 x 768 configuration take 162 us (278 us with two pieces
+// per canary, 200 workgroups in all).
+inline ReduceShape chain_norms_shape(uint64_t n8, uint32_t S) {
+    ReduceShape r = reduce_shape(n8);
+    const uint64_t room = reduce_chunks_per_block(n8 * 8) * S * kReduceMaxSums / 2;
+    uint64_t groups = kReduceThreads;
+    while (groups < r.chunk_groups && (n8 / groups >= 64 ||
+                                           (n8 + groups - 1) / groups > room))
+        groups *= 2;
+    if (groups >= r.chunk_groups) return r;
+    r.cpb = (n8 + groups - 1) / groups;
+    r.chunk_groups = static_cast<uint32_t>(groups);
+    return r;
+}
+
 template <bool kT3, bool kBlock>
 void launch_chain_norms_t(const SimArgs& A, uint32_t m, float gain, const float* ref,
                           double* partial, hipStream_t st) {
@@ -453,7 +477,7 @@ hipError_t launch_tamper_scale_exact_chain(const SimLaunch& p, const float* ref,
                        dim3(256), 0, st, nblocks, tscale, norms);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n == 0) return e;
-    const ReduceShape shape = reduce_shape(n / 8);
+    const ReduceShape shape = chain_norms_shape(n / 8, p.S);
     const uint64_t cpb = shape.cpb;
     // The scales of earlier malicious stages are read from tscale itself.
     SimLaunch q = p;
@@ -472,7 +496,7 @@ hipError_t launch_tamper_scale_exact_chain(const SimLaunch& p, const float* ref,
             launch_chain_norms_t<false, false>(A, m, p.carry, ref, partial, st);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(chain_scale_combine_kernel, dim3((p.C + 255) / 256), dim3(256), 0, st,
+        hipLaunchKernelGGL(chain_scale_combine_kernel, dim3(reduce_grid(p.C)), dim3(kWave), 0, st,
                            partial, cpb, p.C, m, eps, tscale, norms);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

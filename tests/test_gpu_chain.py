@@ -134,3 +134,40 @@ def test_substudy_parity(gpu):
     np.testing.assert_array_equal(h_bits(h), h_o)
     s64, _, _ = oracle.drift_score(h_o, ref_o)
     assert rel_err(score.cpu().numpy(), s64) < 1e-5
+
+
+# The exact-norm scales cut a canary's block into pieces: one thread per group
+# each, the power of two that leaves 32 of them, or what the workspace of one
+# or two stages holds; the last piece ragged, or one group long.
+@pytest.mark.parametrize("shape", [(1, 3, 16, 8192), (2, 2, 16, 8192), (12, 1, 16, 8192),
+                                   (3, 2, 33, 1000), (2, 3, 257, 8), (4, 2, 64, 2056)])
+def test_chain_exact_norm_pieces(gpu, shape):
+    torch, cdt = gpu
+    S, C, T, H = shape
+    announce(f"chain exact norm pieces {shape}")
+    ref = oracle.ref_synth(S, C, T, H, 3, 0, oracle.outlier_gain(H, max(1, H // 100), 20.0, 3, 0))
+    kw = dict(seed=5, cfg_id=2, mal_mask=1 | 1 << (S - 1), sigma_b=1e-2, tamper=1, carry=0.7)
+    norms = torch.empty((S, C, 2), dtype=torch.float64, device="cuda")
+    ts = cdt.tamper_scale_exact(to_dev(torch, ref), 0.05, norms=norms, **kw)
+    torch.cuda.synchronize()
+    ts_o, norms_o = oracle.tamper_scale_exact(ref, 0.05, **kw)
+    assert ulp_diff_f32(ts.cpu().numpy(), ts_o).max() <= 1
+    assert rel_err(norms.cpu().numpy(), norms_o) < 1e-8  # as test_chain_exact_norm
+
+
+@pytest.mark.parametrize("dist", [0, 1])
+def test_chain_of_a_large_array_equals_its_slices(gpu, dist):
+    """2^21 groups take 1024-thread chunks (Gaussian noise), a slice of four
+    canaries 256-thread ones; the activations are the same bits."""
+    torch, cdt = gpu
+    S, C, T, H = 2, 64, 64, 4096
+    announce(f"chain large against slices dist={dist}")
+    ref = torch.randn((S, C, T, H), device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    ts = torch.full((S, C), 0.05, device="cuda")
+    kw = dict(seed=9, cfg_id=4, mal_mask=2, sigma_b=1e-2, benign_dist=dist, tamper=1, carry=0.7)
+    whole = cdt.canary_sim(ref, tscale=ts, **kw)
+    for c0 in (0, 28, 60):
+        part = cdt.canary_sim(ref[:, c0:c0 + 4].contiguous(), canary_base=c0,
+                              tscale=ts[:, c0:c0 + 4].contiguous(), **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(part.view(torch.int16), whole[:, c0:c0 + 4].view(torch.int16)), c0
