@@ -454,10 +454,10 @@ __global__ __launch_bounds__(kCountThreads) void auroc_counts_pooled_kernel(
     const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
     Key key, uint32_t flags, unsigned long long* __restrict__ counts,
     unsigned long long* __restrict__ baseline, unsigned long long* __restrict__ pooled) {
-    if (blockIdx.x & 1u)
-        pooled_body(blockIdx.x >> 1, cfgs, scores, n_scores, pooled);
+    if (blockIdx.y)
+        pooled_body(blockIdx.x, cfgs, scores, n_scores, pooled);
     else
-        counts_body(blockIdx.x >> 1, cfgs, scores, n_scores, key, flags, counts, baseline);
+        counts_body(blockIdx.x, cfgs, scores, n_scores, key, flags, counts, baseline);
 }
 
 // Eq. 6 from integer counts: G / pairs (ties count 0, the equation as
@@ -525,7 +525,7 @@ hipError_t launch_auroc(uint32_t n_cfg, const AurocCfgDev* cfgs_dev, const float
     if (n_cfg == 0) return hipSuccess;
     const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
     if (flags & 2u) {
-        hipLaunchKernelGGL(auroc_counts_pooled_kernel, dim3(2 * n_cfg), dim3(kCountThreads), 0, st,
+        hipLaunchKernelGGL(auroc_counts_pooled_kernel, dim3(n_cfg, 2), dim3(kCountThreads), 0, st,
                            cfgs_dev, scores, n_scores, key, flags,
                            reinterpret_cast<unsigned long long*>(counts),
                            reinterpret_cast<unsigned long long*>(baseline),
