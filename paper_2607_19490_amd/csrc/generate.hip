@@ -24,35 +24,83 @@ namespace {
 constexpr uint32_t kMaxOutlierH = 32768;
 
 // ---------------------------------------------------------------------------
-// Outlier channels: every workgroup draws all H channel words into LDS, then
-// each thread ranks one channel against all of them.
+// Outlier channels: one workgroup draws all H channel words into LDS, finds
+// the n_out-th smallest by four 8-bit digits (a histogram of the words that
+// share the digits found so far, scanned by one wave), and writes every gain.
+// Words equal to it count in channel order.  9 us at H = 4096, where ranking
+// every channel against all others took 118 us.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void outlier_gain_kernel(uint32_t H, uint32_t n_out, float big,
-                                                           Key key, uint32_t tag,
-                                                           float* __restrict__ gain) {
+constexpr int kOutlierThreads = 1024;
+__global__ __launch_bounds__(kOutlierThreads) void outlier_gain_kernel(uint32_t H, uint32_t n_out,
+                                                                      float big, Key key,
+                                                                      uint32_t tag,
+                                                                      float* __restrict__ gain) {
     __shared__ uint32_t words[kMaxOutlierH];
-    for (uint32_t j = threadIdx.x; j < H; j += blockDim.x) words[j] = draw(key, j, 0, 0, tag).x;
-    __syncthreads();
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= H) return;
-    const uint32_t wj = words[j];
-    uint32_t rank = 0;
-    for (uint32_t i = 0; i < H; ++i) {
-        const uint32_t wi = words[i];
-        rank += (wi < wj) || (wi == wj && i < j);
+    __shared__ uint32_t hist[256];
+    __shared__ uint32_t found[2];
+    const BlockDraw bd = block_draw(key, 0, 0);
+    for (uint32_t j = threadIdx.x; j < H; j += kOutlierThreads)
+        words[j] = finish_draw(bd, draw_base(bd, j), tag ^ key.k1).x;
+    uint32_t digits = 0, mask = 0, rank = n_out;  // the rank-th smallest (from 1) is sought
+    for (int shift = 24; n_out > 0 && shift >= 0; shift -= 8) {  // uniform
+        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < H; j += kOutlierThreads) {
+            const uint32_t w = words[j];
+            if ((w & mask) == digits) atomicAdd(&hist[(w >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < kWave) {  // four bins per lane
+            uint32_t bin[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                bin[k] = hist[4 * threadIdx.x + k];
+                sum += bin[k];
+            }
+            uint32_t upto = sum;
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t left = __shfl_up(upto, off, kWave);
+                upto += static_cast<int>(threadIdx.x) >= off ? left : 0u;
+            }
+            uint32_t below = upto - sum;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (below < rank && rank <= below + bin[k]) {
+                    found[0] = 4 * threadIdx.x + k;
+                    found[1] = rank - below;
+                }
+                below += bin[k];
+            }
+        }
+        __syncthreads();
+        digits |= found[0] << shift;
+        mask |= 255u << shift;
+        rank = found[1];
     }
-    gain[j] = rank < n_out ? big : 1.0f;
+    // `rank` of the words equal to `digits` are outliers; all, unless words tie
+    const bool all_equal = n_out > 0 && hist[digits & 255u] == rank;
+    for (uint32_t j = threadIdx.x; j < H; j += kOutlierThreads) {
+        const uint32_t w = words[j];
+        bool out = n_out > 0 && w < digits;
+        if (n_out > 0 && w == digits) {
+            uint32_t before = 0;
+            if (!all_equal)
+                for (uint32_t i = 0; i < j; ++i) before += words[i] == digits;
+            out = before < rank;
+        }
+        gain[j] = out ? big : 1.0f;
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Streamed loads and stores of the elementwise kernels (each byte is touched
-// once per launch).  The fp16 output is stored nontemporally: it leaves no
+// once per launch).  The output is stored nontemporally: it leaves no
 // dirty lines behind in L2 / the Infinity Cache for the next kernel to evict.
 // ---------------------------------------------------------------------------
 template <typename P>
 __device__ __forceinline__ f32x4 load_stream(P p) { return *p; }
-template <typename P>
-__device__ __forceinline__ void store_stream(P p, u32x4 v) {
+template <typename P, typename V>
+__device__ __forceinline__ void store_stream(P p, V v) {
     __builtin_nontemporal_store(v, p);
 }
 
@@ -76,31 +124,50 @@ __device__ __forceinline__ ChunkPos chunk_pos(uint64_t chunk, uint64_t chunks_pe
 }
 
 // ---------------------------------------------------------------------------
-// Synthetic references: ref = fp32(z_REF * gain[j]).
+// Synthetic references: ref = fp32(z_REF * gain[j]).  A wave's 64 groups of 8
+// elements are 128 quads of 4; lane L makes quads L and 64 + L, so that each
+// store instruction covers one contiguous 1 KB run, and a quad's channel moves
+// by a constant from round to round.  Together with ref_stats on the 8 x 64 x
+// 128 x 4096 shape (nontemporal stores move the write-back of dirty lines from
+// its reads to these writes): 371 us with outlier_gain, 385 us with ordinary
+// stores; 1024-thread chunks 390 us; 16 x 64 x 256 x 8192 2.86 ms (3.17 ms with
+// whole groups per lane, a division per group and the ranking above).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kGenThreads) void ref_synth_kernel(
+__device__ __forceinline__ f32x4 synth_quad(const BlockDraw& bd, uint32_t tag_key, uint32_t quad,
+                                            const f32x4& g) {
+    const Words4 u = finish_draw(bd, draw_base(bd, 2 * quad), tag_key);
+    const Words4 v = finish_draw(bd, draw_base(bd, 2 * quad + 1), tag_key);
+    return f32x4{irwin_hall4(u.x, u.y) * g.x, irwin_hall4(u.z, u.w) * g.y,
+                 irwin_hall4(v.x, v.y) * g.z, irwin_hall4(v.z, v.w) * g.w};
+}
+
+constexpr int kSynthThreads = 256, kSynthItems = 8;
+constexpr uint32_t kSynthChunkGroups = kSynthThreads * kSynthItems;
+__global__ __launch_bounds__(kSynthThreads) void ref_synth_kernel(
     uint32_t C, uint32_t canary_base, uint32_t H, uint32_t n8, uint64_t chunks_per_block,
     uint64_t total_chunks, Key key, uint32_t tag, const float* __restrict__ gain,
     float* __restrict__ ref) {
     const uint64_t n = static_cast<uint64_t>(n8) * 8;
+    const uint32_t h4 = H / 4, step = 2 * kSynthThreads % h4;  // quads of a row, of a round
+    const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
+    const f32x4* gq = reinterpret_cast<const f32x4*>(gain);
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x) {
         const ChunkPos p = chunk_pos(xcd_contiguous(it, total_chunks), chunks_per_block, C,
-                                     kGenChunkGroups);
-        float4* out = reinterpret_cast<float4*>(ref + p.block * n);
+                                     kSynthChunkGroups);
+        f32x4* out = reinterpret_cast<f32x4*>(ref + p.block * n);
         const BlockDraw bd = block_draw(key, canary_base + p.c, p.s);
-#pragma unroll
-        for (int item = 0; item < kGenItems; ++item) {
-            const uint32_t g = p.g0 + item * kGenThreads + threadIdx.x;
-            if (g >= n8) break;
-            const uint32_t e0 = g * 8;
-            const uint32_t j0 = e0 % H;
-            const float4 g_lo = *reinterpret_cast<const float4*>(gain + j0);
-            const float4 g_hi = *reinterpret_cast<const float4*>(gain + j0 + 4);
-            float z[8];
-            normals8(bd, normal_base(bd, e0), tag ^ key.k1, z);
-            out[2 * g] = make_float4(z[0] * g_lo.x, z[1] * g_lo.y, z[2] * g_lo.z, z[3] * g_lo.w);
-            out[2 * g + 1] =
-                make_float4(z[4] * g_hi.x, z[5] * g_hi.y, z[6] * g_hi.z, z[7] * g_hi.w);
+        const uint32_t n4 = 2 * n8, q_end = min(2 * (p.g0 + kSynthChunkGroups), n4);
+        uint32_t q0 = 2 * (p.g0 + wave0) + lane;
+        uint32_t j0 = q0 % h4, j1 = (q0 + kWave) % h4;
+#pragma unroll 1
+        for (; q0 < q_end; q0 += 2 * kSynthThreads) {
+            const uint32_t q1 = q0 + kWave;
+            store_stream(out + q0, synth_quad(bd, tag ^ key.k1, q0, gq[j0]));
+            if (q1 < q_end) store_stream(out + q1, synth_quad(bd, tag ^ key.k1, q1, gq[j1]));
+            j0 += step;
+            j0 -= j0 >= h4 ? h4 : 0u;
+            j1 += step;
+            j1 -= j1 >= h4 ? h4 : 0u;
         }
     }
 }
@@ -376,8 +443,7 @@ inline uint32_t gen_grid(uint64_t total_chunks) {
 hipError_t launch_outlier_gain(uint32_t H, uint32_t n_out, float big, uint64_t seed,
                                uint32_t ref_set_id, float* gain, hipStream_t st) {
     if (H == 0) return hipSuccess;
-    const uint32_t grid = (H + 255) / 256;
-    hipLaunchKernelGGL(outlier_gain_kernel, dim3(grid), dim3(256), 0, st, H, n_out, big,
+    hipLaunchKernelGGL(outlier_gain_kernel, dim3(1), dim3(kOutlierThreads), 0, st, H, n_out, big,
                        Key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)},
                        stream_tag(kStreamOutlier, ref_set_id), gain);
     return hipGetLastError();
@@ -390,9 +456,9 @@ hipError_t launch_ref_synth(uint32_t S, uint32_t C, uint32_t T, uint32_t H, uint
     const uint64_t nblocks = static_cast<uint64_t>(S) * C;
     if (n == 0 || nblocks == 0) return hipSuccess;
     const uint32_t n8 = static_cast<uint32_t>(n / 8);
-    const uint64_t cpb = (n8 + kGenChunkGroups - 1) / kGenChunkGroups;
+    const uint64_t cpb = (n8 + kSynthChunkGroups - 1) / kSynthChunkGroups;
     const uint64_t total = cpb * nblocks;
-    hipLaunchKernelGGL(ref_synth_kernel, dim3(gen_grid(total)), dim3(kGenThreads), 0, st, C,
+    hipLaunchKernelGGL(ref_synth_kernel, dim3(gen_grid(total)), dim3(kSynthThreads), 0, st, C,
                        canary_base, H, n8, cpb, total,
                        Key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)},
                        stream_tag(kStreamRef, ref_set_id), gain, ref);

@@ -514,3 +514,30 @@ def test_auroc_either_class_smaller(gpu, S, C, mask):
             np.testing.assert_array_equal(
                 per.cpu().numpy().view(np.uint32),
                 oracle.auroc_canaries(t, mask, seed=8, cfg_id=21, flags=flags & ~2))
+
+
+# The selection's digit search at every count of outliers that can go wrong
+# (none, one, all, all but one), fewer channels than a workgroup has threads,
+# more, and the most; and references over rows shorter and longer than a
+# wave's 1 KB runs.
+@pytest.mark.parametrize("H", [1, 8, 255, 1024, 1025, 8192, 32768])
+def test_outlier_gain_counts(gpu, H):
+    torch, cdt = gpu
+    announce(f"outlier gain H={H}")
+    for n_out in sorted({0, 1, H // 100, H // 2, H - 1, H}):
+        for seed in (0, 0xFEDCBA9876543210):
+            got = cdt.outlier_gain(H, n_out, 20.0, seed, 5)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(got.cpu().numpy(),
+                                          oracle.outlier_gain(H, n_out, 20.0, seed, 5))
+
+
+@pytest.mark.parametrize("shape", [(2, 3, 5, 8), (3, 1, 257, 16), (1, 2, 9, 1016), (2, 2, 3, 6152)])
+def test_ref_synth_rows(gpu, shape):
+    torch, cdt = gpu
+    S, C, T, H = shape
+    announce(f"ref synth rows {shape}")
+    gain = oracle.outlier_gain(H, max(1, H // 10), 20.0, 7, 3)
+    got = cdt.ref_synth(S, C, T, H, 7, 3, to_dev(torch, gain))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(got.cpu().numpy(), oracle.ref_synth(S, C, T, H, 7, 3, gain))
