@@ -74,13 +74,14 @@ struct ReduceWalk {
 // order as drift_partial_kernel<kL2>, so the block sums are bitwise those of
 // canary_sim followed by drift_score.  kStoreH also writes the activations.
 // The next group's references are loaded while the current one is
-// generated and scored (also across chunks), and the register budget is
-// held to 64 (a few spills) so that eight waves share each SIMD.  Per
-// 16 x 256 x 256 x 8192 run: 13.1 ms without the prefetch, 12.4 ms with it,
-// 12.0 ms with the cap (1024-thread groups), 11.4 ms with 512-thread groups,
-// 10.6-11.2 ms with the current 256-thread groups.
+// generated and scored (also across chunks).  Six waves share each SIMD: the
+// pass is bound by issuing the live pass's arithmetic, which six waves keep as
+// busy as eight, and 80 registers hold the Gaussian variants without a spill
+// (the Student-t ones spill up to 4).  Eight waves' 64 spilled 9 to 26, whose
+// scratch traffic sat beside the reference stream: 32 x 32 x 64 x 8192 with one
+// shard under all three tampers 530 us (563 us).
 template <bool kT3, bool kBlock, bool kStoreH>
-__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
 void sim_score_partial_kernel(
     SimArgs A, const float* __restrict__ ref, uint16_t* __restrict__ h,
     double* __restrict__ partial) {
