@@ -406,7 +406,7 @@ typedef struct cdt_auroc_cfg {
 size_t cdt_auroc_workspace_bytes(uint32_t n_cfg);
 
 /* For each configuration g (cfgs: HOST array of n_cfg entries, validated and
- * copied into ws during the call):
+ * copied into ws during the call, or by its kernel where n_cfg <= 32):
  *   counts[g][0..2] = G, E, pairs with G = #{(t, i in M, j not in M):
  *       m_ti > m_tj}, E the ties (Eq. 5 summed over canaries; Eq. 6 as
  *       printed is G / pairs, the Mann-Whitney value (G + E/2) / pairs);

@@ -726,18 +726,25 @@ int check_auroc_outputs(const char* fn, uint32_t flags, uint64_t* counts, uint64
     return CDT_OK;
 }
 
+int check_table_buffer(const char* fn, size_t n_cfg, const void* table, size_t table_bytes) {
+    const size_t need = cdt_auroc_workspace_bytes(static_cast<uint32_t>(n_cfg));
+    if (!table || table_bytes < need)
+        return fail(CDT_EINVAL, "%s: workspace of %zu bytes needed, %zu given", fn, need,
+                    table ? table_bytes : 0);
+    if (!aligned16(table)) return fail(CDT_EALIGN, "%s: ws must be 16-byte aligned", fn);
+    return CDT_OK;
+}
+
 // Copy a validated table (held in library-owned pageable memory, see
 // validated_table) into the device buffer `table` on `st`.  A copy from
 // pageable host memory completes before hipMemcpyAsync returns, so the host
 // table may be released afterwards.
 int upload_table(const char* fn, const std::vector<cdt_auroc_cfg>& cfgs, void* table,
                  size_t table_bytes, hipStream_t st) {
-    const size_t need = cdt_auroc_workspace_bytes(static_cast<uint32_t>(cfgs.size()));
-    if (!table || table_bytes < need)
-        return fail(CDT_EINVAL, "%s: workspace of %zu bytes needed, %zu given", fn, need,
-                    table ? table_bytes : 0);
-    if (!aligned16(table)) return fail(CDT_EALIGN, "%s: ws must be 16-byte aligned", fn);
-    const hipError_t e = hipMemcpyAsync(table, cfgs.data(), need, hipMemcpyHostToDevice, st);
+    const int rc = check_table_buffer(fn, cfgs.size(), table, table_bytes);
+    if (rc) return rc;
+    const hipError_t e = hipMemcpyAsync(table, cfgs.data(), cfgs.size() * sizeof(cdt_auroc_cfg),
+                                        hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return device_status(e, fn);
     return CDT_OK;
 }
@@ -773,6 +780,15 @@ int cdt_auroc(uint32_t n_cfg, const cdt_auroc_cfg* cfgs, const float* scores, ui
                 return fail(CDT_EINVAL, "cdt_auroc: scores is NULL");
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (cdt::auroc_in_args(n_cfg)) {
+        rc = check_table_buffer("cdt_auroc", n_cfg, ws, ws_bytes);
+        if (rc) return rc;
+        return device_status(
+            cdt::launch_auroc_args(n_cfg, reinterpret_cast<const cdt::AurocCfgDev*>(table.data()),
+                                   static_cast<cdt::AurocCfgDev*>(ws), scores, n_scores, seed,
+                                   flags, counts, pooled, baseline, st),
+            "cdt_auroc");
+    }
     rc = upload_table("cdt_auroc", table, ws, ws_bytes, st);
     if (rc) return rc;
     return device_status(cdt::launch_auroc(n_cfg, static_cast<const cdt::AurocCfgDev*>(ws),
@@ -845,6 +861,12 @@ int cdt_auroc_canaries(uint32_t n_cfg, const cdt_auroc_cfg* cfgs, const float* s
                     ws ? ws_bytes : 0);
     if (!aligned16(ws)) return fail(CDT_EALIGN, "%s: ws must be 16-byte aligned", fn);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (cdt::auroc_in_args(n_cfg))
+        return device_status(
+            cdt::launch_auroc_canaries_args(
+                n_cfg, reinterpret_cast<const cdt::AurocCfgDev*>(table.data()), scores, n_scores,
+                seed, flags, per_canary, st),
+            fn);
     // from pageable host memory: the copy completes before the call returns
     const hipError_t e = hipMemcpyAsync(ws, staged.data(), staged.size(), hipMemcpyHostToDevice,
                                         st);

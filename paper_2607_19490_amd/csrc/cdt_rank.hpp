@@ -13,4 +13,10 @@ hipError_t launch_auroc_canaries(uint32_t n_cfg, const AurocCfgDev* cfgs_dev,
                                  uint64_t n_scores, uint64_t seed, uint32_t flags,
                                  uint32_t* per_canary, hipStream_t st);
 
+// The same from a host table that travels in the launch's arguments
+// (auroc_in_args).
+hipError_t launch_auroc_canaries_args(uint32_t n_cfg, const AurocCfgDev* cfgs,
+                                      const float* scores, uint64_t n_scores, uint64_t seed,
+                                      uint32_t flags, uint32_t* per_canary, hipStream_t st);
+
 }  // namespace cdt

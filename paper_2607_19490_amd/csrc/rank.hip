@@ -56,6 +56,36 @@ __device__ __forceinline__ bool cfg_in_bounds(const AurocCfgDev& cfg, uint64_t n
 
 constexpr unsigned long long kBadCfg = ~0ull;  // counts of a configuration out of bounds
 
+// Where a workgroup finds its configuration: in a device table, or in the
+// launch's own arguments.  cdt_auroc and cdt_auroc_canaries are given host
+// tables, and a copy of a small one costs as much as the ranking itself (the
+// host waits for a staged copy, the GPU for its turn in the stream): up to
+// kArgCfgs configurations (1 KB of arguments) travel with the launch.  The
+// pipeline of 4 x 8 x 16 x 256 takes 46.6 us a step (48.7 us with the copy), a
+// Table 1 attack of 12 x 100 x 48 x 768 321 us (324 us).
+struct CfgTable {
+    const AurocCfgDev* cfgs;
+    const uint64_t* offsets;  // per-canary counts: canaries of the configurations before
+    __device__ __forceinline__ AurocCfgDev cfg(uint32_t g) const { return cfgs[g]; }
+    __device__ __forceinline__ uint64_t offset(uint32_t g) const { return offsets[g]; }
+    __device__ __forceinline__ void keep(uint32_t) const {}
+};
+
+constexpr uint32_t kArgCfgs = 32;
+struct CfgArgs {
+    AurocCfgDev cfgs[kArgCfgs];
+    AurocCfgDev* table;  // also left here, as a copy would have
+    __device__ __forceinline__ AurocCfgDev cfg(uint32_t g) const { return cfgs[g]; }
+    __device__ __forceinline__ uint64_t offset(uint32_t g) const {
+        uint64_t before = 0;
+        for (uint32_t i = 0; i < g; ++i) before += cfgs[i].C;
+        return before;
+    }
+    __device__ __forceinline__ void keep(uint32_t g) const {
+        if (threadIdx.x == 0) table[g] = cfgs[g];
+    }
+};
+
 // What one wave needs to rank a configuration's canaries, `per_wave` at a
 // time: lane = (canary within the wave) * width + shard, width the power of
 // two from S on.
@@ -139,10 +169,9 @@ __device__ __forceinline__ float lane_score(const RankCtx& r, const AurocCfgDev&
 
 // Eqs. 5-6 counts of configuration cfg_index (every thread of the workgroup calls it).
 __device__ __forceinline__ void counts_body(
-    uint32_t cfg_index, const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores,
+    uint32_t cfg_index, const AurocCfgDev& cfg, const float* __restrict__ scores,
     uint64_t n_scores, Key key, uint32_t flags, unsigned long long* __restrict__ counts,
     unsigned long long* __restrict__ baseline) {
-    const AurocCfgDev cfg = cfgs[cfg_index];
     if (!cfg_in_bounds(cfg, n_scores)) {  // uniform over the workgroup
         if (threadIdx.x == 0) {
             for (int q = 0; q < 6; ++q) counts[6ull * cfg_index + q] = kBadCfg;
@@ -199,14 +228,14 @@ __device__ __forceinline__ void counts_body(
 
 // Eq. 5 per canary: the same ranking as auroc_counts_kernel, each canary's
 // six counts summed over its lanes and written by the first of them to
-// out[(offset[g] + t) * 6 + q].  A configuration out of bounds gets
+// out[(offset(g) + t) * 6 + q].  A configuration out of bounds gets
 // 0xFFFFFFFF in its entries instead of being read.
+template <typename Src>
 __global__ __launch_bounds__(kCountThreads) void auroc_canaries_kernel(
-    const AurocCfgDev* __restrict__ cfgs, const uint64_t* __restrict__ offsets,
-    const float* __restrict__ scores, uint64_t n_scores, Key key, uint32_t flags,
+    Src src, const float* __restrict__ scores, uint64_t n_scores, Key key, uint32_t flags,
     uint32_t* __restrict__ out) {
-    const AurocCfgDev cfg = cfgs[blockIdx.x];
-    uint32_t* o = out + 6ull * offsets[blockIdx.x];
+    const AurocCfgDev cfg = src.cfg(blockIdx.x);
+    uint32_t* o = out + 6ull * src.offset(blockIdx.x);
     const uint32_t wave = threadIdx.x / kWave;
     if (!cfg_in_bounds(cfg, n_scores)) {  // uniform over the workgroup
         for (uint64_t i = threadIdx.x; i < 6ull * cfg.C; i += kCountThreads) o[i] = ~0u;
@@ -339,12 +368,11 @@ __device__ __forceinline__ void place_keys(const uint32_t* v, uint32_t P2,
 // Pooled Mann-Whitney counts of configuration cfg_index (every thread of the
 // workgroup calls it).
 __device__ __forceinline__ void pooled_body(
-    uint32_t cfg_index, const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores,
+    uint32_t cfg_index, const AurocCfgDev& cfg, const float* __restrict__ scores,
     uint64_t n_scores, unsigned long long* __restrict__ pooled) {
     __shared__ uint32_t v[kPoolKeys];
     __shared__ uint8_t shards[kWave];
     __shared__ unsigned long long red[2][kPoolThreads / kWave];
-    const AurocCfgDev cfg = cfgs[cfg_index];
     unsigned long long* out = pooled + 3ull * cfg_index;
     if (!cfg_in_bounds(cfg, n_scores) ||
         static_cast<uint64_t>(cfg.S) * cfg.C > kPoolMax) {  // uniform over the workgroup
@@ -434,11 +462,12 @@ __device__ __forceinline__ void pooled_body(
     }
 }
 
+template <typename Src>
 __global__ __launch_bounds__(kCountThreads) void auroc_counts_kernel(
-    const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
-    Key key, uint32_t flags, unsigned long long* __restrict__ counts,
-    unsigned long long* __restrict__ baseline) {
-    counts_body(blockIdx.x, cfgs, scores, n_scores, key, flags, counts, baseline);
+    Src src, const float* __restrict__ scores, uint64_t n_scores, Key key, uint32_t flags,
+    unsigned long long* __restrict__ counts, unsigned long long* __restrict__ baseline) {
+    src.keep(blockIdx.x);
+    counts_body(blockIdx.x, src.cfg(blockIdx.x), scores, n_scores, key, flags, counts, baseline);
 }
 
 // The counts and the pooled ranking of a configuration, a workgroup each in
@@ -450,14 +479,18 @@ __global__ __launch_bounds__(kCountThreads) void auroc_counts_kernel(
 // 12.1 us (34.5 us); 40 of 48 x 240 scores, with the per-canary counts and
 // every launch, 59 us (498 us).
 static_assert(kCountThreads == kPoolThreads, "one workgroup shape for both parts");
+template <typename Src>
 __global__ __launch_bounds__(kCountThreads) void auroc_counts_pooled_kernel(
-    const AurocCfgDev* __restrict__ cfgs, const float* __restrict__ scores, uint64_t n_scores,
-    Key key, uint32_t flags, unsigned long long* __restrict__ counts,
-    unsigned long long* __restrict__ baseline, unsigned long long* __restrict__ pooled) {
-    if (blockIdx.y)
-        pooled_body(blockIdx.x, cfgs, scores, n_scores, pooled);
-    else
-        counts_body(blockIdx.x, cfgs, scores, n_scores, key, flags, counts, baseline);
+    Src src, const float* __restrict__ scores, uint64_t n_scores, Key key, uint32_t flags,
+    unsigned long long* __restrict__ counts, unsigned long long* __restrict__ baseline,
+    unsigned long long* __restrict__ pooled) {
+    const AurocCfgDev cfg = src.cfg(blockIdx.x);
+    if (blockIdx.y) {
+        pooled_body(blockIdx.x, cfg, scores, n_scores, pooled);
+    } else {
+        src.keep(blockIdx.x);
+        counts_body(blockIdx.x, cfg, scores, n_scores, key, flags, counts, baseline);
+    }
 }
 
 // Eq. 6 from integer counts: G / pairs (ties count 0, the equation as
@@ -508,35 +541,79 @@ hipError_t launch_auroc_values(uint32_t n_cfg, const uint64_t* counts, const uin
     return hipGetLastError();
 }
 
+namespace {
+
+CfgArgs cfg_args(uint32_t n_cfg, const AurocCfgDev* cfgs, AurocCfgDev* table) {
+    CfgArgs a{};
+    for (uint32_t g = 0; g < n_cfg; ++g) a.cfgs[g] = cfgs[g];
+    a.table = table;
+    return a;
+}
+
+template <typename Src>
+hipError_t launch_canaries_t(const Src& src, uint32_t n_cfg, const float* scores,
+                             uint64_t n_scores, uint64_t seed, uint32_t flags,
+                             uint32_t* per_canary, hipStream_t st) {
+    if (n_cfg == 0) return hipSuccess;
+    const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
+    hipLaunchKernelGGL(auroc_canaries_kernel<Src>, dim3(n_cfg), dim3(kCountThreads), 0, st, src,
+                       scores, n_scores, key, flags, per_canary);
+    return hipGetLastError();
+}
+
+template <typename Src>
+hipError_t launch_auroc_t(const Src& src, uint32_t n_cfg, const float* scores, uint64_t n_scores,
+                          uint64_t seed, uint32_t flags, uint64_t* counts, uint64_t* pooled,
+                          uint64_t* baseline, hipStream_t st) {
+    if (n_cfg == 0) return hipSuccess;
+    const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
+    if (flags & 2u) {
+        hipLaunchKernelGGL(auroc_counts_pooled_kernel<Src>, dim3(n_cfg, 2), dim3(kCountThreads),
+                           0, st, src, scores, n_scores, key, flags,
+                           reinterpret_cast<unsigned long long*>(counts),
+                           reinterpret_cast<unsigned long long*>(baseline),
+                           reinterpret_cast<unsigned long long*>(pooled));
+    } else {
+        hipLaunchKernelGGL(auroc_counts_kernel<Src>, dim3(n_cfg), dim3(kCountThreads), 0, st, src,
+                           scores, n_scores, key, flags,
+                           reinterpret_cast<unsigned long long*>(counts),
+                           reinterpret_cast<unsigned long long*>(baseline));
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool auroc_in_args(uint32_t n_cfg) { return n_cfg <= kArgCfgs; }
+
 hipError_t launch_auroc_canaries(uint32_t n_cfg, const AurocCfgDev* cfgs_dev,
                                  const uint64_t* offsets_dev, const float* scores,
                                  uint64_t n_scores, uint64_t seed, uint32_t flags,
                                  uint32_t* per_canary, hipStream_t st) {
-    if (n_cfg == 0) return hipSuccess;
-    const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
-    hipLaunchKernelGGL(auroc_canaries_kernel, dim3(n_cfg), dim3(kCountThreads), 0, st, cfgs_dev,
-                       offsets_dev, scores, n_scores, key, flags, per_canary);
-    return hipGetLastError();
+    return launch_canaries_t(CfgTable{cfgs_dev, offsets_dev}, n_cfg, scores, n_scores, seed,
+                             flags, per_canary, st);
+}
+
+hipError_t launch_auroc_canaries_args(uint32_t n_cfg, const AurocCfgDev* cfgs,
+                                      const float* scores, uint64_t n_scores, uint64_t seed,
+                                      uint32_t flags, uint32_t* per_canary, hipStream_t st) {
+    return launch_canaries_t(cfg_args(n_cfg, cfgs, nullptr), n_cfg, scores, n_scores, seed, flags,
+                             per_canary, st);
 }
 
 hipError_t launch_auroc(uint32_t n_cfg, const AurocCfgDev* cfgs_dev, const float* scores,
                         uint64_t n_scores, uint64_t seed, uint32_t flags, uint64_t* counts,
                         uint64_t* pooled, uint64_t* baseline, hipStream_t st) {
-    if (n_cfg == 0) return hipSuccess;
-    const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
-    if (flags & 2u) {
-        hipLaunchKernelGGL(auroc_counts_pooled_kernel, dim3(n_cfg, 2), dim3(kCountThreads), 0, st,
-                           cfgs_dev, scores, n_scores, key, flags,
-                           reinterpret_cast<unsigned long long*>(counts),
-                           reinterpret_cast<unsigned long long*>(baseline),
-                           reinterpret_cast<unsigned long long*>(pooled));
-    } else {
-        hipLaunchKernelGGL(auroc_counts_kernel, dim3(n_cfg), dim3(kCountThreads), 0, st,
-                           cfgs_dev, scores, n_scores, key, flags,
-                           reinterpret_cast<unsigned long long*>(counts),
-                           reinterpret_cast<unsigned long long*>(baseline));
-    }
-    return hipGetLastError();
+    return launch_auroc_t(CfgTable{cfgs_dev, nullptr}, n_cfg, scores, n_scores, seed, flags,
+                          counts, pooled, baseline, st);
+}
+
+hipError_t launch_auroc_args(uint32_t n_cfg, const AurocCfgDev* cfgs, AurocCfgDev* table,
+                             const float* scores, uint64_t n_scores, uint64_t seed,
+                             uint32_t flags, uint64_t* counts, uint64_t* pooled,
+                             uint64_t* baseline, hipStream_t st) {
+    return launch_auroc_t(cfg_args(n_cfg, cfgs, table), n_cfg, scores, n_scores, seed, flags,
+                          counts, pooled, baseline, st);
 }
 
 }  // namespace cdt

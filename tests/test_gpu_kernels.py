@@ -541,3 +541,33 @@ def test_ref_synth_rows(gpu, shape):
     got = cdt.ref_synth(S, C, T, H, 7, 3, to_dev(torch, gain))
     torch.cuda.synchronize()
     np.testing.assert_array_equal(got.cpu().numpy(), oracle.ref_synth(S, C, T, H, 7, 3, gain))
+
+
+# Host tables either side of what travels in a launch's arguments (32
+# configurations): the counts of an uploaded table, the oracle's per-canary
+# ones, and the table left in the workspace.
+@pytest.mark.parametrize("n", [1, 31, 32, 33])
+def test_auroc_host_table_sizes(gpu, n):
+    torch, cdt = gpu
+    announce(f"auroc host table of {n}")
+    tables = [inputs.scores(2 + g % 5, 2 + g % 7, seed=g, gap=0.3, mal=[g % 2]) for g in range(n)]
+    cfgs, off = [], 0
+    for g, t in enumerate(tables):
+        C, S = t.shape
+        cfgs.append((S, C, off, 1 << (g % 2), g, 5 * g))
+        off += S * C
+    flat = to_dev(torch, np.concatenate([t.ravel() for t in tables]))
+    for flags in (9, 11):
+        ws = torch.zeros(max(16, 32 * n), dtype=torch.uint8, device="cuda")
+        got = cdt.auroc(cfgs, flat, seed=3, flags=flags, ws=ws)
+        table, _ = cdt.auroc_upload(cfgs, flat.numel(), flags=flags)
+        want = cdt.auroc_launch(table, n, flat, seed=3, flags=flags)
+        per = cdt.auroc_canaries(cfgs, flat, seed=3, flags=9)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert (a is None and b is None) or torch.equal(a, b)
+        assert torch.equal(ws[:32 * n], table[:32 * n])
+        np.testing.assert_array_equal(
+            per.cpu().numpy().view(np.uint32),
+            np.concatenate([oracle.auroc_canaries(t, c[3], seed=3, cfg_id=c[4], canary_base=c[5],
+                                                  flags=9) for t, c in zip(tables, cfgs)]))
