@@ -12,6 +12,7 @@ uint16 words of the C ABI).
 """
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -167,23 +168,31 @@ def _check(rc):
         raise CdtError(rc, lib().cdt_last_error().decode())
 
 
+_TORCH = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
 
 
 def _stream():
+    """The current device's current stream, as hipStream_t bits.  The raw
+    handle, since torch.cuda.current_stream() builds a Stream object per call
+    (2.8 us of a 9 us launch)."""
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need(t, name, dtype, shape=None):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if not t.is_cuda:
         raise ValueError(f"{name} must live on the GPU")
@@ -191,14 +200,16 @@ def _need(t, name, dtype, shape=None):
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
 def _empty(shape, dtype, like=None):
     torch = _torch()
-    dev = like.device if like is not None else torch.device("cuda", torch.cuda.current_device())
-    return torch.empty(shape, dtype=dtype, device=dev)
+    if like is not None:
+        return torch.empty(shape, dtype=dtype, device=like.device)
+    return torch.empty(shape, dtype=dtype,
+                       device=torch.device("cuda", torch.cuda.current_device()))
 
 
 def version():
@@ -499,14 +510,22 @@ def cosine_score_f16ref(h, r, out=None, sums=None, ws=None):
     return _drift(lib().cdt_cosine_score_f16ref, h, r, _torch().float16, out, sums, 3, ws)
 
 
+_CFG5, _CFG6 = struct.Struct("=IIQQI4x"), struct.Struct("=IIQQII")  # AurocCfg, base 0 or given
+
+
 def auroc_cfg_array(cfgs):
     """cfgs: iterable of (S, C, score_off, pos_mask, cfg_id[, canary_base])
     -> ctypes array."""
     cfgs = list(cfgs)
     arr = (AurocCfg * max(1, len(cfgs)))()
-    for i, cfg in enumerate(cfgs):
-        S, C, off, mask, cid = cfg[:5]
-        arr[i] = AurocCfg(S, C, off, mask, cid, cfg[5] if len(cfg) > 5 else 0)
+    try:  # 216 configurations: 22 us packed, 154 us a ctypes structure each
+        packed = b"".join([_CFG5.pack(*c) if len(c) == 5 else _CFG6.pack(*c[:6]) for c in cfgs])
+    except struct.error:  # values ctypes wraps to the field's width, or refuses itself
+        for i, cfg in enumerate(cfgs):
+            S, C, off, mask, cid = cfg[:5]
+            arr[i] = AurocCfg(S, C, off, mask, cid, cfg[5] if len(cfg) > 5 else 0)
+    else:
+        ctypes.memmove(arr, packed, len(packed))
     return arr, len(cfgs)
 
 
@@ -577,7 +596,7 @@ def auroc_canaries(cfgs, scores, *, seed=0, flags=AUROC_CONTROL | AUROC_RANDOM, 
     torch = _torch()
     _need(scores, "scores", torch.float32)
     arr, n = auroc_cfg_array(cfgs)
-    total = sum(int(c[1]) for c in cfgs)
+    total = int(np.frombuffer(arr, dtype=np.uint32)[1::8][:n].sum(dtype=np.uint64))  # their C
     out = _empty((max(total, 1), 6), torch.int32, scores) if out is None else out
     _need(out, "out", torch.int32)
     if out.numel() < 6 * total:
@@ -587,7 +606,7 @@ def auroc_canaries(cfgs, scores, *, seed=0, flags=AUROC_CONTROL | AUROC_RANDOM, 
     _need(ws, "ws", torch.uint8)
     _check(lib().cdt_auroc_canaries(n, arr, _ptr(scores), scores.numel(), seed, flags, _ptr(out),
                                     _ptr(ws), ws.numel(), _stream()))
-    return out[:total]
+    return out if out.dim() > 0 and out.shape[0] == total else out[:total]
 
 
 VALUE_NAMES = ("auroc", "auroc_mw", "control", "control_mw", "pooled", "pooled_mw", "random",

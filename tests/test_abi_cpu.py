@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
 
 from tests.conftest import ROOT
@@ -337,3 +338,20 @@ def test_batch_calls_validate_every_job_on_the_host(cdt):
     assert L.cdt_canary_sim_batch(2, sj, 16, 8, None) == cdt.EINVAL
     assert "workspace" in _err(cdt)
     assert L.cdt_canary_sim_stream(2, 2, 3, 12, None, None, None) == cdt.EINVAL
+
+
+def test_cfg_array_forms(cdt):
+    """The packed table equals one ctypes structure per configuration, for
+    values that fit their fields, values that ctypes wraps, and both lengths."""
+    cfgs = [(3, 4, 0, 1, 2), (64, 1 << 30, 1 << 40, (1 << 64) - 1, (1 << 24) - 1, (1 << 32) - 1),
+            [2, 2, 5, 1, 0], (np.int64(2), True, np.uint64(7), 2, 1)]
+    for extra in ([], [(4, 4, 0, -1, 0)], [(4, 4, 0, 1 << 64, 0, 1 << 32)], [(4, 4, -8, 1, 0, -2)]):
+        arr, n = cdt.auroc_cfg_array(iter(cfgs + extra))
+        assert n == len(cfgs + extra)
+        want = (cdt.AurocCfg * n)()
+        for i, c in enumerate(cfgs + extra):
+            want[i] = cdt.AurocCfg(*c)
+        assert bytes(arr) == bytes(want)
+    assert cdt.auroc_cfg_array([])[1] == 0
+    with pytest.raises(TypeError):
+        cdt.auroc_cfg_array([(2.0, 2, 0, 1, 0)])
