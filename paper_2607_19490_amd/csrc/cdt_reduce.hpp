@@ -4,7 +4,8 @@
 // of Eq. 4 and its cosine variant.  A block (shard, canary) of n = T*H
 // elements is cut into chunks of kReduceChunkElems; one workgroup reduces
 // one chunk to fp64 partial sums in a fixed order (no atomics); a combine
-// kernel adds a block's partials in chunk order.
+// kernel, or a workgroup that holds all of a block's chunks, adds them in
+// chunk order.
 #pragma once
 
 #include <stdint.h>
@@ -66,10 +67,27 @@ namespace {
 
 constexpr int kWavesPerGroup = kReduceThreads / kWave;
 
-// Sum kN per-thread values over the workgroup; thread 0 gets the result.
-template <int kN>
-__device__ __forceinline__ void block_sum(double (&v)[kN]) {
-    __shared__ double lds[kN][kWavesPerGroup];
+// Blocks of kReduceTeam chunks can be reduced by one workgroup of as many times
+// kReduceThreads threads, which does the combine's addition too: a launch less,
+// the same bits.  Eq. 4 takes it up to kTeamMostBlocks blocks (fp32 reference;
+// 8 x 64 x 64 x 1024 32.8 us, 35.0 us with the combine; 12 x 100 x 48 x 768 46.2
+// against 47.4 us, its fp16 reference 30.4 against 31.4 us): beyond, the launch
+// is a small part and workgroups that wait for their slower half cost more
+// (16 x 256 x 8 x 8192 241 against 240 us, 32 x 200 x 40 x 1024 229 against 226
+// us).  The exact-norm sums, which are bound by arithmetic, take it from
+// kTeamLeastBlocks on (12 x 100 x 48 x 768 62 against 64 us): fewer blocks do not
+// fill the CUs with workgroups twice the size (4 x 16 x 48 x 768 15.3 against
+// 11.5 us).
+constexpr int kReduceTeam = 2;
+constexpr uint64_t kTeamMostBlocks = 2048, kTeamLeastBlocks = 512;
+
+// Sum kN per-thread values over a workgroup of kTeam chunks, kReduceThreads
+// threads each: every chunk's total as block_sum forms it, then the totals
+// from 0 in chunk order, as the combine kernels add them.  Thread 0 gets the
+// result.
+template <int kN, int kTeam>
+__device__ __forceinline__ void team_sum(double (&v)[kN]) {
+    __shared__ double lds[kN][kTeam * kWavesPerGroup];
 #pragma unroll
     for (int k = 0; k < kN; ++k) v[k] = wave_sum(v[k]);
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -81,12 +99,22 @@ __device__ __forceinline__ void block_sum(double (&v)[kN]) {
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < kN; ++k) {
-            double t = 0.0;
-            for (int w = 0; w < kWavesPerGroup; ++w) t += lds[k][w];
-            v[k] = t;
+            double all = 0.0;
+            for (int m = 0; m < kTeam; ++m) {
+                double t = 0.0;
+                for (int w = 0; w < kWavesPerGroup; ++w) t += lds[k][m * kWavesPerGroup + w];
+                all = kTeam == 1 ? t : all + t;
+            }
+            v[k] = all;
         }
     }
     __syncthreads();
+}
+
+// One chunk per workgroup.
+template <int kN>
+__device__ __forceinline__ void block_sum(double (&v)[kN]) {
+    team_sum<kN, 1>(v);
 }
 
 // Per-metric element step.  h and the reference are widened exactly to

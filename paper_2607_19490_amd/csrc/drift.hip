@@ -87,19 +87,19 @@ __device__ __forceinline__ uint32_t fold_group(const u32x4& hv, const u32x4& rv,
 // direct (a block is one chunk): the chunk's sums are the block's, and the
 // score is written here; the combine launch is skipped (it would add the one
 // partial to zero, which changes nothing).
-// kU whole rounds of the workgroup (every thread's group is in range) from
-// group `base` on: all loads first, then the sums.
+// kU whole rounds of a chunk's kReduceThreads threads (tid of them, every
+// thread's group in range) from group `base` on: all loads first, then the sums.
 template <DriftMetric kM, bool kReadOnly, int kU>
 __device__ __forceinline__ void drift_rounds(gptr<const u32x4> hb, gptr<const f32x4> ab,
-                                             gptr<const u32x4> rb, uint32_t base,
+                                             gptr<const u32x4> rb, uint32_t base, uint32_t tid,
                                              double (&acc)[DriftTraits<kM>::kSums],
                                              uint32_t& fold) {
     u32x4 hv[kU], rv[kU];
     f32x4 a0[kU], a1[kU];
-    const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
+    const uint32_t lane = tid % kWave, wave0 = tid - lane;
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-        const uint32_t g = base + u * kReduceThreads + threadIdx.x;
+        const uint32_t g = base + u * kReduceThreads + tid;
         hv[u] = __builtin_nontemporal_load(hb + g);
         rv[u] = u32x4{0u, 0u, 0u, 0u};
         a0[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -132,12 +132,12 @@ __device__ __forceinline__ void drift_rounds(gptr<const u32x4> hb, gptr<const f3
 // the 16 x 128 x 256 x 8192 step of three runs takes 17.8 ms, not 15.7.
 // Shared by the single-array and batched launches.
 template <DriftMetric kM, bool kReadOnly>
-__device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
-                                            const void* __restrict__ ref, uint32_t n8,
-                                            uint64_t chunks_per_block, uint32_t chunk_groups,
-                                            uint64_t chunk, double* __restrict__ partial,
-                                            uint32_t S, uint32_t C, float* __restrict__ score,
-                                            double* __restrict__ sums) {
+__device__ __forceinline__ void drift_chunk_sums(const uint16_t* __restrict__ h,
+                                                 const void* __restrict__ ref, uint32_t n8,
+                                                 uint64_t chunks_per_block, uint32_t chunk_groups,
+                                                 uint64_t chunk, uint32_t tid,
+                                                 double (&acc)[DriftTraits<kM>::kSums],
+                                                 uint32_t& fold) {
     using Tr = DriftTraits<kM>;
     const uint64_t n = static_cast<uint64_t>(n8) * 8;
     const uint64_t b = chunk / chunks_per_block;
@@ -150,27 +150,26 @@ __device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
         rb = global_ptr(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(ref) + b * n));
     else
         ab = global_ptr(reinterpret_cast<const f32x4*>(static_cast<const float*>(ref) + b * n));
-    double acc[Tr::kSums];
 #pragma unroll
     for (int k = 0; k < Tr::kSums; ++k) acc[k] = 0.0;
-    uint32_t fold = 0, base = g0;
+    uint32_t base = g0;
     for (; base + kReduceThreads * kReduceUnroll <= g_end; base += kReduceThreads * kReduceUnroll)
-        drift_rounds<kM, kReadOnly, kReduceUnroll>(hb, ab, rb, base, acc, fold);
+        drift_rounds<kM, kReadOnly, kReduceUnroll>(hb, ab, rb, base, tid, acc, fold);
     static_assert(kReduceUnroll == 8, "steps of 4, 2 and 1 make up the rest");
-    const uint32_t rest = (g_end - base) / kReduceThreads;  // workgroup-uniform
+    const uint32_t rest = (g_end - base) / kReduceThreads;  // uniform over the chunk's threads
     if (rest & 4u) {
-        drift_rounds<kM, kReadOnly, 4>(hb, ab, rb, base, acc, fold);
+        drift_rounds<kM, kReadOnly, 4>(hb, ab, rb, base, tid, acc, fold);
         base += kReduceThreads * 4;
     }
     if (rest & 2u) {
-        drift_rounds<kM, kReadOnly, 2>(hb, ab, rb, base, acc, fold);
+        drift_rounds<kM, kReadOnly, 2>(hb, ab, rb, base, tid, acc, fold);
         base += kReduceThreads * 2;
     }
     if (rest & 1u) {
-        drift_rounds<kM, kReadOnly, 1>(hb, ab, rb, base, acc, fold);
+        drift_rounds<kM, kReadOnly, 1>(hb, ab, rb, base, tid, acc, fold);
         base += kReduceThreads;
     }
-    if (const uint32_t g = base + threadIdx.x; g < g_end) {
+    if (const uint32_t g = base + tid; g < g_end) {
         const u32x4 hv = __builtin_nontemporal_load(hb + g);
         u32x4 rv = u32x4{0u, 0u, 0u, 0u};
         f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f}, a1 = a0;
@@ -185,6 +184,20 @@ __device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
         else
             accumulate8<kM>(hv, rv, a0, a1, acc);
     }
+}
+
+template <DriftMetric kM, bool kReadOnly>
+__device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
+                                            const void* __restrict__ ref, uint32_t n8,
+                                            uint64_t chunks_per_block, uint32_t chunk_groups,
+                                            uint64_t chunk, double* __restrict__ partial,
+                                            uint32_t S, uint32_t C, float* __restrict__ score,
+                                            double* __restrict__ sums) {
+    using Tr = DriftTraits<kM>;
+    double acc[Tr::kSums];
+    uint32_t fold = 0;
+    drift_chunk_sums<kM, kReadOnly>(h, ref, n8, chunks_per_block, chunk_groups, chunk,
+                                    threadIdx.x, acc, fold);
     const bool direct = chunks_per_block == 1;
     if constexpr (kReadOnly) {
         if (fold == kFoldSentinel) {
@@ -213,6 +226,27 @@ __global__ __launch_bounds__(kReduceThreads) void drift_partial_kernel(
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x)
         drift_chunk<kM, kReadOnly>(h, ref, n8, chunks_per_block, chunk_groups,
                                    xcd_contiguous(it, total_chunks), partial, S, C, score, sums);
+}
+
+// A block of kTeam chunks in one workgroup, kReduceThreads threads to each,
+// which adds their sums as the combine kernel would and writes the score: the
+// same bits without the combine launch.
+template <DriftMetric kM, int kTeam>
+__global__ __launch_bounds__(kReduceThreads* kTeam) void drift_team_kernel(
+    const uint16_t* __restrict__ h, const void* __restrict__ ref, uint32_t n8,
+    uint32_t chunk_groups, uint64_t nblocks, uint32_t S, uint32_t C, float* __restrict__ score,
+    double* __restrict__ sums) {
+    using Tr = DriftTraits<kM>;
+    const uint32_t tid = threadIdx.x % kReduceThreads, member = threadIdx.x / kReduceThreads;
+    for (uint64_t it = blockIdx.x; it < nblocks; it += gridDim.x) {
+        const uint64_t b = xcd_contiguous(it, nblocks);
+        double acc[Tr::kSums];
+        uint32_t fold = 0;
+        drift_chunk_sums<kM, false>(h, ref, n8, kTeam, chunk_groups, b * kTeam + member, tid, acc,
+                                    fold);
+        team_sum<Tr::kSums, kTeam>(acc);
+        if (threadIdx.x == 0) finish_block<kM>(acc, b, S, C, score, sums);
+    }
 }
 
 // Eq. 4's element step for kJ arrays against one reference: the reference
@@ -452,6 +486,13 @@ hipError_t launch_drift_t(uint32_t S, uint32_t C, uint32_t T, uint32_t H, const 
     const uint64_t cpb = g.cpb, total = cpb * nblocks;
     double* partial = static_cast<double*>(ws);
     const bool direct = cpb == 1;
+    if (cpb == kReduceTeam && nblocks <= kTeamMostBlocks) {
+        hipLaunchKernelGGL((drift_team_kernel<kM, kReduceTeam>), dim3(reduce_grid(nblocks)),
+                           dim3(kReduceThreads * kReduceTeam), 0, st, h, ref,
+                           static_cast<uint32_t>(n / 8), g.chunk_groups, nblocks, S, C, score,
+                           sums);
+        return hipGetLastError();
+    }
     if (total > 0) {
         hipLaunchKernelGGL(drift_partial_kernel<kM>, dim3(reduce_grid(total)),
                            dim3(kReduceThreads), 0, st, h, ref, static_cast<uint32_t>(n / 8), cpb,

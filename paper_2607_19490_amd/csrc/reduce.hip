@@ -131,24 +131,39 @@ void sim_score_partial_kernel(
     }
 }
 
+// Scale and norms of block b.  Blocks of one chunk or of a team are finished by
+// the partial kernel; others leave their partial sums to tamper_scale_combine_kernel.
+__device__ __forceinline__ void finish_scale(double vv, double zz, uint64_t b, double eps,
+                                             float* __restrict__ tscale,
+                                             double* __restrict__ norms) {
+    tscale[b] = zz > 0.0 ? static_cast<float>(eps * sqrt(vv / zz)) : 0.0f;
+    if (norms) {
+        norms[2 * b] = vv;
+        norms[2 * b + 1] = zz;
+    }
+}
+
 // Norms for the exact-norm Gaussian tamper of Section 3.2, tau(v) = v +
 // eps ||v|| N / ||N||: per block vv = sum v^2 over the untampered output (the
 // benign a + delta, or a itself for the clean base) and zz = sum z^2 over
 // the TAMPER_ADD normals, both in fp64.  A scale c = eps sqrt(vv / zz) on
 // those normals adds a perturbation of norm eps ||v||.
-template <bool kT3, bool kBlock>
-__global__ __launch_bounds__(kReduceThreads) void tamper_norms_partial_kernel(
-    SimArgs A, const float* __restrict__ ref, double* __restrict__ partial) {
+template <bool kT3, bool kBlock, int kTeam>
+__global__ __launch_bounds__(kReduceThreads* kTeam) void tamper_norms_partial_kernel(
+    SimArgs A, const float* __restrict__ ref, double* __restrict__ partial, double eps,
+    float* __restrict__ tscale, double* __restrict__ norms) {
     const uint64_t n = static_cast<uint64_t>(A.n8) * 8;
-    for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x) {
-        const uint64_t chunk = xcd_contiguous(it, A.total_chunks);
+    const uint32_t tid = threadIdx.x % kReduceThreads, member = threadIdx.x / kReduceThreads;
+    const uint64_t units = A.total_chunks / kTeam;
+    for (uint64_t it = blockIdx.x; it < units; it += gridDim.x) {
+        const uint64_t chunk = xcd_contiguous(it, units) * kTeam + member;
         const uint64_t b = chunk / A.chunks_per_block;
         const uint32_t g0 = static_cast<uint32_t>(chunk - b * A.chunks_per_block) * A.chunk_groups;
         const uint32_t g_end = min(g0 + A.chunk_groups, A.n8);
         const SimBlock B = sim_block<kBlock>(A, b);
         const f32x4* ab = reinterpret_cast<const f32x4*>(ref + b * n);
         double acc[2] = {0.0, 0.0};
-        for (uint32_t g = g0 + threadIdx.x; g < g_end; g += kReduceThreads) {
+        for (uint32_t g = g0 + tid; g < g_end; g += kReduceThreads) {
             const f32x4 lo = ab[2 * g], hi = ab[2 * g + 1];
             const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             float v[8], z[8];
@@ -167,10 +182,14 @@ __global__ __launch_bounds__(kReduceThreads) void tamper_norms_partial_kernel(
                 acc[1] = fma(zd, zd, acc[1]);
             }
         }
-        block_sum<2>(acc);
+        team_sum<2, kTeam>(acc);
         if (threadIdx.x == 0) {
-            partial[chunk * 2] = acc[0];
-            partial[chunk * 2 + 1] = acc[1];
+            if (kTeam > 1 || A.chunks_per_block == 1) {
+                finish_scale(acc[0], acc[1], b, eps, tscale, norms);
+            } else {
+                partial[chunk * 2] = acc[0];
+                partial[chunk * 2 + 1] = acc[1];
+            }
         }
     }
 }
@@ -280,11 +299,7 @@ __global__ void tamper_scale_combine_kernel(const double* __restrict__ partial,
         vv += partial[(b * chunks_per_block + i) * 2];
         zz += partial[(b * chunks_per_block + i) * 2 + 1];
     }
-    tscale[b] = zz > 0.0 ? static_cast<float>(eps * sqrt(vv / zz)) : 0.0f;
-    if (norms) {
-        norms[2 * b] = vv;
-        norms[2 * b + 1] = zz;
-    }
+    finish_scale(vv, zz, b, eps, tscale, norms);
 }
 
 // sum a^2 and sum |a| over one group of 8.
@@ -408,6 +423,20 @@ hipError_t launch_sim_score(const SimLaunch& p, const float* ref, uint16_t* h, f
                                 num_den, st);
 }
 
+template <bool kT3, bool kBlock>
+void launch_tamper_norms_t(const SimArgs& A, bool team, const float* ref, double* partial, double eps,
+                           float* tscale, double* norms, hipStream_t st) {
+    if (team)
+        hipLaunchKernelGGL((tamper_norms_partial_kernel<kT3, kBlock, kReduceTeam>),
+                           dim3(reduce_grid(A.total_chunks / kReduceTeam)),
+                           dim3(kReduceThreads * kReduceTeam), 0, st, A, ref, partial, eps, tscale,
+                           norms);
+    else
+        hipLaunchKernelGGL((tamper_norms_partial_kernel<kT3, kBlock, 1>),
+                           dim3(reduce_grid(A.total_chunks)), dim3(kReduceThreads), 0, st, A, ref,
+                           partial, eps, tscale, norms);
+}
+
 hipError_t launch_tamper_scale_exact(const SimLaunch& p, const float* ref, double eps,
                                      float* tscale, double* norms, void* ws, hipStream_t st) {
     const uint64_t n = static_cast<uint64_t>(p.T) * p.H;
@@ -415,24 +444,20 @@ hipError_t launch_tamper_scale_exact(const SimLaunch& p, const float* ref, doubl
     if (nblocks == 0) return hipSuccess;
     const ReduceShape shape = reduce_shape(n / 8);
     const uint64_t cpb = shape.cpb, total = cpb * nblocks;
+    const bool team = cpb == kReduceTeam && nblocks >= kTeamLeastBlocks;
     double* partial = static_cast<double*>(ws);
     if (total > 0) {
         const SimArgs A = make_sim_args(p, shape.chunk_groups, cpb, total);
-        const dim3 grid(reduce_grid(total)), block(kReduceThreads);
         if (A.t3 && A.block_mode)
-            hipLaunchKernelGGL((tamper_norms_partial_kernel<true, true>), grid, block, 0, st, A,
-                               ref, partial);
+            launch_tamper_norms_t<true, true>(A, team, ref, partial, eps, tscale, norms, st);
         else if (A.t3)
-            hipLaunchKernelGGL((tamper_norms_partial_kernel<true, false>), grid, block, 0, st, A,
-                               ref, partial);
+            launch_tamper_norms_t<true, false>(A, team, ref, partial, eps, tscale, norms, st);
         else if (A.block_mode)
-            hipLaunchKernelGGL((tamper_norms_partial_kernel<false, true>), grid, block, 0, st, A,
-                               ref, partial);
+            launch_tamper_norms_t<false, true>(A, team, ref, partial, eps, tscale, norms, st);
         else
-            hipLaunchKernelGGL((tamper_norms_partial_kernel<false, false>), grid, block, 0, st, A,
-                               ref, partial);
+            launch_tamper_norms_t<false, false>(A, team, ref, partial, eps, tscale, norms, st);
         const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || cpb == 1 || team) return e;
     }
     const uint64_t grid = (nblocks + 255) / 256;
     hipLaunchKernelGGL(tamper_scale_combine_kernel, dim3(static_cast<uint32_t>(grid)), dim3(256),

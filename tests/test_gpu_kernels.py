@@ -571,3 +571,42 @@ def test_auroc_host_table_sizes(gpu, n):
             per.cpu().numpy().view(np.uint32),
             np.concatenate([oracle.auroc_canaries(t, c[3], seed=3, cfg_id=c[4], canary_base=c[5],
                                                   flags=9) for t, c in zip(tables, cfgs)]))
+
+
+# Blocks of two chunks, either side of the block counts at which one workgroup
+# takes both (2048 for the scores, 512 for the exact-norm scale): a canary's
+# scores, sums and scales are the same bits in a slice of the array.  Block
+# sizes just above a chunk (a lane in the last round), even halves, and two
+# full chunks.
+@pytest.mark.parametrize("TH", [(17, 1928), (48, 768), (8, 8192)])
+def test_two_chunk_blocks_in_slices(gpu, TH):
+    torch, cdt = gpu
+    announce(f"two-chunk blocks {TH}")
+    C = 2049
+    g = torch.Generator(device="cuda").manual_seed(TH[1])
+    ref = torch.randn((1, C, *TH), generator=g, device="cuda")
+    h = (ref * 1.001).half()
+    r = (ref * 0.999).half()
+    bscale = torch.rand((1, C), generator=g, device="cuda") * 1e-3
+
+    def scores(k):
+        out = []
+        for fn, a, b, n in ((cdt.drift_score, h, ref, 2), (cdt.drift_score_f16ref, h, r, 2),
+                            (cdt.cosine_score, h, ref, 3), (cdt.cosine_score_f16ref, h, r, 3)):
+            sums = torch.full((k, 1, n), -1.0, dtype=torch.float64, device="cuda")
+            name = "num_den" if n == 2 else "sums"
+            out += [fn(a[:, :k], b[:, :k], **{name: sums}), sums]
+        return out
+
+    for a, b, c in zip(scores(C), scores(2048), scores(3)):
+        assert torch.equal(a[:2048], b) and torch.equal(a[:3], c)
+    want, _, _ = oracle.drift_score(h[:, :3].cpu().numpy().view(np.uint16), ref[:, :3].cpu().numpy())
+    assert rel_err(scores(3)[0].cpu().numpy(), want) < DRIFT_RTOL
+    for dist in (0, 1):
+        def scale(k):
+            norms = torch.full((1, k, 2), -1.0, dtype=torch.float64, device="cuda")
+            ts = cdt.tamper_scale_exact(ref[:, :k], 0.05, norms=norms, bscale=bscale[:, :k],
+                                        seed=8, cfg_id=21, benign_dist=dist, benign_mode=1)
+            return ts, norms
+        for a, b in zip(scale(512), scale(511)):
+            assert torch.equal(a[:, :511], b)
