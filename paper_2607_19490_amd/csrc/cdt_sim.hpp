@@ -114,16 +114,25 @@ struct SimBlock {
     BlockDraw draw;
 };
 
+// Block `block` = s * C + c of shard s and canary c (of this call's C).
 template <bool kBlock>
-__device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block) {
+__device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block, uint32_t s,
+                                              uint32_t c) {
     SimBlock B;
-    B.s = static_cast<uint32_t>(block / A.C);
-    B.c = A.canary_base + static_cast<uint32_t>(block - static_cast<uint64_t>(B.s) * A.C);
+    B.s = s;
+    B.c = A.canary_base + c;
     B.mal = (A.mal_mask >> B.s) & 1u;
     B.benign = benign_run<kBlock>(A, block);
     B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[block] : 0.0f;
     B.draw = block_draw(A.key, B.c, B.s);
     return B;
+}
+
+template <bool kBlock>
+__device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block) {
+    const uint32_t s = static_cast<uint32_t>(block / A.C);
+    return sim_block<kBlock>(A, block, s,
+                             static_cast<uint32_t>(block - static_cast<uint64_t>(s) * A.C));
 }
 
 // IEEE fp32 sqrt and division on the Student-t draw's own ranges.  q is a

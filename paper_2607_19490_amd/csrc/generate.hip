@@ -206,7 +206,7 @@ __device__ __forceinline__ void sim_chunk(const SimArgs& A, uint64_t chunk,
                                           uint16_t* __restrict__ h) {
     const uint64_t n = static_cast<uint64_t>(A.n8) * 8;
     const ChunkPos p = chunk_pos(chunk, A.chunks_per_block, A.C, A.chunk_groups);
-    const SimBlock B = sim_block<kBlock>(A, p.block);
+    const SimBlock B = sim_block<kBlock>(A, p.block, p.s, p.c);
     const gptr<const f32x4> in = global_ptr(reinterpret_cast<const f32x4*>(ref + p.block * n));
     const gptr<u32x4> out = global_ptr(reinterpret_cast<u32x4*>(h + p.block * n));
     const uint32_t g_end = min(p.g0 + A.chunk_groups, A.n8);
@@ -340,7 +340,9 @@ __global__ __launch_bounds__(kGenThreadsSmall) void canary_sim_batch_kernel(
 // Propagation model: a thread walks one group of 8 elements of one canary
 // through all S stages in order, carrying the live error in registers; a
 // workgroup chunk covers groups of one canary, so the per-stage block state is
-// workgroup-uniform.  Same bytes as the live pass (4 B read, 2 B written per
+// workgroup-uniform (and formed from s and c: found from the block index, its
+// division cost a seventh of a stage's instructions; 8 x 128 x 16 x 4096 58 us,
+// 62 us with it).  Same bytes as the live pass (4 B read, 2 B written per
 // element); nothing is re-read.  Loading the next stage's reference before the
 // current one is generated costs more registers than it hides (8 x 64 x 128 x
 // 4096 with its scales and Eq. 4: 740 against 729 us).
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(kThreads) void canary_chain_kernel(SimArgs A, uint3
             for (uint32_t s = 0; s < S; ++s) {
                 const f32x4 a_lo = load_stream(in), a_hi = load_stream(in + 1);
                 in += stage4;
-                const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(s) * A.C + c);
+                const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(s) * A.C + c, s, c);
                 store_stream(out,
                              chain_group8<kT3, kBlock>(A, B, g * 8, s == 0, gain, a_lo, a_hi, d));
                 out += stage4 / 2;

@@ -223,10 +223,10 @@ __global__ __launch_bounds__(kReduceThreads) void chain_norms_partial_kernel(
             for (uint32_t s = 0; s < m; ++s) {
                 const f32x4 a_lo = in[0], a_hi = in[1];
                 in += stage4;
-                const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(s) * A.C + c);
+                const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(s) * A.C + c, s, c);
                 chain_group8<kT3, kBlock>(A, B, g * 8, s == 0, gain, a_lo, a_hi, d);
             }
-            const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(m) * A.C + c);
+            const SimBlock B = sim_block<kBlock>(A, static_cast<uint64_t>(m) * A.C + c, m, c);
             const f32x4 lo = in[0], hi = in[1];
             const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             float u[8], v[8], z[8];
