@@ -112,6 +112,13 @@ __device__ __forceinline__ void drift_rounds(gptr<const u32x4> hb, gptr<const f3
                             __builtin_nontemporal_load(aw + kWave + lane), a0[u], a1[u]);
         }
     }
+    // Against an fp16 reference the compiler sinks each pair of loads to its
+    // sums otherwise (66 VGPRs, one pair in flight).  fp16-reference Eq. 4 and
+    // cosine, with the barrier and without: 16 x 256 x 8 x 8192 157 and 158
+    // against 163 and 166 us, 8 x 64 x 30 x 1024 10.4 and 10.4 against 15.2 and
+    // 17.1 us (8 x 64 x 65 x 1024, which seven waves a SIMD suit better than
+    // four, 23.5 and 24.0 against 22.6 and 22.9 us).
+    if constexpr (DriftTraits<kM>::kHalfRef) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
         if constexpr (kReadOnly)
