@@ -117,15 +117,21 @@ struct SimBlock {
 // Block `block` = s * C + c of shard s and canary c (of this call's C).
 template <bool kBlock>
 __device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block, uint32_t s,
-                                              uint32_t c) {
+                                              uint32_t c, const BlockDraw& draw) {
     SimBlock B;
     B.s = s;
     B.c = A.canary_base + c;
     B.mal = (A.mal_mask >> B.s) & 1u;
     B.benign = benign_run<kBlock>(A, block);
     B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[block] : 0.0f;
-    B.draw = block_draw(A.key, B.c, B.s);
+    B.draw = draw;
     return B;
+}
+
+template <bool kBlock>
+__device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block, uint32_t s,
+                                              uint32_t c) {
+    return sim_block<kBlock>(A, block, s, c, block_draw(A.key, A.canary_base + c, s));
 }
 
 template <bool kBlock>
@@ -194,6 +200,15 @@ __device__ __forceinline__ void benign8(const BenignRun& R, const BlockDraw& bd,
     }
 }
 
+// x + y as one instruction with its operands in this order: where both are
+// NaN the sum is the first, and the compiler, free to swap them, does so in
+// some of the kernels that must agree bit for bit.
+__device__ __forceinline__ float add_ordered(float x, float y) {
+    float r;
+    asm("v_add_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+
 // Eq. 3: the tampering of a malicious shard, in place on v (which holds the
 // benign output; the clean base replaces it by the noise-free base first).
 __device__ __forceinline__ void tamper8(const SimArgs& A, const SimBlock& B, const NormalBase& nb,
@@ -206,7 +221,7 @@ __device__ __forceinline__ void tamper8(const SimArgs& A, const SimBlock& B, con
         float zt[8];
         normals8(B.draw, nb, A.tag_add, zt);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = v[k] + B.tsc * zt[k];
+        for (int k = 0; k < 8; ++k) v[k] = add_ordered(B.tsc * zt[k], v[k]);
     }
     if (A.tamper & 2u) {
         const Words4 u0 = finish_draw(B.draw, draw_base(B.draw, e0 >> 2), A.tag_flip);

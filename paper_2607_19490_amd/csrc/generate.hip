@@ -246,15 +246,14 @@ __global__ __launch_bounds__(kThreads) void canary_sim_kernel(
         sim_chunk<kT3, kBlock, kStream, kThreads>(A, it, ref, h);
 }
 
-// One chunk of a unit of kJ runs over one reference, in a block that none of
-// them tampers with: each group of 8 references is loaded once, and the part
-// of its Philox calls that no run enters (normal_base: 2 of the 18 multiplies
-// of a call) is formed once for all of them.  The runs share one seed and
-// canary range (plan_batch_groups).  What every group of a run needs is held
-// in scalar registers from the chunk's start (read from the table per group,
-// the sweep's step takes 6.0 ms).  60 VGPRs with four Gaussian runs, 100 with
-// four Student-t ones.
-template <bool kT3, bool kBlock, int kJ>
+// One chunk of a unit of kJ Gaussian runs over one reference, in a block that
+// none of them tampers with: each group of 8 references is loaded once, and the
+// part of its Philox calls that no run enters (normal_base: 2 of the 18
+// multiplies of a call) is formed once for all of them.  The runs share one
+// seed and canary range (plan_batch_groups).  What every group of a run needs
+// is held in scalar registers from the chunk's start (read from the table per
+// group, the sweep's step takes 6.0 ms).  60 VGPRs with four runs.
+template <bool kBlock, int kJ>
 __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ unit,
                                                   const ChunkPos& p) {
     const SimArgs& A0 = unit[0].A;
@@ -289,7 +288,7 @@ __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ 
 #pragma unroll
         for (int j = 0; j < kJ; ++j) {
             float v[8];
-            benign8<kT3, kBlock>(run[j], bd, nb, g * 8, a, a, v);
+            benign8<false, kBlock>(run[j], bd, nb, g * 8, a, a, v);
             store_stream(out[j] + g, pack_half8(v));
             __builtin_amdgcn_sched_barrier(0);  // one run's temporaries at a time
         }
@@ -297,11 +296,64 @@ __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ 
     }
 }
 
+// One chunk of a unit of Student-t runs over one reference: the runs one after
+// another within each group of 8 elements, by one body for every run count,
+// tampered blocks included.  A group of a run is about 1000 instructions, so
+// what it needs can come from the table each time, where the four-fold
+// unrolled form was 62 KB of code, which the compiler unrolled by two only and
+// kept its runs' values in LDS.  12 KB, no LDS, 106 VGPRs (the runs share the
+// first rounds of all their draws but the flips'; 74 VGPRs, sharing those of
+// the one-normal streams alone, are up to 2% slower at large shapes).  Four
+// runs with one malicious shard, against the unrolled form: 4 x 32 x 16 x 512
+// 21.7 against 35.1 us, 12 x 100 x 48 x 768 484 against 493 us, 16 x 64 x 128 x
+// 8192 10.9 against 11.5 ms; every shard malicious 14.0 against 14.8 ms there.
+template <bool kBlock>
+__device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit,
+                                               uint32_t unit_jobs, const ChunkPos& p) {
+    const SimArgs& A0 = unit[0].A;
+    const uint64_t n = static_cast<uint64_t>(A0.n8) * 8;
+    const uint32_t g_end = min(p.g0 + A0.chunk_groups, A0.n8);
+    const gptr<const f32x4> in =
+        global_ptr(reinterpret_cast<const f32x4*>(unit[0].ref + p.block * n));
+    const BlockDraw bd = block_draw(A0.key, A0.canary_base + p.c, p.s);
+    uint32_t g = p.g0 + threadIdx.x;
+    f32x4 nxt_lo = f32x4{0.f, 0.f, 0.f, 0.f}, nxt_hi = nxt_lo;
+    if (g < g_end) {
+        nxt_lo = load_stream(in + 2 * g);
+        nxt_hi = load_stream(in + 2 * g + 1);
+    }
+#pragma unroll 1
+    while (g < g_end) {
+        const f32x4 a_lo = nxt_lo, a_hi = nxt_hi;
+        const uint32_t g_next = g + kGenThreadsSmall;
+        if (g_next < g_end) {
+            nxt_lo = load_stream(in + 2 * g_next);
+            nxt_hi = load_stream(in + 2 * g_next + 1);
+        }
+        const float a[8] = {a_lo.x, a_lo.y, a_lo.z, a_lo.w, a_hi.x, a_hi.y, a_hi.z, a_hi.w};
+        const NormalBase nb = normal_base(bd, g * 8);
+#pragma unroll 1
+        for (uint32_t j = 0; j < unit_jobs; ++j) {
+            const SimArgs& A = unit[j].A;
+            const SimBlock B = sim_block<kBlock>(A, p.block, p.s, p.c, bd);
+            float v[8];
+            benign8<true, kBlock>(B.benign, bd, nb, g * 8, a, a, v);
+            uint32_t e0 = g * 8;
+            asm volatile("" : "+v"(e0));  // the flip draws are formed here, not kept for all runs
+            if (B.mal) tamper8(A, B, nb, e0, a, v);
+            store_stream(global_ptr(reinterpret_cast<u32x4*>(unit[j].h + p.block * n)) + g,
+                         pack_half8(v));
+        }
+        g = g_next;
+    }
+}
+
 // Batched live pass: the jobs' chunks form one iteration range walked by
 // one grid, group by group (batch_iter).  An iteration is one chunk of a unit
-// of the group's runs: together where none of them tampers with the block
-// (benign_chunk_jobs), else run by run, each exactly as the single-run launch
-// generates it.  The units of a larger group are walked chunk-major, so its
+// of the group's runs.  Student-t: run by run within a group of elements
+// (t3_chunk_jobs); Gaussian: together where none of the runs tampers with the
+// block (benign_chunk_jobs), else run by run over the chunk.  Every run's output
+// is exactly what the single-run launch generates.  The units of a larger group are walked chunk-major, so its
 // later units find the chunk in L2.  A malicious block costs up to 2.5 times a
 // benign one, so the chunks go round the XCDs one by one: with a contiguous
 // eighth per XCD, the XCD that holds the malicious shard of 16 finishes last
@@ -317,22 +369,27 @@ __global__ __launch_bounds__(kGenThreadsSmall) void canary_sim_batch_kernel(
         uint64_t chunk;
         if (!batch_iter<false>(groups, n_groups, it, &first, &unit_jobs, &chunk)) continue;
         const SimJobDev* __restrict__ unit = jobs + first;
-        bool together = unit_jobs > 1;
         const SimArgs& A0 = unit[0].A;
         const ChunkPos p = chunk_pos(chunk, A0.chunks_per_block, A0.C, A0.chunk_groups);
-        for (uint32_t j = 0; j < unit_jobs; ++j)
-            together = together && !((unit[j].A.mal_mask >> p.s) & 1u);
-        static_assert(kSimJobsPerIter <= 4, "one case per unit size");
-        if (!together) {
-#pragma unroll 1
-            for (uint32_t j = 0; j < unit_jobs; ++j)
-                sim_chunk<kT3, kBlock, false, kGenThreadsSmall>(unit[j].A, chunk, unit[j].ref, unit[j].h);
-        } else if (unit_jobs == 4) {
-            benign_chunk_jobs<kT3, kBlock, 4>(unit, p);
-        } else if (unit_jobs == 3) {
-            benign_chunk_jobs<kT3, kBlock, 3>(unit, p);
+        if constexpr (kT3) {
+            t3_chunk_jobs<kBlock>(unit, unit_jobs, p);
         } else {
-            benign_chunk_jobs<kT3, kBlock, 2>(unit, p);
+            bool together = unit_jobs > 1;
+            for (uint32_t j = 0; j < unit_jobs; ++j)
+                together = together && !((unit[j].A.mal_mask >> p.s) & 1u);
+            static_assert(kSimJobsPerIter <= 4, "one case per unit size");
+            if (!together) {
+#pragma unroll 1
+                for (uint32_t j = 0; j < unit_jobs; ++j)
+                    sim_chunk<false, kBlock, false, kGenThreadsSmall>(unit[j].A, chunk,
+                                                                      unit[j].ref, unit[j].h);
+            } else if (unit_jobs == 4) {
+                benign_chunk_jobs<kBlock, 4>(unit, p);
+            } else if (unit_jobs == 3) {
+                benign_chunk_jobs<kBlock, 3>(unit, p);
+            } else {
+                benign_chunk_jobs<kBlock, 2>(unit, p);
+            }
         }
     }
 }

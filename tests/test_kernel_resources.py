@@ -23,3 +23,12 @@ def test_fp16_reference_loads_in_flight(found, metric, sums):
     sums and an address."""
     for name, k in _named(found, f"DriftMetricE{metric}E", "drift_", "EEvPKtPKv").items():
         assert k["vgpr_count"] >= 16 * 4 + 2 * sums + 2, (name, k["vgpr_count"])
+
+
+def test_batched_live_pass_keeps_to_registers(found):
+    """Neither form of the batched live pass keeps its runs' values in LDS or
+    scratch, where the compiler puts an array that a loop it did not unroll
+    indexes."""
+    for name, k in _named(found, "canary_sim_batch_kernel").items():
+        assert k["group_segment_fixed_size"] == 0, (name, k)
+        assert k["private_segment_fixed_size"] == 0, (name, k)
