@@ -117,21 +117,15 @@ struct SimBlock {
 // Block `block` = s * C + c of shard s and canary c (of this call's C).
 template <bool kBlock>
 __device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block, uint32_t s,
-                                              uint32_t c, const BlockDraw& draw) {
+                                              uint32_t c) {
     SimBlock B;
     B.s = s;
     B.c = A.canary_base + c;
     B.mal = (A.mal_mask >> B.s) & 1u;
     B.benign = benign_run<kBlock>(A, block);
     B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[block] : 0.0f;
-    B.draw = draw;
+    B.draw = block_draw(A.key, B.c, B.s);
     return B;
-}
-
-template <bool kBlock>
-__device__ __forceinline__ SimBlock sim_block(const SimArgs& A, uint64_t block, uint32_t s,
-                                              uint32_t c) {
-    return sim_block<kBlock>(A, block, s, c, block_draw(A.key, A.canary_base + c, s));
 }
 
 template <bool kBlock>
@@ -201,8 +195,7 @@ __device__ __forceinline__ void benign8(const BenignRun& R, const BlockDraw& bd,
 }
 
 // x + y as one instruction with its operands in this order: where both are
-// NaN the sum is the first, and the compiler, free to swap them, does so in
-// some of the kernels that must agree bit for bit.
+// NaN the sum is the first.
 __device__ __forceinline__ float add_ordered(float x, float y) {
     float r;
     asm("v_add_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
@@ -211,6 +204,12 @@ __device__ __forceinline__ float add_ordered(float x, float y) {
 
 // Eq. 3: the tampering of a malicious shard, in place on v (which holds the
 // benign output; the clean base replaces it by the noise-free base first).
+// The kernels agree bit for bit on NaN too, so each takes the noise as the
+// first operand of the Gaussian tamper's addition.  Where A.clean becomes a
+// select the compiler does so by itself; kOrdered is for where it does not
+// (set everywhere it made no kernel faster, and the exact-norm chain of 24 x 8
+// x 64 x 4096 under block noise 97.0 us, not 92.9).
+template <bool kOrdered = false>
 __device__ __forceinline__ void tamper8(const SimArgs& A, const SimBlock& B, const NormalBase& nb,
                                         uint32_t e0, const float base[8], float v[8]) {
     if (A.clean) {
@@ -221,7 +220,12 @@ __device__ __forceinline__ void tamper8(const SimArgs& A, const SimBlock& B, con
         float zt[8];
         normals8(B.draw, nb, A.tag_add, zt);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = add_ordered(B.tsc * zt[k], v[k]);
+        for (int k = 0; k < 8; ++k) {
+            if constexpr (kOrdered)
+                v[k] = add_ordered(B.tsc * zt[k], v[k]);
+            else
+                v[k] = v[k] + B.tsc * zt[k];
+        }
     }
     if (A.tamper & 2u) {
         const Words4 u0 = finish_draw(B.draw, draw_base(B.draw, e0 >> 2), A.tag_flip);

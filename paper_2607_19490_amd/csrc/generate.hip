@@ -335,12 +335,18 @@ __device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit
 #pragma unroll 1
         for (uint32_t j = 0; j < unit_jobs; ++j) {
             const SimArgs& A = unit[j].A;
-            const SimBlock B = sim_block<kBlock>(A, p.block, p.s, p.c, bd);
+            SimBlock B;
+            B.s = p.s;
+            B.c = A.canary_base + p.c;
+            B.mal = (A.mal_mask >> p.s) & 1u;
+            B.benign = benign_run<kBlock>(A, p.block);
+            B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[p.block] : 0.0f;
+            B.draw = bd;
             float v[8];
             benign8<true, kBlock>(B.benign, bd, nb, g * 8, a, a, v);
             uint32_t e0 = g * 8;
             asm volatile("" : "+v"(e0));  // the flip draws are formed here, not kept for all runs
-            if (B.mal) tamper8(A, B, nb, e0, a, v);
+            if (B.mal) tamper8<true>(A, B, nb, e0, a, v);
             store_stream(global_ptr(reinterpret_cast<u32x4*>(unit[j].h + p.block * n)) + g,
                          pack_half8(v));
         }
