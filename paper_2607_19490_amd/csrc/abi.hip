@@ -533,8 +533,8 @@ int plan_drift_batch(const char* fn, uint32_t n_jobs, const cdt_drift_job* jobs,
     }
     plan->groups.resize(nt);
     uint32_t ng = 0;
-    plan->total_iters = cdt::plan_batch_groups(nt, keys.data(),
-                                               cdt::kDriftJobsPerIter, plan->groups.data(), &ng);
+    cdt::group_batch_jobs(nt, keys.data(), cdt::kDriftJobsPerIter, plan->groups.data(), &ng);
+    plan->total_iters = cdt::place_batch_groups(plan->groups.data(), ng);
     plan->groups.resize(ng);
     if (plan->total_blocks > kMaxBlocks * 16)
         return fail(CDT_ELIMIT, "%s: the batch holds too many blocks", fn);

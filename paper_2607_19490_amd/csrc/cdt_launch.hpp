@@ -121,10 +121,12 @@ struct BatchKey {
 // launch whose units alternate between 4 jobs and 2 keeps some CUs on the
 // long ones (six runs of the 12 x 100 x 48 x 768 shape: 427 us for the live
 // pass, Eq. 4 and the ranking with 4 + 2, 377 us with 3 + 3).  Jobs whose
-// random counters differ in more than the tag are not put into one unit.
-// Fills groups[0 .. *n_groups) and returns the padded iteration count.
-inline uint64_t plan_batch_groups(uint32_t n_jobs, const BatchKey* keys, uint32_t max_jobs,
-                                  BatchGroupDev* groups, uint32_t* n_groups) {
+// random counters differ in more than the tag are not put into one unit: a
+// group that holds another seed or canary range than its first job's is taken
+// apart, every job a unit of its own.  Fills groups[0 .. *n_groups) but for
+// their iterations (place_batch_groups).
+inline void group_batch_jobs(uint32_t n_jobs, const BatchKey* keys, uint32_t max_jobs,
+                             BatchGroupDev* groups, uint32_t* n_groups) {
     *n_groups = 0;
     for (uint32_t j = 0; j < n_jobs; ++j) {
         if (*n_groups) {
@@ -146,15 +148,73 @@ inline uint64_t plan_batch_groups(uint32_t n_jobs, const BatchKey* keys, uint32_
         g.jobs_per_iter = max_jobs;
         groups[(*n_groups)++] = g;
     }
-    uint64_t total = 0;
     for (uint32_t k = 0; k < *n_groups; ++k) {
         BatchGroupDev& g = groups[k];
         g.units = (g.n_jobs + g.jobs_per_iter - 1) / g.jobs_per_iter;
         g.jobs_per_iter = (g.n_jobs + g.units - 1) / g.units;
+    }
+}
+
+// The groups' iterations one after another; returns the padded iteration count.
+inline uint64_t place_batch_groups(BatchGroupDev* groups, uint32_t n_groups) {
+    uint64_t total = 0;
+    for (uint32_t k = 0; k < n_groups; ++k) {
+        BatchGroupDev& g = groups[k];
         g.iter_begin = total;
         total += (g.chunks + kXcds - 1) / kXcds * kXcds * g.units;
     }
     return total;
+}
+
+// How a live pass's work is cut: threads per workgroup and 8-element groups
+// per chunk.
+struct GenShape {
+    uint32_t threads, chunk_groups;
+    uint64_t cpb;  // chunks per block
+};
+
+// 256-thread chunks of as many groups per thread (up to kGenItems) as leave
+// 4096 workgroups, cut evenly within a block of n8 groups.  Fewer groups
+// where the launch is small fill the chip (Student-t, 12 x 30 x 48 x 768:
+// 88 us with Eq. 4 and the ranking, 102 us in 8192-group chunks).  Where a
+// workgroup generates `runs` = 3 or 4 runs over its chunk, 2048 of them will do,
+// and the chunks of a block are the evenest of up to twice as many: a unit of
+// four 12 x 30 x 48 x 768 runs takes 46 us Gaussian and 155 us Student-t, 55
+// and 181 us in the chunks of a single run (six rounds, not three); leaving 4096
+// is faster there (146 us) and slower on 12 x 100 (512 against 482 us).
+inline GenShape gen_shape(uint64_t n8, uint64_t all_groups, uint32_t runs = 1) {
+    constexpr uint64_t kT = kGenThreadsSmall;
+    uint64_t items = all_groups / (kT * (runs > 2 ? 2048u * runs : 4096u));
+    items = items < 1 ? 1 : items > kGenItems ? kGenItems : items;
+    uint64_t cpb = (n8 + kT * items - 1) / (kT * items);
+    if (runs > 2) {
+        const uint64_t rounds = (n8 + kT - 1) / kT, most = 2 * cpb;
+        uint64_t least_idle = ~0ull;
+        for (uint64_t c = cpb; c < most && c <= rounds; ++c) {
+            const uint64_t idle = (rounds + c - 1) / c * c - rounds;
+            if (idle < least_idle) {
+                least_idle = idle;
+                cpb = c;
+            }
+        }
+    }
+    const uint64_t per = (n8 + cpb - 1) / cpb;
+    GenShape g;
+    g.threads = kT;
+    g.chunk_groups = static_cast<uint32_t>((per + kT - 1) / kT * kT);
+    g.cpb = (n8 + g.chunk_groups - 1) / g.chunk_groups;
+    return g;
+}
+
+// Most runs of a unit of a batched live pass over all_groups groups (of all
+// jobs): as many as leave 1024 workgroups of one group per thread.  The runs of
+// a unit share loads and the first rounds of their draws, but follow one
+// another in its threads: four 4 x 8 x 16 x 256 runs (256 workgroups apart) take
+// 6.8 us apart and 11.8 us together, Student-t 8.5 and 17.6 us; six of 4 x 32 x
+// 16 x 512 (3072) 13.0 and 11.8 us, Student-t 24.6 and 23.7 us.
+inline uint32_t sim_unit_runs(uint64_t all_groups) {
+    const uint64_t fill = all_groups / (kGenThreadsSmall * 1024u);
+    return fill < 1 ? 1 : fill > kSimJobsPerIter ? kSimJobsPerIter : static_cast<uint32_t>(fill);
 }
 
 // Batched live pass over runs of one noise distribution and mode, carry 0:

@@ -296,20 +296,20 @@ __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ 
     }
 }
 
-// One chunk of a unit of Student-t runs over one reference: the runs one after
-// another within each group of 8 elements, by one body for every run count,
-// tampered blocks included.  A group of a run is about 1000 instructions, so
-// what it needs can come from the table each time, where the four-fold
-// unrolled form was 62 KB of code, which the compiler unrolled by two only and
-// kept its runs' values in LDS.  12 KB, no LDS, 106 VGPRs (the runs share the
-// first rounds of all their draws but the flips'; 74 VGPRs, sharing those of
-// the one-normal streams alone, are up to 2% slower at large shapes).  Four
-// runs with one malicious shard, against the unrolled form: 4 x 32 x 16 x 512
-// 21.7 against 35.1 us, 12 x 100 x 48 x 768 484 against 493 us, 16 x 64 x 128 x
-// 8192 10.9 against 11.5 ms; every shard malicious 14.0 against 14.8 ms there.
+// One chunk of a unit of Student-t runs over one reference, the runs one after
+// another within each group of 8 elements: one body for every run count, with
+// the tampering of the runs that tamper.  What a run needs comes from the table
+// each time: a group of a run is about 1000 instructions; unrolled over four
+// runs that was 62 KB of code, which the compiler unrolled by two only and kept
+// the runs' values in LDS.  12 KB, no LDS, 106 VGPRs (the runs share the first
+// rounds of all their draws but the flips'; 74 VGPRs, sharing those of the
+// one-normal streams alone, are up to 2% slower at large shapes).  Four runs
+// with one malicious shard, against the unrolled form: 4 x 32 x 16 x 512 21.7
+// against 35.1 us, 12 x 100 x 48 x 768 484 against 493 us, 16 x 64 x 128 x 8192
+// 10.9 against 11.5 ms.
 template <bool kBlock>
 __device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit,
-                                               uint32_t unit_jobs, const ChunkPos& p) {
+                                              uint32_t unit_jobs, const ChunkPos& p) {
     const SimArgs& A0 = unit[0].A;
     const uint64_t n = static_cast<uint64_t>(A0.n8) * 8;
     const uint32_t g_end = min(p.g0 + A0.chunk_groups, A0.n8);
@@ -359,8 +359,9 @@ __device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit
 // of the group's runs.  Student-t: run by run within a group of elements
 // (t3_chunk_jobs); Gaussian: together where none of the runs tampers with the
 // block (benign_chunk_jobs), else run by run over the chunk.  Every run's output
-// is exactly what the single-run launch generates.  The units of a larger group are walked chunk-major, so its
-// later units find the chunk in L2.  A malicious block costs up to 2.5 times a
+// is exactly what the single-run launch generates.  The
+// units of a larger group are walked chunk-major, so its later units find the
+// chunk in L2.  A malicious block costs up to 2.5 times a
 // benign one, so the chunks go round the XCDs one by one: with a contiguous
 // eighth per XCD, the XCD that holds the malicious shard of 16 finishes last
 // (the step of three 16 x 128 x 256 x 8192 runs: 16.0 ms against 18.1 ms;
@@ -438,30 +439,6 @@ __global__ __launch_bounds__(kThreads) void canary_chain_kernel(SimArgs A, uint3
             }
         }
     }
-}
-
-// How a live pass's work is cut: threads per workgroup and 8-element groups
-// per chunk.
-struct GenShape {
-    uint32_t threads, chunk_groups;
-    uint64_t cpb;  // chunks per block
-};
-
-// 256-thread chunks of as many groups per thread (up to kGenItems) as leave
-// 4096 workgroups, cut evenly within a block of n8 groups.  Fewer groups
-// where the launch is small fill the chip (Student-t, 12 x 30 x 48 x 768:
-// 88 us with Eq. 4 and the ranking, 102 us in 8192-group chunks).
-inline GenShape gen_shape(uint64_t n8, uint64_t all_groups) {
-    constexpr uint64_t kT = kGenThreadsSmall;
-    uint64_t items = all_groups / (kT * 4096);
-    items = items < 1 ? 1 : items > kGenItems ? kGenItems : items;
-    const uint64_t cpb = (n8 + kT * items - 1) / (kT * items);
-    const uint64_t per = (n8 + cpb - 1) / cpb;
-    GenShape g;
-    g.threads = kT;
-    g.chunk_groups = static_cast<uint32_t>((per + kT - 1) / kT * kT);
-    g.cpb = (n8 + g.chunk_groups - 1) / g.chunk_groups;
-    return g;
 }
 
 // The single-run Gaussian pass is half bound by its mixed read and write
@@ -636,13 +613,12 @@ hipError_t launch_canary_sim_batch(uint32_t n_jobs, const SimLaunch* runs,
         if (n8 == 0 || nblocks == 0) continue;
         t3 = p.benign_dist == 1;
         block_mode = p.benign_mode == 1;
-        const GenShape g = gen_shape(n8, all_groups);
         SimJobDev d;
-        d.A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
+        d.A = make_sim_args(p, 0, 0, 0);  // its chunks: below, from its group's units
         d.ref = refs[j];
         d.h = hs[j];
         jobs.push_back(d);
-        keys.push_back(BatchKey{refs[j], g.cpb * nblocks, p.S, p.C, static_cast<uint32_t>(n8), p.seed,
+        keys.push_back(BatchKey{refs[j], 0, p.S, p.C, static_cast<uint32_t>(n8), p.seed,
                                 p.canary_base});
     }
     if (jobs.empty()) return hipSuccess;
@@ -651,8 +627,19 @@ hipError_t launch_canary_sim_batch(uint32_t n_jobs, const SimLaunch* runs,
     std::vector<char> staged(goff + n * sizeof(BatchGroupDev), 0);
     BatchGroupDev* groups = reinterpret_cast<BatchGroupDev*>(staged.data() + goff);
     uint32_t n_groups = 0;
-    const uint64_t total = plan_batch_groups(n, keys.data(), kSimJobsPerIter,
-                                             groups, &n_groups);
+    group_batch_jobs(n, keys.data(), sim_unit_runs(all_groups), groups, &n_groups);
+    for (uint32_t k = 0; k < n_groups; ++k) {
+        BatchGroupDev& G = groups[k];
+        const BatchKey& key = keys[G.first_job];
+        const GenShape g = gen_shape(key.n8, all_groups, G.jobs_per_iter);
+        G.chunks = g.cpb * key.S * key.C;
+        for (uint32_t j = G.first_job; j < G.first_job + G.n_jobs; ++j) {
+            jobs[j].A.chunk_groups = g.chunk_groups;
+            jobs[j].A.chunks_per_block = g.cpb;
+            jobs[j].A.total_chunks = G.chunks;
+        }
+    }
+    const uint64_t total = place_batch_groups(groups, n_groups);
     memcpy(staged.data(), jobs.data(), n * sizeof(SimJobDev));
     const size_t bytes = goff + n_groups * sizeof(BatchGroupDev);
     hipError_t e = hipMemcpyAsync(table, staged.data(), bytes, hipMemcpyHostToDevice, st);

@@ -352,3 +352,32 @@ def test_canary_sim_batch_units(gpu, shape, dist, mode):
     want = oracle.canary_sim(ref.cpu().numpy(), tscale=ts.cpu().numpy(), bscale=bs.cpu().numpy(),
                              **kw_o)
     np.testing.assert_array_equal(h_bits(h), want)
+
+
+# Large enough for units of two to four runs, and with eight runs for chunks of
+# more than one group per thread; blocks end inside a round of a chunk.  The
+# reference and with it the scales hold infinities and NaN.
+@pytest.mark.parametrize("dist,mode", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_canary_sim_batch_units_of_large_batches(gpu, dist, mode):
+    torch, cdt = gpu
+    announce(f"canary_sim_batch large units dist={dist} mode={mode}")
+    shape = S, C, T, H = 16, 8, 33, 1032
+    ref = torch.randn(shape, generator=torch.Generator("cuda").manual_seed(5), device="cuda")
+    specials = torch.tensor([np.inf, -np.inf, np.nan, 1e30, -7e4, 1e-40, 0.0, -0.0])
+    ref.view(-1)[::65521][:64] = specials.repeat(8).cuda()
+    q, m = cdt.ref_stats(ref)
+    ts, bs = cdt.block_scales(q, m, T, H, 0.05, 1e-2)
+    for n_runs, odd in ((2, None), (3, None), (4, None), (5, None), (8, None), (4, "seed")):
+        jobs = []
+        for j in range(n_runs):
+            kw = dict(seed=0x123456789ABC, cfg_id=30 + j, sigma_b=1e-2, benign_dist=dist,
+                      benign_mode=mode, mal_mask=1 << (S - 1 if j % 3 else S // 2),
+                      tamper=(1, 2, 4, 7)[j % 4], tscale=ts, bscale=bs, flip_p=0.25, scale=1.5)
+            if odd and j == n_runs - 1:
+                kw[odd] = 77
+            jobs.append((ref, torch.empty(shape, dtype=torch.float16, device="cuda"), kw))
+        cdt.canary_sim_batch(jobs)
+        for j, (_, h, kw) in enumerate(jobs):
+            one = cdt.canary_sim(ref, **kw)
+            torch.cuda.synchronize()
+            assert torch.equal(h.view(torch.int16), one.view(torch.int16)), (n_runs, odd, j)
