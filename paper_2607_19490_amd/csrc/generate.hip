@@ -296,10 +296,12 @@ __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ 
     }
 }
 
-// One chunk of a unit of Student-t runs over one reference, the runs one after
-// another within each group of 8 elements: one body for every run count, with
-// the tampering of the runs that tamper.  What a run needs comes from the table
-// each time: a group of a run is about 1000 instructions; unrolled over four
+// One chunk of a unit of runs over one reference, the runs one after another
+// within each group of 8 elements: one body for every run count, with the
+// tampering of the runs that tamper.  What a run needs comes from the table each
+// time.
+//
+// Student-t: a group of a run is about 1000 instructions; unrolled over four
 // runs that was 62 KB of code, which the compiler unrolled by two only and kept
 // the runs' values in LDS.  12 KB, no LDS, 106 VGPRs (the runs share the first
 // rounds of all their draws but the flips'; 74 VGPRs, sharing those of the
@@ -307,9 +309,16 @@ __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ 
 // with one malicious shard, against the unrolled form: 4 x 32 x 16 x 512 21.7
 // against 35.1 us, 12 x 100 x 48 x 768 484 against 493 us, 16 x 64 x 128 x 8192
 // 10.9 against 11.5 ms.
-template <bool kBlock>
-__device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit,
-                                              uint32_t unit_jobs, const ChunkPos& p) {
+//
+// Gaussian, where a run of the unit tampers with the block, against run by run
+// over the chunk: four runs with every shard malicious, 8 x 32 x 32 x 512 31.3
+// against 34.9 us, 16 x 64 x 128 x 8192 6.38 against 6.87 ms; with one shard in
+// eight 18.8 against 18.9 us.  A unit of one run is better off with sim_chunk,
+// which keeps its values in registers (24 runs of 16 x 32 x 64 x 4096 that share
+// no unit 2.56 against 2.67 ms).
+template <bool kT3, bool kBlock>
+__device__ __forceinline__ void sim_chunk_jobs(const SimJobDev* __restrict__ unit,
+                                               uint32_t unit_jobs, const ChunkPos& p) {
     const SimArgs& A0 = unit[0].A;
     const uint64_t n = static_cast<uint64_t>(A0.n8) * 8;
     const uint32_t g_end = min(p.g0 + A0.chunk_groups, A0.n8);
@@ -343,7 +352,7 @@ __device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit
             B.tsc = (B.mal && (A.tamper & 1u)) ? A.tscale[p.block] : 0.0f;
             B.draw = bd;
             float v[8];
-            benign8<true, kBlock>(B.benign, bd, nb, g * 8, a, a, v);
+            benign8<kT3, kBlock>(B.benign, bd, nb, g * 8, a, a, v);
             uint32_t e0 = g * 8;
             asm volatile("" : "+v"(e0));  // the flip draws are formed here, not kept for all runs
             if (B.mal) tamper8<true>(A, B, nb, e0, a, v);
@@ -356,10 +365,9 @@ __device__ __forceinline__ void t3_chunk_jobs(const SimJobDev* __restrict__ unit
 
 // Batched live pass: the jobs' chunks form one iteration range walked by
 // one grid, group by group (batch_iter).  An iteration is one chunk of a unit
-// of the group's runs.  Student-t: run by run within a group of elements
-// (t3_chunk_jobs); Gaussian: together where none of the runs tampers with the
-// block (benign_chunk_jobs), else run by run over the chunk.  Every run's output
-// is exactly what the single-run launch generates.  The
+// of the group's runs: Gaussian ones together where none of them tampers with
+// the block (benign_chunk_jobs), else run by run within a group of elements
+// (sim_chunk_jobs), each exactly as the single-run launch generates it.  The
 // units of a larger group are walked chunk-major, so its later units find the
 // chunk in L2.  A malicious block costs up to 2.5 times a
 // benign one, so the chunks go round the XCDs one by one: with a contiguous
@@ -379,17 +387,17 @@ __global__ __launch_bounds__(kGenThreadsSmall) void canary_sim_batch_kernel(
         const SimArgs& A0 = unit[0].A;
         const ChunkPos p = chunk_pos(chunk, A0.chunks_per_block, A0.C, A0.chunk_groups);
         if constexpr (kT3) {
-            t3_chunk_jobs<kBlock>(unit, unit_jobs, p);
+            sim_chunk_jobs<kT3, kBlock>(unit, unit_jobs, p);
         } else {
-            bool together = unit_jobs > 1;
+            bool together = true;
             for (uint32_t j = 0; j < unit_jobs; ++j)
                 together = together && !((unit[j].A.mal_mask >> p.s) & 1u);
             static_assert(kSimJobsPerIter <= 4, "one case per unit size");
-            if (!together) {
-#pragma unroll 1
-                for (uint32_t j = 0; j < unit_jobs; ++j)
-                    sim_chunk<false, kBlock, false, kGenThreadsSmall>(unit[j].A, chunk,
-                                                                      unit[j].ref, unit[j].h);
+            if (unit_jobs == 1) {
+                sim_chunk<kT3, kBlock, false, kGenThreadsSmall>(unit[0].A, chunk, unit[0].ref,
+                                                                unit[0].h);
+            } else if (!together) {
+                sim_chunk_jobs<kT3, kBlock>(unit, unit_jobs, p);
             } else if (unit_jobs == 4) {
                 benign_chunk_jobs<kBlock, 4>(unit, p);
             } else if (unit_jobs == 3) {
