@@ -129,9 +129,15 @@ __device__ __forceinline__ ChunkPos chunk_pos(uint64_t chunk, uint64_t chunks_pe
 // store instruction covers one contiguous 1 KB run, and a quad's channel moves
 // by a constant from round to round.  Together with ref_stats on the 8 x 64 x
 // 128 x 4096 shape (nontemporal stores move the write-back of dirty lines from
-// its reads to these writes): 371 us with outlier_gain, 385 us with ordinary
-// stores; 1024-thread chunks 390 us; 16 x 64 x 256 x 8192 2.86 ms (3.17 ms with
-// whole groups per lane, a division per group and the ranking above).
+// its reads to these writes): 367 us, 380 us with ordinary stores; 16 x 64 x
+// 256 x 8192 2.88 ms (3.00 ms with whole groups per lane and a division per
+// group).  kLines: every block starts on a 64-byte boundary.  Where one does
+// not, the runs end inside lines, and nontemporal stores write those in parts:
+// 10 x 75 x 97 x 1288 98 us with them, 82 us with ordinary stores, 16 x 64 x 255
+// x 8200 2.16 against 1.76 ms; at 64 bytes (10 x 75 x 97 x 1296) 79.8 against
+// 81.6 us.  The chunks of a block are even: 12 x 100 x 48 x 768 39.0 us, 41.0 us
+// with two of eight rounds and one of two; 16 x 64 x 33 x 1048 30.3 against 33.1
+// us.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ f32x4 synth_quad(const BlockDraw& bd, uint32_t tag_key, uint32_t quad,
                                             const f32x4& g) {
@@ -143,27 +149,37 @@ __device__ __forceinline__ f32x4 synth_quad(const BlockDraw& bd, uint32_t tag_ke
 
 constexpr int kSynthThreads = 256, kSynthItems = 8;
 constexpr uint32_t kSynthChunkGroups = kSynthThreads * kSynthItems;
+template <bool kLines, typename P, typename V>
+__device__ __forceinline__ void store_synth(P p, V v) {
+    if constexpr (kLines)
+        store_stream(p, v);
+    else
+        *p = v;
+}
+
+template <bool kLines>
 __global__ __launch_bounds__(kSynthThreads) void ref_synth_kernel(
     uint32_t C, uint32_t canary_base, uint32_t H, uint32_t n8, uint64_t chunks_per_block,
-    uint64_t total_chunks, Key key, uint32_t tag, const float* __restrict__ gain,
-    float* __restrict__ ref) {
+    uint32_t chunk_groups, uint64_t total_chunks, Key key, uint32_t tag,
+    const float* __restrict__ gain, float* __restrict__ ref) {
     const uint64_t n = static_cast<uint64_t>(n8) * 8;
     const uint32_t h4 = H / 4, step = 2 * kSynthThreads % h4;  // quads of a row, of a round
     const uint32_t lane = threadIdx.x % kWave, wave0 = threadIdx.x - lane;
     const f32x4* gq = reinterpret_cast<const f32x4*>(gain);
     for (uint64_t it = blockIdx.x; it < total_chunks; it += gridDim.x) {
         const ChunkPos p = chunk_pos(xcd_contiguous(it, total_chunks), chunks_per_block, C,
-                                     kSynthChunkGroups);
+                                     chunk_groups);
         f32x4* out = reinterpret_cast<f32x4*>(ref + p.block * n);
         const BlockDraw bd = block_draw(key, canary_base + p.c, p.s);
-        const uint32_t n4 = 2 * n8, q_end = min(2 * (p.g0 + kSynthChunkGroups), n4);
+        const uint32_t n4 = 2 * n8, q_end = min(2 * (p.g0 + chunk_groups), n4);
         uint32_t q0 = 2 * (p.g0 + wave0) + lane;
         uint32_t j0 = q0 % h4, j1 = (q0 + kWave) % h4;
 #pragma unroll 1
         for (; q0 < q_end; q0 += 2 * kSynthThreads) {
             const uint32_t q1 = q0 + kWave;
-            store_stream(out + q0, synth_quad(bd, tag ^ key.k1, q0, gq[j0]));
-            if (q1 < q_end) store_stream(out + q1, synth_quad(bd, tag ^ key.k1, q1, gq[j1]));
+            store_synth<kLines>(out + q0, synth_quad(bd, tag ^ key.k1, q0, gq[j0]));
+            if (q1 < q_end)
+                store_synth<kLines>(out + q1, synth_quad(bd, tag ^ key.k1, q1, gq[j1]));
             j0 += step;
             j0 -= j0 >= h4 ? h4 : 0u;
             j1 += step;
@@ -508,10 +524,17 @@ hipError_t launch_ref_synth(uint32_t S, uint32_t C, uint32_t T, uint32_t H, uint
     const uint32_t n8 = static_cast<uint32_t>(n / 8);
     const uint64_t cpb = (n8 + kSynthChunkGroups - 1) / kSynthChunkGroups;
     const uint64_t total = cpb * nblocks;
-    hipLaunchKernelGGL(ref_synth_kernel, dim3(gen_grid(total)), dim3(kSynthThreads), 0, st, C,
-                       canary_base, H, n8, cpb, total,
-                       Key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)},
-                       stream_tag(kStreamRef, ref_set_id), gain, ref);
+    const uint32_t chunk_groups = static_cast<uint32_t>(
+        ((n8 + cpb - 1) / cpb + kSynthThreads - 1) / kSynthThreads * kSynthThreads);
+    const Key key{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32)};
+    const dim3 grid(gen_grid(total)), block(kSynthThreads);
+    const uint32_t tag = stream_tag(kStreamRef, ref_set_id);
+    if (n8 % 2 == 0 && reinterpret_cast<uintptr_t>(ref) % 64 == 0)
+        hipLaunchKernelGGL(ref_synth_kernel<true>, grid, block, 0, st, C, canary_base, H, n8, cpb,
+                           chunk_groups, total, key, tag, gain, ref);
+    else
+        hipLaunchKernelGGL(ref_synth_kernel<false>, grid, block, 0, st, C, canary_base, H, n8,
+                           cpb, chunk_groups, total, key, tag, gain, ref);
     return hipGetLastError();
 }
 

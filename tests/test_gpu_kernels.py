@@ -546,6 +546,24 @@ def test_ref_synth_rows(gpu, shape):
 # Host tables either side of what travels in a launch's arguments (32
 # configurations): the counts of an uploaded table, the oracle's per-canary
 # ones, and the table left in the workspace.
+# Blocks of an odd and an even number of groups (32 bytes each), of one chunk,
+# of two even ones and of two with a ragged end, in arrays that start 16, 32 and
+# 64 bytes into their buffer.
+@pytest.mark.parametrize("skip", [4, 8, 16])
+@pytest.mark.parametrize("shape", [(2, 3, 5, 8), (3, 2, 6, 8), (2, 2, 4, 8192), (2, 2, 3, 6160)])
+def test_ref_synth_alignment(gpu, shape, skip):
+    torch, cdt = gpu
+    announce(f"ref_synth {shape} skip={skip}")
+    S, C, T, H = shape
+    gain = oracle.outlier_gain(H, max(1, H // 100), 20.0, 3, 2)
+    buf = torch.full((S * C * T * H + 32,), 7.0, device="cuda")
+    out = buf[skip:skip + S * C * T * H].view(shape)
+    cdt.ref_synth(S, C, T, H, 3, 2, to_dev(torch, gain), out)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(out.cpu().numpy(), oracle.ref_synth(S, C, T, H, 3, 2, gain))
+    assert bool((buf[:skip] == 7.0).all()) and bool((buf[skip + out.numel():] == 7.0).all())
+
+
 @pytest.mark.parametrize("n", [1, 31, 32, 33])
 def test_auroc_host_table_sizes(gpu, n):
     torch, cdt = gpu
