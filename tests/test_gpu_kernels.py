@@ -532,6 +532,25 @@ def test_outlier_gain_counts(gpu, H):
                                           oracle.outlier_gain(H, n_out, 20.0, seed, 5))
 
 
+# Two channels whose words are equal at the place of the last outlier: the lower
+# one alone is an outlier with n_out of them, both with one more.
+@pytest.mark.parametrize("seed,n_out,low,high", [(39, 13623, 5577, 8904),
+                                                 (12, 16942, 21032, 26105),
+                                                 (35, 28664, 11053, 19718)])
+def test_outlier_gain_ties(gpu, seed, n_out, low, high):
+    torch, cdt = gpu
+    H, tag = 32768, 8 << 24 | 5  # CDT_STREAM_OUTLIER, ref_set_id
+    words = [oracle.philox([j, 0, 0, tag], [seed, 0])[0] for j in (low, high)]
+    assert words[0] == words[1]
+    announce(f"outlier gain tie seed={seed} n_out={n_out}")
+    for n in (n_out - 1, n_out, n_out + 1):
+        want = oracle.outlier_gain(H, n, 20.0, seed, 5)
+        assert (want[low], want[high]) == ((1.0, 1.0), (20.0, 1.0), (20.0, 20.0))[n - n_out + 1]
+        got = cdt.outlier_gain(H, n, 20.0, seed, 5)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("shape", [(2, 3, 5, 8), (3, 1, 257, 16), (1, 2, 9, 1016), (2, 2, 3, 6152)])
 def test_ref_synth_rows(gpu, shape):
     torch, cdt = gpu
