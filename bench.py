@@ -13,7 +13,10 @@ Default workload: Llama-70B-shaped, 16 shards x 256 canaries x 256 tokens x
 hidden 8192 (48 GiB of activations), three runs: additive Gaussian eps 0.05,
 sign flip of 0.1% of elements, uniform rescale by 1.05.
 
-Prints one JSON line:
+Prints one JSON line of the contract's keys, under 2000 characters
+(result_line): the metric, the roofline, the detection rates, the sweep's rate
+and the CPU oracle's.  The whole result goes to stderr as one line, "[bench]
+result: {...}" (with --sweep-only, the sweep alone on stdout):
   value          drift-scored activation bytes (2 B fp16 + 4 B fp32 per
                  element and run, 4 B per block score) per second of the
                  whole step;
@@ -1166,6 +1169,24 @@ def cpu_baseline(W, args):
     }
 
 
+CONTRACT_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+                 "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config",
+                 "roofline")
+LINE_PARTS = {"canary_sim": ("avg_launch_ms", "GBps"), "detection": None,
+              "sweep": ("configs_per_s",),
+              "cpu_baseline": ("value", "unit", "cores", "kind", "sample")}
+
+
+def result_line(res):
+    """The line printed on stdout: what reads it may keep only its last 2000
+    characters."""
+    line = {k: res[k] for k in CONTRACT_KEYS}
+    for key, parts in LINE_PARTS.items():
+        if key in res:
+            line[key] = res[key] if parts is None else {p: res[key][p] for p in parts}
+    return json.dumps(line)
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -1210,7 +1231,8 @@ def main():
     if not args.no_cpu_baseline:
         log("cpu baseline (oracle)")
         res["cpu_baseline"] = cpu_baseline(W, args)
-    print(json.dumps(res), flush=True)
+    log("result: " + json.dumps(res))
+    print(result_line(res), flush=True)
 
 
 if __name__ == "__main__":

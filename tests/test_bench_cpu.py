@@ -54,3 +54,27 @@ def test_cpu_baseline_fields_on_tiny():
     cb = bench.cpu_baseline(W, args)
     assert cb["kind"] == "oracle" and cb["unit"] == "GB/s" and cb["cores"] >= 1
     assert cb["value"] > 0 and isinstance(cb["sample"], str) and cb["sample"]
+
+
+def test_printed_line_is_whole_in_its_last_2000_characters():
+    """Every section of a full result is far longer than what the line takes of
+    it."""
+    import json
+
+    res = {k: 123456.7891 for k in bench.CONTRACT_KEYS}
+    res["config"] = {"workload": "llama70b", "shape_SxCxTxH": [16, 256, 256, 8192],
+                     "runs": ["add0.05", "flip0.001", "scale1.05"], "inputs": "x" * 60,
+                     "step": "x" * 105}
+    res["roofline"] = dict({f"figure_{i:02d}_per_launch": 51547224581.25 for i in range(13)},
+                           kernel="x" * 90)
+    res["detection"] = {"add0.05": 1.0, "flip0.001": 1.0, "scale1.05": 1.0}
+    res["canary_sim"] = {"avg_launch_ms": 20.1234, "GBps": 5123.1, "alu_roofline": {"x": "x" * 900}}
+    res["sweep"] = {"configs_per_s": 12345.6, "per_set": ["x" * 90] * 9}
+    res["cpu_baseline"] = {"value": 2.1, "unit": "GB/s", "cores": 16, "kind": "oracle",
+                           "sample": "x" * 130, "other_rows": ["x" * 90] * 9}
+    res["substudies"] = ["x" * 90] * 40
+    line = bench.result_line(res)
+    assert len(line) < 2000 and "\n" not in line
+    back = json.loads(line)
+    assert all(back[k] == res[k] for k in bench.CONTRACT_KEYS)
+    assert back["cpu_baseline"]["value"] == 2.1 and back["sweep"] == {"configs_per_s": 12345.6}
