@@ -173,6 +173,20 @@ struct GenShape {
     uint64_t cpb;  // chunks per block
 };
 
+// The number of chunks from cpb on, below twice as many, that leaves the fewest
+// rounds of a block's chunks idle.
+inline uint64_t evenest_cut(uint64_t rounds, uint64_t cpb) {
+    uint64_t best = cpb, least_idle = ~0ull;
+    for (uint64_t c = cpb; c < 2 * cpb && c <= rounds; ++c) {
+        const uint64_t idle = (rounds + c - 1) / c * c - rounds;
+        if (idle < least_idle) {
+            least_idle = idle;
+            best = c;
+        }
+    }
+    return best;
+}
+
 // 256-thread chunks of as many groups per thread (up to kGenItems) as leave
 // 4096 workgroups, cut evenly within a block of n8 groups.  Fewer groups
 // where the launch is small fill the chip (Student-t, 12 x 30 x 48 x 768:
@@ -187,17 +201,7 @@ inline GenShape gen_shape(uint64_t n8, uint64_t all_groups, uint32_t runs = 1) {
     uint64_t items = all_groups / (kT * (runs > 2 ? 2048u * runs : 4096u));
     items = items < 1 ? 1 : items > kGenItems ? kGenItems : items;
     uint64_t cpb = (n8 + kT * items - 1) / (kT * items);
-    if (runs > 2) {
-        const uint64_t rounds = (n8 + kT - 1) / kT, most = 2 * cpb;
-        uint64_t least_idle = ~0ull;
-        for (uint64_t c = cpb; c < most && c <= rounds; ++c) {
-            const uint64_t idle = (rounds + c - 1) / c * c - rounds;
-            if (idle < least_idle) {
-                least_idle = idle;
-                cpb = c;
-            }
-        }
-    }
+    if (runs > 2) cpb = evenest_cut((n8 + kT - 1) / kT, cpb);
     const uint64_t per = (n8 + cpb - 1) / cpb;
     GenShape g;
     g.threads = kT;

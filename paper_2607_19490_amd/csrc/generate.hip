@@ -465,35 +465,53 @@ __global__ __launch_bounds__(kThreads) void canary_chain_kernel(SimArgs A, uint3
     }
 }
 
-// The single-run Gaussian pass is half bound by its mixed read and write
-// stream, which longer chunks serve better once the array is large: 1024 x 8
-// against 256 x 8 on 16 x 64 x 256 x 8192 takes 4.24 against 4.32 ms (live
-// pass and Eq. 4), the same on 8 x 64 x 128 x 4096 (0.56 ms), and fills the
-// chip worse below that (8 x 16 x 47 x 1032: 57 against 54 us).  The Student-t
-// pass and the batched passes are bound by their arithmetic and take 256
-// threads at every size (four Student-t runs of the 8 x 64 x 128 x 4096 shape:
-// 3.25 against 3.51 ms).
-inline GenShape gen_shape_single(uint64_t n8, uint64_t nblocks, bool t3) {
-    if (t3 || n8 * nblocks < (1ull << 22)) return gen_shape(n8, n8 * nblocks);
+// 1024-thread chunks of up to kGenItems groups per thread, cut evenly (16 x 40 x
+// 2048-element blocks of a 64-canary run, 10 rounds: 83 us, 105 us as 8 and 2).
+inline GenShape gen_shape_large(uint64_t n8) {
     GenShape g;
     g.threads = kGenThreads;
-    g.chunk_groups = kGenChunkGroups;
-    g.cpb = (n8 + kGenChunkGroups - 1) / kGenChunkGroups;
+    const uint64_t cpb = evenest_cut((n8 + kGenThreads - 1) / kGenThreads,
+                                     (n8 + kGenChunkGroups - 1) / kGenChunkGroups);
+    const uint64_t per = (n8 + cpb - 1) / cpb;
+    g.chunk_groups =
+        static_cast<uint32_t>((per + kGenThreads - 1) / kGenThreads * kGenThreads);
+    g.cpb = (n8 + g.chunk_groups - 1) / g.chunk_groups;
     return g;
 }
 
+// The single-run Gaussian pass is half bound by its mixed read and write
+// stream, which longer chunks serve better once the array is large, and fills
+// the chip worse below that (8 x 16 x 47 x 1032: 57 against 54 us).  256 against
+// 1024 threads, live pass alone:
+//   without tampering  2^22 groups in blocks of 8192  32.7  31.6 us
+//                      2^22.4 in blocks of 4608       43.9  41.8 us
+//                      2^22 in blocks of 512          34.0  50.4 us
+//                      2^26 in blocks of 131072       592   571 us
+//                      2^25 in blocks of 4096         293   301 us
+//   one shard of 8 under all three tampers, whose chunks cost up to 2.5 times
+//   the others'        2^22 in blocks of 8192         35.3  44.5 us
+//                      2^23 in blocks of 16384        69.5  72.2 us
+//                      2^24 in blocks of 16384        155   157 us
+//                      2^26 in blocks of 131072       629   621 us
+// The Student-t pass and the batched passes are bound by their arithmetic and
+// take 256 threads at every size (four Student-t runs of the 8 x 64 x 128 x 4096
+// shape: 3.25 against 3.51 ms).
+inline GenShape gen_shape_single(uint64_t n8, uint64_t nblocks, bool t3, bool tampers) {
+    const uint64_t all = n8 * nblocks, large = 1ull << 24;
+    if (t3 || all < (tampers ? large : large / 4) || n8 < kGenChunkGroups / (all < large ? 2 : 1))
+        return gen_shape(n8, all);
+    return gen_shape_large(n8);
+}
+
 // The propagation pass has C canaries of n8 groups (S stages each) to spread:
-// 256 threads until that fills 1024-thread chunks well (live pass, scales, Eq. 4
-// and ranking, 256 against 1024 threads: 8 x 128 x 16 x 4096 187 against 242 us,
-// 8 x 64 x 64 x 4096 397 against 373 us, 8 x 64 x 128 x 4096 757 against 744 us).
+// 256 threads until that fills 1024-thread chunks well, and where blocks are no
+// whole number of them (live pass alone, 256 against 1024 threads: 8 x 128 x 128
+// x 1024 188 against 163 us, 16 x 64 x 64 x 4096 346 against 329 us; 8 x 64 x 257
+// x 1024 179 against 186 us, 32 x 256 x 65 x 2048 1.35 against 1.60 ms).
 // The Student-t variant needs more than the 128 registers that 1024 threads leave.
 inline GenShape gen_shape_chain(uint64_t n8, uint64_t C, bool t3) {
-    if (t3 || n8 * C < (1ull << 21)) return gen_shape(n8, n8 * C);
-    GenShape g;
-    g.threads = kGenThreads;
-    g.chunk_groups = kGenChunkGroups;
-    g.cpb = (n8 + kGenChunkGroups - 1) / kGenChunkGroups;
-    return g;
+    if (t3 || n8 % kGenChunkGroups || n8 * C < (1ull << 21)) return gen_shape(n8, n8 * C);
+    return gen_shape_large(n8);
 }
 
 // Grid for a chunked elementwise walk: 64 workgroups per CU; larger jobs
@@ -576,25 +594,26 @@ hipError_t launch_canary_chain(const SimLaunch& p, const float* ref, uint16_t* h
     return launch_chain_t<false, false>(p, ref, h, st);
 }
 
-template <bool kT3, bool kBlock, int kThreads>
+template <bool kT3, bool kBlock, bool kStream, int kThreads>
 void launch_sim_k(const SimArgs& A, const float* ref, uint16_t* h, hipStream_t st) {
-    hipLaunchKernelGGL((canary_sim_kernel<kT3, kBlock, false, kThreads>),
+    hipLaunchKernelGGL((canary_sim_kernel<kT3, kBlock, kStream, kThreads>),
                        dim3(gen_grid(A.total_chunks)), dim3(kThreads), 0, st, A, ref, h);
 }
 
-template <bool kT3, bool kBlock>
+template <bool kT3, bool kBlock, bool kStream = false>
 hipError_t launch_sim_t(const SimLaunch& p, const float* ref, uint16_t* h, hipStream_t st) {
     const uint64_t n8 = static_cast<uint64_t>(p.T) * p.H / 8;
     const uint64_t nblocks = static_cast<uint64_t>(p.S) * p.C;
-    const GenShape g = gen_shape_single(n8, nblocks, kT3);
+    const uint64_t shards = p.S >= 64 ? ~0ull : (1ull << p.S) - 1;
+    const GenShape g = gen_shape_single(n8, nblocks, kT3, p.tamper && (p.mal_mask & shards));
     const SimArgs A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
     if constexpr (!kT3) {
         if (g.threads == kGenThreads) {
-            launch_sim_k<kT3, kBlock, kGenThreads>(A, ref, h, st);
+            launch_sim_k<kT3, kBlock, kStream, kGenThreads>(A, ref, h, st);
             return hipGetLastError();
         }
     }
-    launch_sim_k<kT3, kBlock, kGenThreadsSmall>(A, ref, h, st);
+    launch_sim_k<kT3, kBlock, kStream, kGenThreadsSmall>(A, ref, h, st);
     return hipGetLastError();
 }
 
@@ -699,16 +718,7 @@ hipError_t launch_canary_sim_stream(uint32_t S, uint32_t C, uint32_t T, uint32_t
     p.C = C;
     p.T = T;
     p.H = H;
-    const GenShape g = gen_shape_single(n8, nblocks, false);
-    const SimArgs A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
-    const dim3 grid(gen_grid(A.total_chunks));
-    if (g.threads == kGenThreads)
-        hipLaunchKernelGGL((canary_sim_kernel<false, false, true, kGenThreads>), grid,
-                           dim3(kGenThreads), 0, st, A, ref, h);
-    else
-        hipLaunchKernelGGL((canary_sim_kernel<false, false, true, kGenThreadsSmall>), grid,
-                           dim3(kGenThreadsSmall), 0, st, A, ref, h);
-    return hipGetLastError();
+    return launch_sim_t<false, false, true>(p, ref, h, st);
 }
 
 }  // namespace cdt

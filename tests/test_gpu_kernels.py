@@ -532,6 +532,27 @@ def test_outlier_gain_counts(gpu, H):
                                           oracle.outlier_gain(H, n_out, 20.0, seed, 5))
 
 
+# The single-run pass over arrays of its large cuts against slices of a few
+# canaries, which take the small ones: blocks just above a 1024-thread chunk's
+# 8192 groups.
+@pytest.mark.parametrize("mal", [0, 0b101])
+@pytest.mark.parametrize("shape", [(16, 128, 65, 1024), (8, 64, 65, 1024)])
+def test_canary_sim_of_a_large_array_equals_its_slices(gpu, shape, mal):
+    torch, cdt = gpu
+    announce(f"canary_sim large {shape} mal={mal}")
+    S, C, T, H = shape
+    ref = torch.empty(shape, device="cuda").normal_(
+        generator=torch.Generator("cuda").manual_seed(3))
+    kw = dict(seed=11, cfg_id=9, sigma_b=1e-3, mal_mask=mal, tamper=7 if mal else 0,
+              flip_p=0.25, scale=1.5)
+    ts = torch.full((S, C), 0.5, device="cuda")
+    h = cdt.canary_sim(ref, tscale=ts, **kw)
+    for c in range(0, C, 4):
+        part = cdt.canary_sim(ref[:, c:c + 4].contiguous(), tscale=ts[:, c:c + 4].contiguous(),
+                              canary_base=c, **kw)
+        assert torch.equal(h[:, c:c + 4].view(torch.int16), part.view(torch.int16)), c
+
+
 # Two channels whose words are equal at the place of the last outlier: the lower
 # one alone is an outlier with n_out of them, both with one more.
 @pytest.mark.parametrize("seed,n_out,low,high", [(39, 13623, 5577, 8904),
