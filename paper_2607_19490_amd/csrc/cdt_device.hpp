@@ -22,6 +22,21 @@ __device__ __forceinline__ uint64_t xcd_contiguous(uint64_t it, uint64_t total) 
     return x * base + (x < rem ? x : rem) + local;
 }
 
+// Iteration `it` of `total` chunks, `per_shard` of them to a shard -> its chunk:
+// XCD it % 8 walks one contiguous eighth of each shard, shard by shard.  What an
+// uneven eighth leaves of the shards comes last.
+__host__ __device__ __forceinline__ uint64_t shard_eighths(uint64_t it, uint64_t total,
+                                                           uint64_t per_shard) {
+    const uint64_t eighth = per_shard / kXcds, rest = per_shard % kXcds;
+    const uint64_t even = total / per_shard * (eighth * kXcds);
+    if (it < even) {
+        const uint64_t x = it % kXcds, l = it / kXcds, s = l / eighth;
+        return s * per_shard + x * eighth + (l - s * eighth);
+    }
+    const uint64_t l = it - even, s = l / rest;
+    return s * per_shard + eighth * kXcds + (l - s * rest);
+}
+
 // Native 16-byte vectors (usable with the nontemporal load/store builtins).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -254,12 +254,18 @@ __device__ __forceinline__ void sim_chunk(const SimArgs& A, uint64_t chunk,
 
 // Chunks go round the XCDs one by one (see canary_sim_batch_kernel; with five
 // shards, one of them under all three tampers, 1.42 ms against 1.69 ms for a
-// 5 x 64 x 256 x 8192 run and its Eq. 4).
-template <bool kT3, bool kBlock, bool kStream, int kThreads>
+// 5 x 64 x 256 x 8192 run and its Eq. 4).  Over the largest arrays each XCD is
+// better off in one place (walks_shard_eighths), with kEighths in its own
+// instantiation: the index arithmetic takes eight more VGPRs.
+template <bool kT3, bool kBlock, bool kStream, int kThreads, bool kEighths>
 __global__ __launch_bounds__(kThreads) void canary_sim_kernel(
     SimArgs A, const float* __restrict__ ref, uint16_t* __restrict__ h) {
-    for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x)
-        sim_chunk<kT3, kBlock, kStream, kThreads>(A, it, ref, h);
+    for (uint64_t it = blockIdx.x; it < A.total_chunks; it += gridDim.x) {
+        uint64_t chunk = it;
+        if constexpr (kEighths)
+            chunk = shard_eighths(it, A.total_chunks, A.chunks_per_block * A.C);
+        sim_chunk<kT3, kBlock, kStream, kThreads>(A, chunk, ref, h);
+    }
 }
 
 // One chunk of a unit of kJ Gaussian runs over one reference, in a block that
@@ -503,6 +509,14 @@ inline GenShape gen_shape_single(uint64_t n8, uint64_t nblocks, bool t3, bool ta
     return gen_shape_large(n8);
 }
 
+// Above 2^28 groups (8 GiB of references) the single-run pass takes the chunks
+// in each shard's eighths, one to an XCD: 16 x 256 x 256 x 8192 9.7 ms benign and
+// 9.8 ms with a shard under all three tampers, 9.9 and 10.1 ms with the chunks
+// round the XCDs (the XCDs' one eighth of the array each, which leaves the
+// malicious shard to two of them: 9.6 and 10.9 ms).  Below, the chunks round the
+// XCDs are as good or better: 16 x 64 x 128 x 4096 577 against 591 us.
+inline bool walks_shard_eighths(uint64_t all_groups) { return all_groups > (1ull << 28); }
+
 // The propagation pass has C canaries of n8 groups (S stages each) to spread:
 // 256 threads until that fills 1024-thread chunks well, and where blocks are no
 // whole number of them (live pass alone, 256 against 1024 threads: 8 x 128 x 128
@@ -594,9 +608,9 @@ hipError_t launch_canary_chain(const SimLaunch& p, const float* ref, uint16_t* h
     return launch_chain_t<false, false>(p, ref, h, st);
 }
 
-template <bool kT3, bool kBlock, bool kStream, int kThreads>
+template <bool kT3, bool kBlock, bool kStream, int kThreads, bool kEighths>
 void launch_sim_k(const SimArgs& A, const float* ref, uint16_t* h, hipStream_t st) {
-    hipLaunchKernelGGL((canary_sim_kernel<kT3, kBlock, kStream, kThreads>),
+    hipLaunchKernelGGL((canary_sim_kernel<kT3, kBlock, kStream, kThreads, kEighths>),
                        dim3(gen_grid(A.total_chunks)), dim3(kThreads), 0, st, A, ref, h);
 }
 
@@ -609,11 +623,14 @@ hipError_t launch_sim_t(const SimLaunch& p, const float* ref, uint16_t* h, hipSt
     const SimArgs A = make_sim_args(p, g.chunk_groups, g.cpb, g.cpb * nblocks);
     if constexpr (!kT3) {
         if (g.threads == kGenThreads) {
-            launch_sim_k<kT3, kBlock, kStream, kGenThreads>(A, ref, h, st);
+            if (walks_shard_eighths(n8 * nblocks))
+                launch_sim_k<kT3, kBlock, kStream, kGenThreads, true>(A, ref, h, st);
+            else
+                launch_sim_k<kT3, kBlock, kStream, kGenThreads, false>(A, ref, h, st);
             return hipGetLastError();
         }
     }
-    launch_sim_k<kT3, kBlock, kStream, kGenThreadsSmall>(A, ref, h, st);
+    launch_sim_k<kT3, kBlock, kStream, kGenThreadsSmall, false>(A, ref, h, st);
     return hipGetLastError();
 }
 

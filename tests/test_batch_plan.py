@@ -1,5 +1,5 @@
-"""How the batched live pass cuts its work, from the library's own host code
-compiled by itself (CPU only)."""
+"""How the live pass cuts and orders its work, from the library's own code
+compiled for the host by itself (CPU only)."""
 import ctypes
 import os
 import subprocess
@@ -9,8 +9,12 @@ import pytest
 from tests.conftest import ROOT
 
 SOURCE = """
+#include "cdt_device.hpp"
 #include "cdt_launch.hpp"
 #include <vector>
+extern "C" uint64_t eighths(uint64_t it, uint64_t total, uint64_t per_shard) {
+    return cdt::shard_eighths(it, total, per_shard);
+}
 // Workgroups of `runs` runs over one reference of `blocks` blocks of n8 groups.
 extern "C" uint64_t plan(uint32_t runs, uint32_t blocks, uint32_t n8, uint32_t* per_unit) {
     const uint64_t all = static_cast<uint64_t>(runs) * blocks * n8;
@@ -31,7 +35,7 @@ extern "C" uint64_t plan(uint32_t runs, uint32_t blocks, uint32_t n8, uint32_t* 
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def host(tmp_path_factory):
     hipcc = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
@@ -42,7 +46,12 @@ def plan(tmp_path_factory):
                     "-I", os.path.join(ROOT, "paper_2607_19490_amd", "csrc"),
                     "-I", os.path.join(ROOT, "include"), str(d / "plan.hip"), "-o", so],
                    check=True, capture_output=True)
-    fn = ctypes.CDLL(so).plan
+    return ctypes.CDLL(so)
+
+
+@pytest.fixture(scope="module")
+def plan(host):
+    fn = host.plan
     fn.argtypes = [ctypes.c_uint32] * 3 + [ctypes.POINTER(ctypes.c_uint32)]
     fn.restype = ctypes.c_uint64
 
@@ -68,3 +77,19 @@ def test_joint_runs_leave_the_chip_full(plan, blocks, n8):
         seen.add(per_unit)
     if blocks * n8 >= 1 << 20:  # large enough for units of every size
         assert seen == {1, 2, 3, 4}
+
+
+@pytest.mark.parametrize("shards", [1, 2, 16, 17])
+@pytest.mark.parametrize("per_shard", [1, 7, 8, 9, 24, 61, 64])
+def test_shard_eighths(host, shards, per_shard):
+    """Every chunk once; an XCD's chunks of a shard follow one another."""
+    fn = host.eighths
+    fn.argtypes, fn.restype = [ctypes.c_uint64] * 3, ctypes.c_uint64
+    total = shards * per_shard
+    order = [fn(it, total, per_shard) for it in range(total)]
+    assert sorted(order) == list(range(total))
+    eighth = per_shard // 8
+    for x in range(8):
+        mine = order[x:shards * eighth * 8:8]
+        assert mine == [s * per_shard + x * eighth + i for s in range(shards)
+                        for i in range(eighth)]

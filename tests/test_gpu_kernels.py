@@ -534,9 +534,10 @@ def test_outlier_gain_counts(gpu, H):
 
 # The single-run pass over arrays of its large cuts against slices of a few
 # canaries, which take the small ones: blocks just above a 1024-thread chunk's
-# 8192 groups.
+# 8192 groups, and the order of the largest arrays, with shards that do not
+# divide into eighths (61 canaries of 52 chunks).
 @pytest.mark.parametrize("mal", [0, 0b101])
-@pytest.mark.parametrize("shape", [(16, 128, 65, 1024), (8, 64, 65, 1024)])
+@pytest.mark.parametrize("shape", [(16, 128, 65, 1024), (8, 64, 65, 1024), (17, 61, 260, 8192)])
 def test_canary_sim_of_a_large_array_equals_its_slices(gpu, shape, mal):
     torch, cdt = gpu
     announce(f"canary_sim large {shape} mal={mal}")
