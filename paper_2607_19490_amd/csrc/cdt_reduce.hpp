@@ -2,8 +2,9 @@
 // live pass, the exact-norm tamper and the reference statistics): the
 // chunking constants, the workgroup sum and the per-element accumulation
 // of Eq. 4 and its cosine variant.  A block (shard, canary) of n = T*H
-// elements is cut into chunks of kReduceChunkElems; one workgroup reduces
-// one chunk to fp64 partial sums in a fixed order (no atomics); a combine
+// elements is cut into even chunks of at most kReduceChunkElems (reduce_shape);
+// kReduceThreads threads reduce a chunk to fp64 partial sums in a fixed order (no
+// atomics), in a workgroup of their own or beside a block's other chunk; a combine
 // kernel, or a workgroup that holds all of a block's chunks, adds them in
 // chunk order.
 #pragma once
@@ -69,17 +70,17 @@ constexpr int kWavesPerGroup = kReduceThreads / kWave;
 
 // Blocks of kReduceTeam chunks can be reduced by one workgroup of as many times
 // kReduceThreads threads, which does the combine's addition too: a launch less,
-// the same bits.  Eq. 4 takes it up to kTeamMostBlocks blocks (fp32 reference;
-// 8 x 64 x 64 x 1024 32.8 us, 35.0 us with the combine; 12 x 100 x 48 x 768 46.2
-// against 47.4 us, its fp16 reference 30.4 against 31.4 us): beyond, the launch
-// is a small part and workgroups that wait for their slower half cost more
-// (16 x 256 x 8 x 8192 241 against 240 us, 32 x 200 x 40 x 1024 229 against 226
-// us).  The exact-norm sums, which are bound by arithmetic, take it from
-// kTeamLeastBlocks on (12 x 100 x 48 x 768 62 against 64 us): fewer blocks do not
-// fill the CUs with workgroups twice the size (4 x 16 x 48 x 768 15.3 against
-// 11.5 us).
+// the same bits.  Eq. 4 takes it up to kTeamMostBlocks blocks (8 x 64 x 64 x 1024
+// 30.7 us, 33.2 us with the combine; 12 x 100 x 48 x 768 39.6 against 41.9 us, its
+// fp16 reference 27.1 against 29.0 us; 16 x 256 x 8 x 8192 230 against 235 us,
+// 32 x 200 x 40 x 1024 226 against 229 us): beyond, the launch is a small part and
+// workgroups that wait for their slower half cost as much (32 x 256 x 64 x 1024
+// 464 against 462 us).  The exact-norm sums, which are bound by arithmetic, take
+// it from kTeamLeastBlocks on (12 x 100 x 48 x 768 62 against 64 us): fewer blocks
+// do not fill the CUs with workgroups twice the size (4 x 16 x 48 x 768 15.3
+// against 11.5 us).
 constexpr int kReduceTeam = 2;
-constexpr uint64_t kTeamMostBlocks = 2048, kTeamLeastBlocks = 512;
+constexpr uint64_t kTeamMostBlocks = 6400, kTeamLeastBlocks = 512;
 
 // Sum kN per-thread values over a workgroup of kTeam chunks, kReduceThreads
 // threads each: every chunk's total as block_sum forms it, then the totals

@@ -4,8 +4,10 @@
 //
 // drift_score is bound by HBM bandwidth: 2 B of fp16 h plus 4 B of fp32 a
 // per element, each read exactly once.  Layout of the work:
-//   * a block of n = T*H elements is cut into chunks of kReduceChunkElems;
-//     one kReduceThreads-thread workgroup reduces one chunk;
+//   * a block of n = T*H elements is cut into even chunks of whole rounds, at
+//     most kReduceChunkElems elements each (reduce_shape); kReduceThreads
+//     threads reduce a chunk, in a workgroup of their own or, with two chunks
+//     a block, side by side in one (drift_team_kernel);
 //   * each thread streams groups of 8 elements (one 16-byte h load, two
 //     16-byte a loads), kReduceUnroll groups in flight before any use; the
 //     loads are nontemporal (read once, no reuse);
@@ -17,8 +19,8 @@
 //     (h - a is exact in fp64), so the partial sums carry no cancellation;
 //   * wave butterfly sums, then an LDS pass over the waves, give one
 //     (D, R) pair per chunk in a fixed order (no atomics);
-//   * a combine kernel adds a block's chunk partials in chunk order and
-//     forms m = sqrt(D / R).
+//   * a combine kernel, or the workgroup that holds a whole block, adds a
+//     block's chunk partials in chunk order and forms m = sqrt(D / R).
 #include <math.h>
 
 #include "cdt_device.hpp"
@@ -81,59 +83,55 @@ __device__ __forceinline__ uint32_t fold_group(const u32x4& hv, const u32x4& rv,
     return x;
 }
 
-// kReadOnly: the same chunks, loads and lane exchange with Eq. 4's
-// arithmetic replaced by an XOR fold of the loaded words: the rate the memory
-// system gives this access pattern, against which the drift kernel is judged.
-// direct (a block is one chunk): the chunk's sums are the block's, and the
-// score is written here; the combine launch is skipped (it would add the one
-// partial to zero, which changes nothing).
 // kU whole rounds of a chunk's kReduceThreads threads (tid of them, every
-// thread's group in range) from group `base` on: all loads first, then the sums.
+// thread's group in range) from group `base` on: all loads first, then the lane
+// exchange and the sums.  The barrier between them keeps it so: the compiler
+// otherwise waits for each round's loads before it issues the next round's.  With
+// it and without (Eq. 4): 12 x 100 x 48 x 768 39.8 against 45.9 us, 32 x 256 x 17
+// x 1000 120 against 134 us, 8 x 64 x 32 x 1024 16.8 against 23.8 us, 16 x 64 x 256 x
+// 8192 1.82 ms both; against an fp16 reference 16 x 256 x 8 x 8192 157 against
+// 163 us, 8 x 64 x 30 x 1024 10.4 against 15.2 us (8 x 64 x 65 x 1024, which seven
+// waves a SIMD suit better than four, 23.5 against 22.6 us).
 template <DriftMetric kM, bool kReadOnly, int kU>
 __device__ __forceinline__ void drift_rounds(gptr<const u32x4> hb, gptr<const f32x4> ab,
                                              gptr<const u32x4> rb, uint32_t base, uint32_t tid,
                                              double (&acc)[DriftTraits<kM>::kSums],
                                              uint32_t& fold) {
+    constexpr bool kHalf = DriftTraits<kM>::kHalfRef;
     u32x4 hv[kU], rv[kU];
-    f32x4 a0[kU], a1[kU];
+    f32x4 q0[kU], q1[kU];
     const uint32_t lane = tid % kWave, wave0 = tid - lane;
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
         const uint32_t g = base + u * kReduceThreads + tid;
         hv[u] = __builtin_nontemporal_load(hb + g);
-        rv[u] = u32x4{0u, 0u, 0u, 0u};
-        a0[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-        a1[u] = a0[u];
-        if constexpr (DriftTraits<kM>::kHalfRef) {
+        if constexpr (kHalf) {
             rv[u] = __builtin_nontemporal_load(rb + g);
         } else {
             const gptr<const f32x4> aw = ab + 2 * (base + u * kReduceThreads + wave0);
-            quads_to_groups(__builtin_nontemporal_load(aw + lane),
-                            __builtin_nontemporal_load(aw + kWave + lane), a0[u], a1[u]);
+            q0[u] = __builtin_nontemporal_load(aw + lane);
+            q1[u] = __builtin_nontemporal_load(aw + kWave + lane);
         }
     }
-    // Against an fp16 reference the compiler sinks each pair of loads to its
-    // sums otherwise (66 VGPRs, one pair in flight).  fp16-reference Eq. 4 and
-    // cosine, with the barrier and without: 16 x 256 x 8 x 8192 157 and 158
-    // against 163 and 166 us, 8 x 64 x 30 x 1024 10.4 and 10.4 against 15.2 and
-    // 17.1 us (8 x 64 x 65 x 1024, which seven waves a SIMD suit better than
-    // four, 23.5 and 24.0 against 22.6 and 22.9 us).
-    if constexpr (DriftTraits<kM>::kHalfRef) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
+        f32x4 a0 = f32x4{0.f, 0.f, 0.f, 0.f}, a1 = a0;
+        if constexpr (!kHalf) {
+            rv[u] = u32x4{0u, 0u, 0u, 0u};
+            quads_to_groups(q0[u], q1[u], a0, a1);
+        }
         if constexpr (kReadOnly)
-            fold ^= fold_group(hv[u], rv[u], a0[u], a1[u]);
+            fold ^= fold_group(hv[u], rv[u], a0, a1);
         else
-            accumulate8<kM>(hv[u], rv[u], a0[u], a1[u], acc);
+            accumulate8<kM>(hv[u], rv[u], a0, a1, acc);
     }
 }
 
 // One chunk of one block array: its partial sums (or, direct, its block's
 // score), in a fixed order: a thread's groups ascend, whatever the steps they
 // are loaded in.  Steps of kReduceUnroll rounds, then of 4, 2 and 1, then a
-// round that is not whole: only its lanes branch per load (all rounds of a
-// last step did, and every round against an fp16 reference).  118 VGPRs, four
-// waves per SIMD (136, three); 16 x 256 x 256 x 8192: 7.20 against 7.25 ms.
+// round that is not whole: only its lanes branch per load.
 // The batched form keeps one loop of predicated steps: cut the same way, the
 // compiler holds fewer of its loads in flight (158 VGPRs instead of 256) and
 // the 16 x 128 x 256 x 8192 step of three runs takes 17.8 ms, not 15.7.
@@ -193,6 +191,12 @@ __device__ __forceinline__ void drift_chunk_sums(const uint16_t* __restrict__ h,
     }
 }
 
+// kReadOnly: the same chunks, loads and lane exchange with Eq. 4's
+// arithmetic replaced by an XOR fold of the loaded words: the rate the memory
+// system gives this access pattern, against which the drift kernel is judged.
+// direct (a block is one chunk): the chunk's sums are the block's, and the
+// score is written here; the combine launch is skipped (it would add the one
+// partial to zero, which changes nothing).
 template <DriftMetric kM, bool kReadOnly>
 __device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
                                             const void* __restrict__ ref, uint32_t n8,
@@ -224,8 +228,13 @@ __device__ __forceinline__ void drift_chunk(const uint16_t* __restrict__ h,
     }
 }
 
+// Waves per SIMD that the registers of the 24 loads in flight must leave: 144
+// VGPRs without the bound, three waves (12 x 100 x 48 x 768 50 against 40 us).
+template <DriftMetric kM>
+constexpr int kDriftWaves = DriftTraits<kM>::kHalfRef ? 1 : 4;
+
 template <DriftMetric kM, bool kReadOnly = false>
-__global__ __launch_bounds__(kReduceThreads) void drift_partial_kernel(
+__global__ __launch_bounds__(kReduceThreads, kDriftWaves<kM>) void drift_partial_kernel(
     const uint16_t* __restrict__ h, const void* __restrict__ ref, uint32_t n8,
     uint64_t chunks_per_block, uint32_t chunk_groups, uint64_t total_chunks,
     double* __restrict__ partial, uint32_t S, uint32_t C, float* __restrict__ score,
@@ -239,7 +248,7 @@ __global__ __launch_bounds__(kReduceThreads) void drift_partial_kernel(
 // which adds their sums as the combine kernel would and writes the score: the
 // same bits without the combine launch.
 template <DriftMetric kM, int kTeam>
-__global__ __launch_bounds__(kReduceThreads* kTeam) void drift_team_kernel(
+__global__ __launch_bounds__(kReduceThreads* kTeam, kDriftWaves<kM>) void drift_team_kernel(
     const uint16_t* __restrict__ h, const void* __restrict__ ref, uint32_t n8,
     uint32_t chunk_groups, uint64_t nblocks, uint32_t S, uint32_t C, float* __restrict__ score,
     double* __restrict__ sums) {

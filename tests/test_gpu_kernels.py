@@ -669,3 +669,18 @@ def test_two_chunk_blocks_in_slices(gpu, TH):
             return ts, norms
         for a, b in zip(scale(512), scale(511)):
             assert torch.equal(a[:, :511], b)
+
+
+# The most blocks of two chunks that Eq. 4 reduces in one workgroup each, and one
+# more.
+def test_two_chunk_blocks_at_the_most_in_one_workgroup(gpu):
+    torch, cdt = gpu
+    announce("two-chunk blocks, 6400 and 6401")
+    C = 6401
+    ref = torch.randn((1, C, 17, 1928), generator=torch.Generator("cuda").manual_seed(9),
+                      device="cuda")
+    h = (ref * 1.001).half()
+    for fn, b in ((cdt.drift_score, ref), (cdt.cosine_score, ref),
+                  (cdt.drift_score_f16ref, (ref * 0.999).half())):
+        more, most = fn(h, b), fn(h[:, :C - 1], b[:, :C - 1])
+        assert torch.equal(more[:C - 1], most)

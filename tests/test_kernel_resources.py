@@ -2,7 +2,7 @@
 written: what a source line alone does not show (CPU only)."""
 import pytest
 
-from tests.kernel_resources import kernels
+from tests.kernel_resources import kernels, most_loads_without_a_wait
 
 
 @pytest.fixture(scope="module")
@@ -16,13 +16,17 @@ def _named(found, *parts):
     return sel
 
 
-@pytest.mark.parametrize("metric,sums", [(1, 2), (3, 3)], ids=["l2", "cosine"])
-def test_fp16_reference_loads_in_flight(found, metric, sums):
-    """Eq. 4 and the cosine against an fp16 reference load 8 groups of both
-    arrays before the first sum: 16 loads of 4 registers, beside the fp64
-    sums and an address."""
-    for name, k in _named(found, f"DriftMetricE{metric}E", "drift_", "EEvPKtPKv").items():
-        assert k["vgpr_count"] >= 16 * 4 + 2 * sums + 2, (name, k["vgpr_count"])
+@pytest.mark.parametrize("kernel", ["drift_partial_kernel", "drift_team_kernel"])
+@pytest.mark.parametrize("metric,loads", [(0, 24), (1, 16), (2, 24), (3, 16)],
+                         ids=["l2", "l2_f16", "cosine", "cosine_f16"])
+def test_block_reductions_load_a_step_before_its_sums(tmp_path, kernel, metric, loads):
+    """Eq. 4 and the cosine load 8 groups of a thread (16 bytes of activations
+    each, and 32 of an fp32 or 16 of an fp16 reference) before they wait for
+    the first."""
+    found = most_loads_without_a_wait(tmp_path, kernel)
+    runs = {k: v for k, v in found.items() if f"DriftMetricE{metric}E" in k}
+    assert runs
+    assert all(v >= loads for v in runs.values()), runs
 
 
 def test_batched_live_pass_keeps_to_registers(found):
