@@ -22,7 +22,8 @@
  *     NULL = the default stream).  The calls that take a HOST table
  *     (cdt_auroc, cdt_auroc_upload, cdt_auroc_canaries and the batched
  *     launches) copy it from library-held pageable memory, a copy that is
- *     complete when the call returns; nothing else waits on the host.
+ *     complete when the call returns, or pass a small one with the launch;
+ *     nothing else waits on the host.
  *   - Arguments are validated before any device work; on failure nothing is
  *     launched and an error code is returned.  cdt_last_error() gives a
  *     per-thread description of the last failure.
@@ -201,12 +202,11 @@ int cdt_canary_sim(uint32_t S, uint32_t C, uint32_t T, uint32_t H, const cdt_sim
  * from its ref with its own parameters, bitwise as cdt_canary_sim would.
  * The chunks of all jobs form one grid, so short runs share the launch's
  * ramp-up and tail.  Consecutive jobs that read the same ref array in the
- * same shape are generated together, so that each
- * reference chunk is read from HBM about once for all of them: with fewer
- * than 8 such jobs their work is walked chunk by chunk, the jobs of a chunk
- * one after another (re-reads from L2); with 8 or more, each XCD takes its
- * own jobs over the same reference offsets (re-reads from the last-level
- * cache).  Order the jobs so that runs sharing references are adjacent.
+ * same shape, with the same seed and canary_base, are generated together: up
+ * to 4 of them form a unit, whose chunks load each reference once, and the
+ * units of a chunk follow one another, so that the later ones find it in L2.
+ * Batches too small to fill the chip with such units are generated in smaller
+ * ones.  Order the jobs so that runs sharing references are adjacent.
  * Every job must use the same benign_dist and benign_mode and carry 0
  * (CDT_EINVAL otherwise); their shapes, tamper settings and scales may
  * differ.  jobs and each p: HOST, read during the call (the job and group
@@ -227,10 +227,10 @@ int cdt_canary_sim_batch(uint32_t n_jobs, const cdt_sim_job* jobs, void* ws, siz
 
 /* Measurement aid for the live pass's memory bound: reads ref and writes h
  * exactly as cdt_canary_sim does for Gaussian noise on independent stages
- * (the same chunks, loads, prefetch and stores), with the live-pass
- * arithmetic replaced by h = fp16_rne(a), no random numbers drawn.  Its rate
- * is what the memory system delivers for the live pass's 4 B-read and
- * 2 B-write access pattern.  Errors as cdt_canary_sim. */
+ * without tampering (the same chunks, loads, prefetch and stores), with the
+ * live-pass arithmetic replaced by h = fp16_rne(a), no random numbers drawn.
+ * Its rate is what the memory system delivers for the live pass's 4 B-read
+ * and 2 B-write access pattern.  Errors as cdt_canary_sim. */
 int cdt_canary_sim_stream(uint32_t S, uint32_t C, uint32_t T, uint32_t H, const float* ref,
                           uint16_t* h, void* stream);
 
@@ -406,7 +406,8 @@ typedef struct cdt_auroc_cfg {
 size_t cdt_auroc_workspace_bytes(uint32_t n_cfg);
 
 /* For each configuration g (cfgs: HOST array of n_cfg entries, validated and
- * copied into ws during the call, or by its kernel where n_cfg <= 32):
+ * copied into ws during the call, or, where n_cfg <= 32, by its kernel, so
+ * that the table in ws is there for later work on `stream` only):
  *   counts[g][0..2] = G, E, pairs with G = #{(t, i in M, j not in M):
  *       m_ti > m_tj}, E the ties (Eq. 5 summed over canaries; Eq. 6 as
  *       printed is G / pairs, the Mann-Whitney value (G + E/2) / pairs);
@@ -472,8 +473,10 @@ int cdt_auroc_values(uint32_t n_cfg, const uint64_t* counts, const uint64_t* poo
 /* Eq. 5 per canary: the counts behind each canary's A^(t) = G_t / (|M| |N|)
  * (Eq. 6 is their mean), the paper's per-canary view of the detector against
  * its controls (Section 4.5).  For configuration g of cfgs (HOST array,
- * validated exactly as cdt_auroc validates it and copied into ws during the
- * call, so a stream capture must not record it) and each of its canaries t:
+ * validated exactly as cdt_auroc validates it; where n_cfg <= 32 it travels
+ * with the launch and ws is not written, so a stream capture can record the
+ * call; else it is copied into ws during the call, which a capture must not
+ * record) and each of its canaries t:
  *   per_canary[o_g + t][0..1] = G_t, E_t: positive shard i beats / ties
  *       negative shard j, over that canary's pairs (i in M, j not in M);
  *   per_canary[o_g + t][2..3] = the same for the scrambled-label control
@@ -487,7 +490,7 @@ int cdt_auroc_values(uint32_t n_cfg, const uint64_t* counts, const uint64_t* poo
  * (CDT_AUROC_POOLED has no per-canary form: CDT_EINVAL).
  * per_canary: device uint32 [sum of C][6] (written, caller-owned).
  * ws: cdt_auroc_canaries_workspace_bytes(n_cfg) device bytes, 16-byte
- * aligned (the table and the canary offsets). */
+ * aligned (the table and the canary offsets), needed for every n_cfg. */
 size_t cdt_auroc_canaries_workspace_bytes(uint32_t n_cfg);
 int cdt_auroc_canaries(uint32_t n_cfg, const cdt_auroc_cfg* cfgs, const float* scores,
                        uint64_t n_scores, uint64_t seed, uint32_t flags, uint32_t* per_canary,

@@ -140,9 +140,11 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 // the 18 multiplies left per call, shared by every stream and run drawn at
 // the same q), and finish_draw does the rest: 16 multiplies, 14 three-operand
 // XORs and 4 two-operand ones (before: 18 and 19).  Same words as draw().
-// With irwin_hall4's subtraction the 16 x 128 x 256 x 8192 step of three runs
-// takes 18.6 ms (18.96 ms), a Student-t run of 16 x 128 x 128 x 4096 with its
-// Eq. 4 4.19 ms (4.31 ms), the fused pass of 32 x 32 x 64 x 8192 631 us (646).
+// Together with irwin_hall4's subtraction this took 1.9% off the step of three
+// 16 x 128 x 256 x 8192 runs (18.96 to 18.6 ms; 16.0 ms with what came after),
+// 2.8% off a Student-t run of 16 x 128 x 128 x 4096 with its Eq. 4 (4.31 to 4.19
+// ms; now 4.0) and 2.3% off the fused pass of 32 x 32 x 64 x 8192 (646 to 631
+// us; now 544).
 struct BlockDraw {
     uint32_t k0, k1;          // the key
     uint32_t z2, x2, z3, x3;  // hi(M0 x1) ^ k1, y1 ^ k0, w2 ^ k1 and k0 of rounds 1, 1, 2, 2

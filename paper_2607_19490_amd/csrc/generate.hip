@@ -272,9 +272,9 @@ __global__ __launch_bounds__(kThreads) void canary_sim_kernel(
 // none of them tampers with: each group of 8 references is loaded once, and the
 // part of its Philox calls that no run enters (normal_base: 2 of the 18
 // multiplies of a call) is formed once for all of them.  The runs share one
-// seed and canary range (plan_batch_groups).  What every group of a run needs
+// seed and canary range (group_batch_jobs).  What every group of a run needs
 // is held in scalar registers from the chunk's start (read from the table per
-// group, the sweep's step takes 6.0 ms).  60 VGPRs with four runs.
+// group, 24 runs of 16 x 32 x 64 x 4096 take 6.0 ms against 3.3 ms).
 template <bool kBlock, int kJ>
 __device__ __forceinline__ void benign_chunk_jobs(const SimJobDev* __restrict__ unit,
                                                   const ChunkPos& p) {
@@ -391,12 +391,12 @@ __device__ __forceinline__ void sim_chunk_jobs(const SimJobDev* __restrict__ uni
 // the block (benign_chunk_jobs), else run by run within a group of elements
 // (sim_chunk_jobs), each exactly as the single-run launch generates it.  The
 // units of a larger group are walked chunk-major, so its later units find the
-// chunk in L2.  A malicious block costs up to 2.5 times a
-// benign one, so the chunks go round the XCDs one by one: with a contiguous
-// eighth per XCD, the XCD that holds the malicious shard of 16 finishes last
-// (the step of three 16 x 128 x 256 x 8192 runs: 16.0 ms against 18.1 ms;
-// 18.5 ms with the runs generated apart, 19.3 ms at 18 multiplies a call).
-// With 24 runs of 16 x 32 x 64 x 4096 the step takes 3.3 ms (3.75 ms).
+// chunk in L2.  A malicious block costs up to 2.5 times a benign one, so the
+// chunks go round the XCDs one by one: with a contiguous eighth per XCD, the
+// XCD that holds the malicious shard of 16 finishes last (three 16 x 128 x 256
+// x 8192 runs with their scales and Eq. 4: 16.0 ms against 18.1 ms; 18.5 ms
+// with the runs generated apart, 19.3 ms at 18 multiplies a call).  24 runs of
+// 16 x 32 x 64 x 4096 so take 3.3 ms (3.75 ms).
 template <bool kT3, bool kBlock>
 __global__ __launch_bounds__(kGenThreadsSmall) void canary_sim_batch_kernel(
     const SimJobDev* __restrict__ jobs, const BatchGroupDev* __restrict__ groups,
